@@ -77,15 +77,19 @@ typedef struct pf_opts {
                                  core; the set-up picks the cheapest split, default 8 */
   int32_t factor_max_core;    /* largest dense Schur core, default 384 */
   /* feeder solve */
-  int32_t zbus_sparse;        /* 0: dense product Z r on the matrix cores (default); 1: Y_NN^-1 r
-                                 by level-scheduled solves with a sparse L D L^T of Y_NN (the
-                                 sparse variant named as future work in Sec. II-B) */
+  int32_t zbus_sparse;        /* how a feeder that is not a tree without shunts (see
+                                 pf_dist_network_create) forms Z r: 0: dense product on the matrix
+                                 cores (default); 1: Y_NN^-1 r by level-scheduled solves with a
+                                 sparse L D L^T of Y_NN (the sparse variant named as future work
+                                 in Sec. II-B).  On a tree Z r is a sum of segment voltages over
+                                 each path, in FP64, whatever this and `precision` say */
   int32_t zbus_async;         /* 0: the host reads each iteration's active count back and stops
                                  enqueuing once none is left, waiting one iteration behind the
                                  device (default); 1: all zbus_max_iter iterations are enqueued
                                  at once and exit on the device once no scenario is active, so
                                  the call returns without waiting (each exited iteration still
-                                 costs its two launches, about 3.6 us) */
+                                 costs its two launches, about 3.6 us).  A tree's solve is one
+                                 launch and never waits */
   /* transmission Newton step */
   int32_t nr_direct;          /* 0: preconditioned GMRES (default); 1: exact Newton step by a
                                  per-scenario sparse LU of J on a shared symbolic analysis (the
@@ -308,7 +312,11 @@ pf_status pf_dist_ybus_from_segments(int32_t n_bus, int32_t n_seg, const int32_t
  * delta_nodes[n_delta][3] (phase nodes a, b, c of each delta-loaded bus).
  * Computes the reduced impedance Z = inv(Y_NN) over the non-slack nodes N and
  * the no-load voltage v0 = -Z Y_NS v_S (Sec. II-B, eq. (10)) in FP64, keeps Z
- * in FP64 and FP32 on the device.  setup_opts may be null.
+ * in FP64 and FP32 on the device.  A tree without shunts (nodes 3 b, 3 b + 1,
+ * 3 b + 2 the phases of bus b, at most 1024 buses below the slack, symmetric
+ * segments, row sums of Ybus zero up to rounding, each delta load on one bus
+ * in phase order) needs no Z: its segments' 3x3 impedances are kept instead,
+ * and v0 is the slack voltage.  setup_opts may be null.
  * Errors: PF_INVALID_ARG, PF_SINGULAR_SETUP, PF_OUT_OF_MEMORY, PF_HIP_ERROR. */
 pf_status pf_dist_network_create(pf_context* ctx, int32_t n_node, int32_t nnz, const int32_t* row_ptr,
                                  const int32_t* col_idx, const double* y_re, const double* y_im,

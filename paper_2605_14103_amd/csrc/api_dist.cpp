@@ -137,8 +137,26 @@ pf_status pf_dist_solve(pf_dist_network* h, const pf_opts* opts, int32_t batch, 
     require(s_wye && s_delta && v_out && iters && converged, "null required pointer");
     activate(net->ctx);
     const hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
-    std::lock_guard<std::mutex> lk(net->order.mu);
     const bool mixed = o.precision == PF_MIXED;
+    ZbusLaunch a{};
+    a.batch = batch;
+    a.ld = ld;
+    a.s_wye = s_wye;
+    a.s_delta = s_delta;
+    a.v_out = v_out;
+    a.iters = iters;
+    a.converged = converged;
+    a.final_mismatch = final_mismatch;
+    a.sum_abs_change = sum_abs_change;
+    a.tol = o.tol;
+    a.max_iter = o.zbus_max_iter;
+    a.sparse = o.zbus_sparse;
+    a.async = o.zbus_async;
+    if (net->tree_nb > 0) {   // no workspace, so nothing to order
+      run_zbus(*net, mixed, a, hs);
+      return;
+    }
+    std::lock_guard<std::mutex> lk(net->order.mu);
     const int rows = (batch + ZB_BM - 1) / ZB_BM * ZB_BM;
     const size_t tsz = mixed ? sizeof(float) : sizeof(double);
     net->order.grow(net->ws_v, net->ctx, (size_t)batch * net->Kp * sizeof(double));
@@ -159,20 +177,6 @@ pf_status pf_dist_solve(pf_dist_network* h, const pf_opts* opts, int32_t batch, 
                             sizeof(int32_t) * (o.zbus_max_iter + 1), hipHostMallocDefault));
       net->count_host_len = o.zbus_max_iter + 1;
     }
-    ZbusLaunch a{};
-    a.batch = batch;
-    a.ld = ld;
-    a.s_wye = s_wye;
-    a.s_delta = s_delta;
-    a.v_out = v_out;
-    a.iters = iters;
-    a.converged = converged;
-    a.final_mismatch = final_mismatch;
-    a.sum_abs_change = sum_abs_change;
-    a.tol = o.tol;
-    a.max_iter = o.zbus_max_iter;
-    a.sparse = o.zbus_sparse;
-    a.async = o.zbus_async;
     a.v = net->ws_v.as<double>();
     a.r = net->ws_r.as<void>();
     a.st = net->ws_s.as<double>();

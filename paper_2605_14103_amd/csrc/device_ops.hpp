@@ -54,6 +54,47 @@ __device__ __forceinline__ double wave_total(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// v of lane `l` (constant), in every lane
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// row shift by N lanes, 0 into the lanes it does not reach
+template <int N>
+__device__ __forceinline__ double dpp_row_shr(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x110 + N, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(lo, lo, 0x110 + N, 0xf, 0xf, true));
+}
+
+// Inclusive prefix sum over the lanes of a wave: shifts by 1, 2, 4 and 8
+// within rows of 16, then the row broadcasts.
+__device__ __forceinline__ double wave_prefix(double v) {
+  v += dpp_row_shr<1>(v);
+  v += dpp_row_shr<2>(v);
+  v += dpp_row_shr<4>(v);
+  v += dpp_row_shr<8>(v);
+  v += dpp_d<0x142, 0xa>(v);  // row_bcast15 into rows 1 and 3
+  v += dpp_d<0x143, 0xc>(v);  // row_bcast31 into rows 2 and 3
+  return v;
+}
+
+// max over the wave of values that are not negative, NaN if any is (every lane gets it)
+__device__ __forceinline__ double wave_nanmax_pos(double v) {
+  const bool bad = __any(v != v);
+  v = __builtin_fmax(v, 0.0);
+  v = __builtin_fmax(v, dpp_d<0xB1, 0xf>(v));
+  v = __builtin_fmax(v, dpp_d<0x4E, 0xf>(v));
+  v = __builtin_fmax(v, dpp_d<0x141, 0xf>(v));
+  v = __builtin_fmax(v, dpp_d<0x140, 0xf>(v));
+  v = __builtin_fmax(v, dpp_d<0x142, 0xa>(v));
+  v = __builtin_fmax(v, dpp_d<0x143, 0xc>(v));
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+  return bad ? __builtin_nan("") : __hiloint2double(hi, lo);
+}
+
 // max that propagates NaN
 __device__ __forceinline__ double nanmax(double a, double b) {
   if (a != a) return a;

@@ -19,6 +19,26 @@
 
 namespace pfx {
 
+// A radial feeder without shunts as a tree of three-phase buses, for the
+// tree form of the iteration (zb_tree): every bus but the slack has a position
+// in depth-first preorder, so a bus's subtree is the positions q .. last(q).
+// Entering and leaving a bus are events e of the same traversal.
+struct TreeDev {
+  int nb, nbp;             // buses below the slack; rounded up to 64
+  const int4* bus;         // [nbp] x: caller's index of phase a | phases with a wye load << 24 |
+                           //       (delta load ? 1 << 27 : 0), y: free index of phase a,
+                           //       z: parent's position (-1: the slack), w: last(q)
+  const int4* link;        // [nbp] first eight children as 16-bit positions (0x8000: none)
+  const int2* rest;        // [nbp] x: first entry of the other children in `more`, y: their count
+  const int* more;
+  const int* kids;         // [nbp / 64] most children (up to eight) of a wave's buses
+  const int2* event;       // [nbp] events 2 q and 2 q + 1: position entered, or ~position left
+  const double2* y;        // [6][nbp] the segment above: admittance aa, bb, cc, ab, bc, ca
+  const double2* z;        // [6][nbp] and its inverse
+  int slack;               // caller's index of the slack's phase a
+  double v_slack[6];
+};
+
 // Free nodes are also grouped in slices of 64 (one wavefront) for the
 // residual kernel: nNs = nN rounded up to 64, and a thread of the residual's
 // workgroup owns nodes t + k * ZB_THREADS.
@@ -69,6 +89,9 @@ struct DistNetwork {
   DeviceBuffer W64, W32;   // Kp x Np real-block Z (Np = 2 nN rounded up to the N tile); W32
                            // row-major, W64 in K blocks of ZB_BK: (k, n) at
                            // ((k / ZB_BK) Np + n) ZB_BK + k % ZB_BK
+  // Tree form (nb > 0: the feeder is a tree of at most ZB_TREE_MAX buses, see build_tree)
+  int tree_nb = 0, tree_nbp = 0;
+  DeviceBuffer tr_bus, tr_link, tr_rest, tr_more, tr_kids, tr_event, tr_y, tr_z;
   DeviceBuffer slack_d;    // 3 slack node indices
   DeviceBuffer vslack_d;   // 6 doubles
   // workspaces (grow-only); calls on one network must not overlap
@@ -78,6 +101,7 @@ struct DistNetwork {
   int count_host_len = 0;
   ~DistNetwork();
   DistDev view() const;
+  TreeDev tree_view() const;
 };
 
 DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_t* row_ptr,
@@ -89,6 +113,7 @@ DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_
 // Residual workgroup size and GEMM tile sizes shared by the host sizing and
 // the kernels.
 constexpr int ZB_THREADS = 256;
+constexpr int ZB_TREE_MAX = 1024;   // buses of the tree form: one thread each
 constexpr int ZB_MAX_FREE = 4096;   // free nodes (the residual keeps v in LDS)
 constexpr int ZB_BM = 128;   // scenarios per tile
 constexpr int ZB_BN = 128;   // output reals per tile
@@ -126,7 +151,8 @@ struct ZbusLaunch {
   uint8_t* step_done;
 };
 
-// Runs the whole fixed point on `stream` (host loop over iterations).
+// Runs the whole fixed point on `stream`: one launch in the tree form,
+// otherwise a host loop over iterations.
 void run_zbus(DistNetwork& net, bool mixed, const ZbusLaunch& a, hipStream_t s);
 
 // Serving-engine pieces over the scenarios a.slots[0 .. a.batch): start them

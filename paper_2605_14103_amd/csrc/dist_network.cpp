@@ -1,6 +1,7 @@
 // Feeder registration: slack/non-slack split, reduced impedance matrix
 // Z = inv(Y_NN) and no-load voltage v0 = -Z Y_NS v_S (Sec. II-B, eq. (10)).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <complex>
 #include <map>
@@ -71,7 +72,172 @@ void invert_dense(std::vector<cplx>& A, int n) {
 
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
+// inverse of a symmetric 3x3 given as aa, bb, cc, ab, bc, ca, by its adjugate
+std::array<cplx, 6> invert_sym3(const std::array<cplx, 6>& m) {
+  const cplx a = m[0], b = m[1], c = m[2], d = m[3], e = m[4], f = m[5];
+  const cplx A = b * c - e * e, D = f * e - d * c, F = d * e - f * b;
+  const cplx det = a * A + d * D + f * F;
+  return {A / det, (a * c - f * f) / det, (a * b - d * d) / det, D / det, (d * f - a * e) / det, F / det};
+}
+
+// Tree form of a feeder (TreeDev), if it is one: nodes 3 b, 3 b + 1, 3 b + 2
+// are bus b's phases, the slack is one bus in phase order, each delta load sits on one bus in
+// phase order, Ybus joins buses in a tree, every block off the diagonal is
+// symmetric and equals its mirror, and every diagonal block is minus the sum
+// of the others in its row up to the rounding of that sum (no shunts).
+// Otherwise the network keeps the forms for a general Y_NN.
+void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const int32_t* col_idx, const double* y_re,
+                const double* y_im, const std::vector<uint8_t>& wye,
+                const std::vector<int>& delta_next) {
+  const int n = net.n_node, nbus = n / 3, s = net.slack[0] / 3;
+  if (n % 3 != 0 || nbus < 2 || nbus - 1 > ZB_TREE_MAX) return;
+  for (int p = 0; p < 3; ++p)
+    if (net.slack[p] != 3 * s + p) return;
+  auto free_of = [&](int b) { return 3 * b - (b > s ? 3 : 0); };   // free index of bus b's phase a
+  struct Block {
+    cplx y[3][3] = {};
+  };
+  // the free buses' rows (the slack's are not part of the problem and not read)
+  std::vector<std::map<int, Block>> rows(nbus);
+  for (int i : net.free2ext)
+    for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p)
+      rows[i / 3][col_idx[p] / 3].y[i % 3][col_idx[p] % 3] += cplx(y_re[p], y_im[p]);
+  size_t ends = 0;   // each segment's ends at free buses
+  std::vector<int> top;   // buses next to the slack
+  constexpr double eps = 2.3e-16;
+  for (int b = 0; b < nbus; ++b) {
+    ends += rows[b].size() - rows[b].count(b);
+    if (rows[b].count(s)) top.push_back(b);
+    double mag[3][3] = {};
+    cplx tot[3][3] = {};
+    for (auto& [c, B] : rows[b]) {
+      if (c != b && c != s && !rows[c].count(b)) return;
+      double big = 0.0;
+      for (int q = 0; q < 9; ++q) big = std::max(big, std::abs(B.y[q / 3][q % 3]));
+      const double tol = 64 * eps * big;
+      for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+          const cplx y = B.y[i][j];
+          tot[i][j] += y;
+          mag[i][j] += std::abs(y);
+          if (c == b) continue;
+          if (!(std::abs(y - B.y[j][i]) <= tol)) return;
+          if (c != s && !(std::abs(y - rows[c][b].y[i][j]) <= tol)) return;
+        }
+    }
+    for (int i = 0; i < 3; ++i)
+      for (int j = 0; j < 3; ++j)
+        if (!(std::abs(tot[i][j]) <= 64 * eps * mag[i][j])) return;
+  }
+  if (ends != 2 * (size_t)(nbus - 1) - top.size()) return;
+  for (int b = 0; b < nbus; ++b) {
+    if (b == s) continue;
+    const int f = free_of(b);
+    const bool has = delta_next[f] >= 0;
+    for (int p = 0; p < 3; ++p)
+      if (delta_next[f + p] != (has ? f + (p + 1) % 3 : -1)) return;
+  }
+  // preorder from the slack
+  std::vector<int> order, parent(nbus, -1), pos(nbus, -1), last(nbus, -1);
+  std::vector<int> event;   // bus entered, or ~bus left
+  std::vector<std::pair<int, bool>> todo = {{s, false}};
+  while (!todo.empty()) {
+    const auto [b, leave] = todo.back();
+    todo.pop_back();
+    if (leave) {
+      last[b] = (int)order.size() - 1;
+      event.push_back(~b);
+      continue;
+    }
+    if (b != s) {
+      pos[b] = (int)order.size();
+      order.push_back(b);
+      event.push_back(b);
+      todo.push_back({b, true});
+    }
+    std::vector<int> next = b == s ? top : std::vector<int>();
+    if (b != s)
+      for (auto& [c, B] : rows[b])
+        if (c != b && c != parent[b]) next.push_back(c);
+    for (auto it = next.rbegin(); it != next.rend(); ++it) {
+      if (*it == s || parent[*it] >= 0) return;
+      parent[*it] = b;
+      todo.push_back({*it, false});
+    }
+  }
+  const int nb = (int)order.size(), nbp = round_up(nb, 64);
+  if (nb != nbus - 1) return;
+  std::vector<int> bus(4 * (size_t)nbp, 0), link(4 * (size_t)nbp, (int)0x80008000u), more, ev(2 * (size_t)nbp, 0);
+  std::vector<int> rest(2 * (size_t)nbp, 0), kids(nbp / 64, 0);
+  std::vector<double> y(12 * (size_t)nbp, 0.0), z(12 * (size_t)nbp, 0.0);
+  for (int q = 0; q < nb; ++q) {
+    const int b = order[q], f = free_of(b);
+    int flags = 0;
+    for (int p = 0; p < 3; ++p) flags |= wye[f + p] ? 1 << (24 + p) : 0;
+    if (delta_next[f] >= 0) flags |= 1 << 27;
+    bus[4 * q] = 3 * b | flags;
+    bus[4 * q + 1] = f;
+    bus[4 * q + 2] = parent[b] == s ? -1 : pos[parent[b]];
+    bus[4 * q + 3] = last[b];
+    std::vector<int> ch;
+    for (auto& [c, B] : rows[b])
+      if (c != b && c != parent[b]) ch.push_back(pos[c]);
+    auto at = [&](size_t k) { return k < ch.size() ? ch[k] : 0x8000; };
+    for (size_t k = 0; k < 4; ++k) link[4 * (size_t)q + k] = at(2 * k) | at(2 * k + 1) << 16;
+    rest[2 * (size_t)q] = (int)more.size();
+    rest[2 * (size_t)q + 1] = ch.size() > 8 ? (int)ch.size() - 8 : 0;
+    if (ch.size() > 8) more.insert(more.end(), ch.begin() + 8, ch.end());
+    kids[q / 64] = std::max(kids[q / 64], std::min(8, (int)ch.size()));
+    const Block& B = rows[b][parent[b]];
+    const std::array<cplx, 6> ys = {-B.y[0][0], -B.y[1][1], -B.y[2][2], -B.y[0][1], -B.y[1][2], -B.y[2][0]};
+    const std::array<cplx, 6> zs = invert_sym3(ys);
+    constexpr int at3[3][3] = {{0, 3, 5}, {3, 1, 4}, {5, 4, 2}};
+    for (int i = 0; i < 3; ++i)
+      for (int j = 0; j < 3; ++j) {
+        cplx e = i == j ? -1.0 : 0.0;
+        for (int k = 0; k < 3; ++k) e += ys[at3[i][k]] * zs[at3[k][j]];
+        if (!(std::abs(e) <= 1e-10)) return;   // (nearly) singular segment
+      }
+    for (int k = 0; k < 6; ++k) {
+      const size_t o = 2 * ((size_t)k * nbp + q);
+      y[o] = ys[k].real();
+      y[o + 1] = ys[k].imag();
+      z[o] = zs[k].real();
+      z[o + 1] = zs[k].imag();
+    }
+  }
+  for (int e = 0; e < 2 * nb; ++e) ev[e] = event[e] >= 0 ? pos[event[e]] : ~pos[~event[e]];
+  if (more.empty()) more.push_back(0);
+  net.tree_nb = nb;
+  net.tree_nbp = nbp;
+  net.tr_bus = upload(ctx, bus);
+  net.tr_link = upload(ctx, link);
+  net.tr_rest = upload(ctx, rest);
+  net.tr_more = upload(ctx, more);
+  net.tr_kids = upload(ctx, kids);
+  net.tr_event = upload(ctx, ev);
+  net.tr_y = upload(ctx, y);
+  net.tr_z = upload(ctx, z);
+}
+
 }  // namespace
+
+TreeDev DistNetwork::tree_view() const {
+  TreeDev d;
+  d.nb = tree_nb;
+  d.nbp = tree_nbp;
+  d.bus = tr_bus.as<int4>();
+  d.link = tr_link.as<int4>();
+  d.rest = tr_rest.as<int2>();
+  d.more = tr_more.as<int>();
+  d.kids = tr_kids.as<int>();
+  d.event = tr_event.as<int2>();
+  d.y = tr_y.as<double2>();
+  d.z = tr_z.as<double2>();
+  d.slack = slack[0];
+  for (int k = 0; k < 6; ++k) d.v_slack[k] = v_slack[k];
+  return d;
+}
 
 DistDev DistNetwork::view() const {
   DistDev d;
@@ -144,7 +310,6 @@ DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_
   std::vector<SellRow> rows(nNs);
   std::vector<double> cc(2 * (size_t)nNs, 0.0);
   int nnz_nn = 0;
-  std::vector<cplx> Yd((size_t)nN * nN, cplx(0.0));
   for (int fi = 0; fi < nN; ++fi) {
     const int e = net->free2ext[fi];
     require(row_ptr[e + 1] >= row_ptr[e], "row_ptr must be non-decreasing");
@@ -161,65 +326,12 @@ DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_
         acc += y * cplx(v_slack[2 * s], v_slack[2 * s + 1]);
       }
     }
-    for (auto& [j, y] : row) {
-      rows[fi].emplace_back(j, y.real(), y.imag());
-      Yd[(size_t)fi * nN + j] = y;
-    }
+    for (auto& [j, y] : row) rows[fi].emplace_back(j, y.real(), y.imag());
     nnz_nn += (int)row.size();
     cc[2 * fi] = acc.real();
     cc[2 * fi + 1] = acc.imag();
   }
   net->nnz = nnz_nn;
-
-  // Sparse L D L^T of Y_NN for the sparse variant, checked against the dense
-  // inverse below.
-  std::vector<int> zp(nN + 1, 0), zc;
-  std::vector<cplx> zv;
-  for (int i = 0; i < nN; ++i) {
-    for (auto [j, re, im] : rows[i]) {
-      zc.push_back(j);
-      zv.push_back(cplx(re, im));
-    }
-    zp[i + 1] = (int)zc.size();
-  }
-  const ComplexLdl zf = complex_ldl(nN, zp, zc, zv);
-  invert_dense(Yd, nN);  // Yd now holds Z
-  {
-    std::vector<cplx> b(nN), ref(nN, cplx(0.0));
-    for (int i = 0; i < nN; ++i) b[i] = cplx(std::sin(0.37 * i + 0.1), std::cos(0.91 * i));
-    for (int i = 0; i < nN; ++i)
-      for (int l = 0; l < nN; ++l) ref[i] += Yd[(size_t)i * nN + l] * b[l];
-    const std::vector<cplx> x = complex_ldl_solve(zf, b);
-    double err = 0.0, mag = 0.0;
-    for (int i = 0; i < nN; ++i) {
-      err = std::max(err, std::abs(x[i] - ref[i]));
-      mag = std::max(mag, std::abs(ref[i]));
-    }
-    if (!(err <= 1e-8 * mag))
-      fail(PF_SINGULAR_SETUP, "sparse factor of Y_NN disagrees with the dense inverse (" + std::to_string(err) + ")");
-  }
-  std::vector<double> v0(2 * (size_t)nN);
-  for (int i = 0; i < nN; ++i) {
-    cplx s(0.0);
-    for (int l = 0; l < nN; ++l) s += Yd[(size_t)i * nN + l] * cplx(cc[2 * l], cc[2 * l + 1]);
-    v0[2 * i] = -s.real();
-    v0[2 * i + 1] = -s.imag();
-  }
-  const int Kp = net->Kp, Np = net->Np;
-  // W row-major (Kp x Np; the FP32 copy keeps this layout) ...
-  std::vector<double> W((size_t)Kp * Np, 0.0);
-  for (int i = 0; i < nN; ++i)
-    for (int l = 0; l < nN; ++l) {
-      const cplx z = Yd[(size_t)i * nN + l];
-      W[(size_t)(2 * l) * Np + 2 * i] = z.real();
-      W[(size_t)(2 * l + 1) * Np + 2 * i] = -z.imag();
-      W[(size_t)(2 * l) * Np + 2 * i + 1] = z.imag();
-      W[(size_t)(2 * l + 1) * Np + 2 * i + 1] = z.real();
-    }
-  // ... and the FP64 copy in K blocks of ZB_BK: (k, n) at ((k / ZB_BK) Np + n) ZB_BK + k % ZB_BK
-  std::vector<double> Wb((size_t)Kp * Np);
-  for (int k = 0; k < Kp; ++k)
-    for (int n = 0; n < Np; ++n) Wb[((size_t)(k / ZB_BK) * Np + n) * ZB_BK + k % ZB_BK] = W[(size_t)k * Np + n];
 
   // Load tables.
   std::vector<uint8_t> wye(nN, 0);
@@ -245,6 +357,7 @@ DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_
   }
   net->n_wye = n_wye;
   net->n_delta = n_delta;
+  build_tree(ctx, *net, row_ptr, col_idx, y_re, y_im, wye, dn);
 
   std::vector<int> nodes(4 * (size_t)nNs, 0);
   for (int i = 0; i < nN; ++i) {
@@ -254,6 +367,68 @@ DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_
     nodes[4 * i + 3] = dpv[i] >= 0 ? net->free2ext[dpv[i]] : 0;
   }
   for (int i = nN; i < nNs; ++i) nodes[4 * i + 1] = -1;
+
+  std::vector<double> v0(2 * (size_t)nN);
+  net->free2ext_d = upload(ctx, net->free2ext);
+  net->slack_d = upload(ctx, std::vector<int>(net->slack, net->slack + 3));
+  net->vslack_d = upload(ctx, std::vector<double>(net->v_slack, net->v_slack + 6));
+  if (net->tree_nb > 0) {
+    // without shunts the no-load voltage is the slack's everywhere
+    for (int i = 0; i < nN; ++i)
+      for (int q = 0; q < 2; ++q) v0[2 * (size_t)i + q] = v_slack[2 * (net->free2ext[i] % 3) + q];
+    net->v0 = upload(ctx, v0);
+    return net.release();
+  }
+
+  // Sparse L D L^T of Y_NN for the sparse variant, checked against the dense
+  // inverse below.
+  std::vector<int> zp(nN + 1, 0), zc;
+  std::vector<cplx> zv, Yd((size_t)nN * nN, cplx(0.0));
+  for (int i = 0; i < nN; ++i) {
+    for (auto [j, re, im] : rows[i]) {
+      zc.push_back(j);
+      zv.push_back(cplx(re, im));
+      Yd[(size_t)i * nN + j] = cplx(re, im);
+    }
+    zp[i + 1] = (int)zc.size();
+  }
+  const ComplexLdl zf = complex_ldl(nN, zp, zc, zv);
+  invert_dense(Yd, nN);  // Yd now holds Z
+  {
+    std::vector<cplx> b(nN), ref(nN, cplx(0.0));
+    for (int i = 0; i < nN; ++i) b[i] = cplx(std::sin(0.37 * i + 0.1), std::cos(0.91 * i));
+    for (int i = 0; i < nN; ++i)
+      for (int l = 0; l < nN; ++l) ref[i] += Yd[(size_t)i * nN + l] * b[l];
+    const std::vector<cplx> x = complex_ldl_solve(zf, b);
+    double err = 0.0, mag = 0.0;
+    for (int i = 0; i < nN; ++i) {
+      err = std::max(err, std::abs(x[i] - ref[i]));
+      mag = std::max(mag, std::abs(ref[i]));
+    }
+    if (!(err <= 1e-8 * mag))
+      fail(PF_SINGULAR_SETUP, "sparse factor of Y_NN disagrees with the dense inverse (" + std::to_string(err) + ")");
+  }
+  for (int i = 0; i < nN; ++i) {
+    cplx s(0.0);
+    for (int l = 0; l < nN; ++l) s += Yd[(size_t)i * nN + l] * cplx(cc[2 * l], cc[2 * l + 1]);
+    v0[2 * i] = -s.real();
+    v0[2 * i + 1] = -s.imag();
+  }
+  const int Kp = net->Kp, Np = net->Np;
+  // W row-major (Kp x Np; the FP32 copy keeps this layout) ...
+  std::vector<double> W((size_t)Kp * Np, 0.0);
+  for (int i = 0; i < nN; ++i)
+    for (int l = 0; l < nN; ++l) {
+      const cplx z = Yd[(size_t)i * nN + l];
+      W[(size_t)(2 * l) * Np + 2 * i] = z.real();
+      W[(size_t)(2 * l + 1) * Np + 2 * i] = -z.imag();
+      W[(size_t)(2 * l) * Np + 2 * i + 1] = z.imag();
+      W[(size_t)(2 * l + 1) * Np + 2 * i + 1] = z.real();
+    }
+  // ... and the FP64 copy in K blocks of ZB_BK: (k, n) at ((k / ZB_BK) Np + n) ZB_BK + k % ZB_BK
+  std::vector<double> Wb((size_t)Kp * Np);
+  for (int k = 0; k < Kp; ++k)
+    for (int n = 0; n < Np; ++n) Wb[((size_t)(k / ZB_BK) * Np + n) * ZB_BK + k % ZB_BK] = W[(size_t)k * Np + n];
 
   upload_sell(ctx, build_sell(rows, 4), true, net->y);
   {
@@ -338,11 +513,8 @@ DistNetwork* dist_network_create(Context* ctx, int n_node, int nnz, const int32_
   net->node = upload(ctx, nodes);
   net->c = upload(ctx, cc);
   net->v0 = upload(ctx, v0);
-  net->free2ext_d = upload(ctx, net->free2ext);
   net->W64 = upload(ctx, Wb);
   net->W32 = upload(ctx, std::vector<float>(W.begin(), W.end()));
-  net->slack_d = upload(ctx, std::vector<int>(net->slack, net->slack + 3));
-  net->vslack_d = upload(ctx, std::vector<double>(net->v_slack, net->v_slack + 6));
   return net.release();
 }
 

@@ -17,6 +17,9 @@
 //                 operands straight from memory; FP32: staged through LDS)
 //   zb_sparse     (sparse variant, instead of the GEMM) v += Y_NN^-1 r by
 //                 level-scheduled solves with the sparse L D L^T of Y_NN
+// On a radial feeder without shunts one kernel runs the whole iteration:
+//   zb_tree       Z r as path sums of z_s (subtree sum of r), all in registers
+//                 and LDS
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -54,6 +57,21 @@ __device__ __forceinline__ void st2(float* base, unsigned i, double x, double y)
 __device__ __forceinline__ D2 conj_div(D2 s, double vr, double vi) {
   const double d = vr * vr + vi * vi;
   return D2{(s.x * vr + s.y * vi) / d, -(s.y * vr - s.x * vi) / d};
+}
+
+// o = m d for a symmetric 3x3 m (aa, bb, cc, ab, bc, ca)
+__device__ __forceinline__ void sym3(const D2 (&m)[6], const D2 (&d)[3], D2 (&o)[3]) {
+  constexpr int at[3][3] = {{0, 3, 5}, {3, 1, 4}, {5, 4, 2}};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    o[i] = D2{0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const D2 y = m[at[i][j]];
+      o[i].x += y.x * d[j].x - y.y * d[j].y;
+      o[i].y += y.x * d[j].y + y.y * d[j].x;
+    }
+  }
 }
 
 constexpr int WYE_BIT = 1 << 30;
@@ -605,6 +623,304 @@ __global__ __launch_bounds__(ZB_THREADS) void zb_finish(DistDev net, ZbusLaunch 
   }
 }
 
+// Tree form of the whole fixed point for a radial feeder without shunts: one
+// workgroup per scenario, thread q owns the bus at preorder position q (its
+// three voltages and loads in registers).  There Z r needs no factor: the
+// current through the segment above bus q is the sum of r over its subtree,
+// J_q = sum r(q .. last(q)), and (Z r)_q is the sum of z_a J_a over the path
+// from the slack to q.  Both are prefix sums over the traversal: the subtree
+// sum is a difference of prefixes in preorder, and the path sum the prefix of
+// u = z J over the entering (+u) and leaving (-u) events up to q's entry.  The
+// residual r = i(v) - (Y_NN v + Y_NS v_S) is formed from the segments'
+// currents y (v_parent - v_q), which is the same sum as Y_NN v + c without its
+// cancellation.
+//
+// Bound: seven short phases between barriers per iteration (LDS latency, the
+// two scans and the complex divisions, about 500 FP64 instructions a wave);
+// HBM is touched for the loads and the result only.  Against this, the general
+// forms pay two launches, a read-back and a pass of v and r through HBM per
+// iteration, and a dense product or a few hundred dependent factor levels.
+// Measured, 300 buses: one scenario 1222 -> 32 us, 4096 scenarios 2843 (dense)
+// -> 364 us, 1000 in mixed precision 1038 -> 111 us; 600 buses, 1024 scenarios
+// 1059 (sparse factor) -> 215 us.  So it is taken for every such feeder.
+//
+// STEP: an engine's step (a.slots): v, the statistics and the flags come from
+// and go back to the slot's state, `steps` residuals at most; otherwise the
+// solve runs from v0 to its end and writes the outputs.
+template <bool STEP>
+__global__ __launch_bounds__(ZB_TREE_MAX) void zb_tree(TreeDev net, const double* v0, int Kp, ZbusLaunch a,
+                                                       int steps) {
+  extern __shared__ D2 tsm[];
+  constexpr int MAXW = ZB_TREE_MAX / WAVE;
+  __shared__ double red[2][MAXW], tot[2][MAXW][8];
+  const int nbp = net.nbp, nw = nbp / WAVE;
+  D2* A = tsm;             // [nbp][3] v, then the prefixes of r, then the path sums
+  D2* B = tsm + 3 * nbp;   // [nbp][3] segment currents, then u
+  const int g = blockIdx.x, b = STEP ? a.slots[g] : g;
+  if (STEP && a.active[b] == 0) {
+    if (threadIdx.x == 0) a.step_done[g] = 1;
+    return;
+  }
+  const int q = threadIdx.x, wv = wave_id(), lane = lane_id();
+  const bool live = q < net.nb;
+  const int4 bus = cld(net.bus, (unsigned)q);
+  int4 link = cld(net.link, (unsigned)q);
+  int2 ev = cld(net.event, (unsigned)q);
+  const int2 rest = cld(net.rest, (unsigned)q);
+  const int kids = __builtin_amdgcn_readfirstlane(cld(net.kids, (unsigned)wv));
+  const unsigned ext = (unsigned)bus.x & 0xffffffu;
+  const bool delta = (bus.x >> 27) & 1;
+  const bool wye = (bus.x >> 24) & 7;
+  const double* SW = a.s_wye + 2 * (int64_t)b * a.ld;
+  const double* SD = a.s_delta + 2 * (int64_t)b * a.ld;
+  // the bus's loads (a delta bus that also has wye loads reads those in each iteration)
+  D2 s[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    s[p] = D2{0.0, 0.0};
+    if (delta) s[p] = ld2(SD, ext + p);
+    else if ((bus.x >> (24 + p)) & 1) s[p] = ld2(SW, ext + p);
+  }
+  D2 v[3];
+  double* vrow = STEP ? a.v + (int64_t)b * Kp : nullptr;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    v[p] = D2{1.0, 0.0};
+    if (live) v[p] = STEP ? ld2(vrow, (unsigned)bus.y + p) : ld2(v0, (unsigned)bus.y + p);
+  }
+  int it = STEP ? a.iters[b] : 0;
+  double sprev = STEP ? a.st[3 * (int64_t)b + 1] : 0.0;
+  double mm = 0.0, sabs = 0.0, change = STEP ? a.st[3 * (int64_t)b + 2] : 0.0;
+  bool conv = false, more = true;
+  // workgroup prefix sums of six values per thread, in two halves around a barrier
+  auto totals = [&](double (&x)[6], int buf) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) x[c] = wave_prefix(x[c]);
+    if (lane == WAVE - 1) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) tot[buf][wv][c] = x[c];
+    }
+  };
+  // (lane c sums component c over the waves before this one)
+  auto offsets = [&](double (&x)[6], int buf) {
+    double o = 0.0;
+    for (int w = 0; w < wv; w += 4) {
+      double t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = tot[buf][w + u][lane & 7];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) o += w + u < wv ? t[u] : 0.0;
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) x[c] += lane_value(o, c);
+  };
+  for (int k = 0;; ++k) {
+    // the segment's y and z are read again in each iteration, and what follows
+    // from link and ev is formed again (hiding their values keeps some 80
+    // registers from being held throughout)
+    const double2 *yp = net.y, *zp = net.z;
+    asm volatile("" : "+s"(yp), "+s"(zp), "+v"(link.x), "+v"(link.y), "+v"(link.z), "+v"(link.w), "+v"(ev.x), "+v"(ev.y));
+#pragma unroll
+    for (int p = 0; p < 3; ++p) A[3 * q + p] = v[p];
+    D2 y[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const double2 t = cld(yp, (unsigned)(c * nbp + q));
+      y[c] = D2{t.x, t.y};
+    }
+    __syncthreads();
+    // current through the segment above: y (v_parent - v)
+    D2 cur[3];
+    {
+      D2 d[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const D2 up = bus.z >= 0 ? A[3 * bus.z + p] : D2{net.v_slack[2 * p], net.v_slack[2 * p + 1]};
+        d[p] = up - v[p];
+      }
+      sym3(y, d, cur);
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) B[3 * q + p] = cur[p];
+    // load currents into the bus (none at positions past the last bus): one
+    // division per phase serves a delta branch or a wye load
+    D2 r[3];
+    {
+      D2 f[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const D2 d = delta ? v[p] - v[(p + 1) % 3] : v[p];
+        f[p] = D2{0.0, 0.0};
+        if (delta || ((bus.x >> (24 + p)) & 1)) f[p] = conj_div(s[p], d.x, d.y);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p) r[p] = delta ? f[(p + 2) % 3] - f[p] : -f[p];
+    }
+    if (delta && wye) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        if ((bus.x >> (24 + p)) & 1) r[p] -= conj_div(ld2(SW, ext + p), v[p].x, v[p].y);
+    }
+    __syncthreads();
+    // r = i(v) + current from above - currents into the children
+#pragma unroll
+    for (int p = 0; p < 3; ++p) r[p] += cur[p];
+    // (children by pairs, as many as the wave's buses have; absent ones read position 0's and count 0)
+    auto child = [&](int c) {   // c constant
+      const int w = c < 2 ? link.x : c < 4 ? link.y : c < 6 ? link.z : link.w;
+      return (c & 1 ? w >> 16 : w) & 0xffff;
+    };
+    auto pair = [&](int c) {
+      const int c0 = child(c), c1 = child(c + 1);
+      D2 i0[3], i1[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        i0[p] = B[3 * (c0 & 0x7fff) + p];
+        i1[p] = B[3 * (c1 & 0x7fff) + p];
+      }
+      const double f0 = c0 & 0x8000 ? 0.0 : 1.0, f1 = c1 & 0x8000 ? 0.0 : 1.0;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        r[p] -= f0 * i0[p];
+        r[p] -= f1 * i1[p];
+      }
+    };
+    if (kids > 0) pair(0);
+    if (kids > 2) pair(2);
+    if (kids > 4) pair(4);
+    if (kids > 6) pair(6);
+    for (int c = 0; c < rest.y; ++c) {
+      const int ch = cld(net.more, (unsigned)(rest.x + c));
+#pragma unroll
+      for (int p = 0; p < 3; ++p) r[p] -= B[3 * ch + p];
+    }
+    double x[6];
+    double m1 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      if (!live) r[p] = D2{0.0, 0.0};
+      const double dr = v[p].x * r[p].x + v[p].y * r[p].y, di = v[p].y * r[p].x - v[p].x * r[p].y;  // v conj(r)
+      m1 = nanmax(m1, dr * dr + di * di);
+      s1 += live ? sqrt(v[p].x * v[p].x + v[p].y * v[p].y) : 0.0;
+      x[2 * p] = r[p].x;
+      x[2 * p + 1] = r[p].y;
+    }
+    m1 = wave_nanmax_pos(m1);
+    s1 = wave_total(s1);
+    if (lane == 0) {
+      red[0][wv] = m1;
+      red[1][wv] = s1;
+    }
+    totals(x, 0);
+    __syncthreads();
+    // (lane w takes wave w's partials)
+    mm = sqrt(wave_nanmax_pos(lane < nw ? red[0][lane & (MAXW - 1)] : 0.0));
+    sabs = wave_total(lane < nw ? red[1][lane & (MAXW - 1)] : 0.0);
+    if (it > 0) change = fabs(sabs - sprev);
+    sprev = sabs;
+    conv = mm <= a.tol;
+    more = !conv && mm == mm && it < a.max_iter;
+    if (!more) break;
+    ++it;
+    offsets(x, 0);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) A[3 * q + p] = D2{x[2 * p], x[2 * p + 1]};
+    D2 z[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const double2 t = cld(zp, (unsigned)(c * nbp + q));
+      z[c] = D2{t.x, t.y};
+    }
+    __syncthreads();
+    // subtree sums and u = z J
+    {
+      D2 J[3], u[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) J[p] = A[3 * bus.w + p] - D2{x[2 * p], x[2 * p + 1]} + r[p];
+      sym3(z, J, u);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) B[3 * q + p] = u[p];
+    }
+    __syncthreads();
+    // this thread's two events
+    const int e0 = ev.x >= 0 ? ev.x : ~ev.x, e1 = ev.y >= 0 ? ev.y : ~ev.y;
+    const double g0 = !live ? 0.0 : ev.x < 0 ? -1.0 : 1.0, g1 = !live ? 0.0 : ev.y < 0 ? -1.0 : 1.0;
+    double h[6];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const D2 t0 = B[3 * e0 + p], t1 = g1 * B[3 * e1 + p];
+      x[2 * p] = g0 * t0.x + t1.x;
+      x[2 * p + 1] = g0 * t0.y + t1.y;
+      h[2 * p] = t1.x;
+      h[2 * p + 1] = t1.y;
+    }
+    totals(x, 1);
+    __syncthreads();
+    offsets(x, 1);
+    // prefix at the second event, and at the first (less the second's term)
+    if (live) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const D2 t = {x[2 * p], x[2 * p + 1]};
+        if (ev.y >= 0) A[3 * e1 + p] = t;
+        if (ev.x >= 0) A[3 * e0 + p] = t - D2{h[2 * p], h[2 * p + 1]};
+      }
+    }
+    __syncthreads();
+    if (live) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) v[p] += A[3 * q + p];
+    }
+    if (STEP && k + 1 >= steps) break;
+  }
+  if (STEP) {
+    if (live) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) st2(vrow, (unsigned)bus.y + p, v[p].x, v[p].y);
+    }
+  } else {
+    double* out = a.v_out + 2 * (int64_t)b * a.ld;
+    if (live) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) st2(out, ext + p, v[p].x, v[p].y);
+    }
+    if (q == 0) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) st2(out, (unsigned)(net.slack + p), net.v_slack[2 * p], net.v_slack[2 * p + 1]);
+    }
+  }
+  if (threadIdx.x == 0) {
+    a.iters[b] = it;
+    if (STEP) {
+      double* st = a.st + 3 * (int64_t)b;
+      st[0] = mm;
+      st[1] = sprev;
+      st[2] = change;
+      if (!more) {
+        a.converged[b] = conv ? 1 : 0;
+        a.active[b] = 0;
+      }
+      a.step_done[g] = more ? 0 : 1;
+    } else {
+      a.converged[b] = conv ? 1 : 0;
+      if (a.final_mismatch) a.final_mismatch[b] = mm;
+      if (a.sum_abs_change) a.sum_abs_change[b] = change;
+    }
+  }
+}
+
+void launch_tree(DistNetwork& net, const ZbusLaunch& a, int steps, hipStream_t s) {
+  const TreeDev d = net.tree_view();
+  const size_t lds = (size_t)6 * d.nbp * sizeof(D2);
+  auto kernel = a.slots ? zb_tree<true> : zb_tree<false>;
+  if (lds > 60 * 1024)
+    PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds));
+  hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(d.nbp), lds, s, d, net.v0.as<double>(), net.Kp, a, steps);
+  PFX_HIP(hipGetLastError());
+}
+
 // The update's GEMM: FP64 without LDS (W in K blocks), FP32 through LDS (W row-major).
 template <typename T>
 void launch_gemm(const DistDev& d, const T* W, const ZbusLaunch& a, int it, int tiles, hipStream_t s) {
@@ -715,7 +1031,8 @@ void zbus_init_slots(DistNetwork& net, const ZbusLaunch& a, hipStream_t s) {
 
 void zbus_step(DistNetwork& net, bool mixed, const ZbusLaunch& a, int iters, hipStream_t s) {
   if (a.batch == 0) return;
-  if (mixed) zbus_step_t<float>(net, a, iters, s);
+  if (net.tree_nb > 0) launch_tree(net, a, iters, s);
+  else if (mixed) zbus_step_t<float>(net, a, iters, s);
   else zbus_step_t<double>(net, a, iters, s);
 }
 
@@ -728,7 +1045,8 @@ void zbus_finish_slots(DistNetwork& net, const ZbusLaunch& a, hipStream_t s) {
 
 void run_zbus(DistNetwork& net, bool mixed, const ZbusLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
-  if (mixed) run_zbus_t<float>(net, a, s);
+  if (net.tree_nb > 0) launch_tree(net, a, 0, s);
+  else if (mixed) run_zbus_t<float>(net, a, s);
   else run_zbus_t<double>(net, a, s);
 }
 

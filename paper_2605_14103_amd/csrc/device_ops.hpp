@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace pfx {
 
 constexpr int WAVE = 64;
@@ -60,12 +62,89 @@ __device__ __forceinline__ double lane_value(double v, int l) {
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// sum over each four lanes (a quad), in all of them
+__device__ __forceinline__ float quad_total(float v) {
+  v += dpp_f<0xB1, 0xf>(v);
+  return v + dpp_f<0x4E, 0xf>(v);
+}
+__device__ __forceinline__ double quad_total(double v) {
+  v += dpp_d<0xB1, 0xf>(v);
+  return v + dpp_d<0x4E, 0xf>(v);
+}
+
+// v + v of the lane's partner row: rows 0 and 1, and 2 and 3 (HALVES: the
+// wave's two halves)
+template <bool HALVES>
+__device__ __forceinline__ float row_pair_sum(float v) {
+  const unsigned u = __float_as_uint(v);
+  const auto r = HALVES ? __builtin_amdgcn_permlane32_swap(u, u, false, false)
+                        : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <bool HALVES>
+__device__ __forceinline__ double row_pair_sum(double v) {
+  const unsigned l = __double2loint(v), h = __double2hiint(v);
+  const auto a = HALVES ? __builtin_amdgcn_permlane32_swap(l, l, false, false)
+                        : __builtin_amdgcn_permlane16_swap(l, l, false, false);
+  const auto b = HALVES ? __builtin_amdgcn_permlane32_swap(h, h, false, false)
+                        : __builtin_amdgcn_permlane16_swap(h, h, false, false);
+  return __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+}
+
 // row shift by N lanes, 0 into the lanes it does not reach
 template <int N>
 __device__ __forceinline__ double dpp_row_shr(double v) {
   const int lo = __double2loint(v), hi = __double2hiint(v);
   return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x110 + N, 0xf, 0xf, true),
                           __builtin_amdgcn_update_dpp(lo, lo, 0x110 + N, 0xf, 0xf, true));
+}
+
+template <int N>
+__device__ __forceinline__ float dpp_row_shr(float v) {
+  const int x = __float_as_int(v);
+  return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x110 + N, 0xf, 0xf, true));
+}
+
+// (a0 + a1) or (a0 + a1) + (a2 + a3) with each a the wave's total as wave_total
+// forms it, bit for bit, in every lane.  The first steps fold the values into
+// one: lane l carries value l mod NU from then on.
+__device__ __forceinline__ float dpp_v(float v, std::integral_constant<int, 1>) { return dpp_f<0xB1, 0xf>(v); }
+__device__ __forceinline__ float dpp_v(float v, std::integral_constant<int, 2>) { return dpp_f<0x4E, 0xf>(v); }
+__device__ __forceinline__ double dpp_v(double v, std::integral_constant<int, 1>) { return dpp_d<0xB1, 0xf>(v); }
+__device__ __forceinline__ double dpp_v(double v, std::integral_constant<int, 2>) { return dpp_d<0x4E, 0xf>(v); }
+
+// lanes with bit B of their number clear: a0 of this lane and its partner at
+// distance B; the others: a1 of both
+template <int B, typename T>
+__device__ __forceinline__ T fold_units(T a0, T a1) {
+  const bool b = threadIdx.x & B;
+  return (b ? a1 : a0) + dpp_v(b ? a0 : a1, std::integral_constant<int, B>{});
+}
+
+// The rest of the way from values folded into v (NU = 4: by 1, then by 2;
+// NU = 2: by 1, then v + its partner at 2).
+template <int NU, typename T>
+__device__ __forceinline__ T wave_total_folded(T v) {
+  v += dpp_row_shr<4>(v);   // the row's total ends in its last four lanes
+  v += dpp_row_shr<8>(v);
+  v = row_pair_sum<false>(v);
+  v = row_pair_sum<true>(v);
+  v += dpp_v(v, std::integral_constant<int, 1>{});
+  if constexpr (NU == 4) v += dpp_v(v, std::integral_constant<int, 2>{});
+  return lane_value(v, 15);
+}
+
+template <int NU, typename T>
+__device__ __forceinline__ T wave_total_units(const T (&a)[NU]) {
+  static_assert(NU == 2 || NU == 4, "units");
+  T v = fold_units<1>(a[0], a[1]);
+  if constexpr (NU == 4) v = fold_units<2>(v, fold_units<1>(a[2], a[3]));
+  else v += dpp_v(v, std::integral_constant<int, 2>{});
+  return wave_total_folded<NU>(v);
 }
 
 // Inclusive prefix sum over the lanes of a wave: shifts by 1, 2, 4 and 8

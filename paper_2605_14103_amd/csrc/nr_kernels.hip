@@ -2,7 +2,7 @@
 // workgroup per scenario, and its adjoint.
 //
 // A workgroup owns one scenario for its whole solve.  Thread t owns internal
-// buses i = t + k BLOCK (k < KB) and, for each, both Newton-state entries of
+// buses i = t + k VB (k < KB; see Shape) and, for each, both Newton-state entries of
 // that bus (angle and magnitude; see tx.hpp): vectors of the Newton space live
 // in registers as w[k] (angle of bus slot k) and w[KB + k] (magnitude), and in
 // HBM as two planes of nbp entries, so every streaming access is coalesced and
@@ -43,13 +43,49 @@ namespace pfx {
 
 namespace {
 
-template <int BLOCK>
-__device__ __forceinline__ unsigned row(int k) {
-  return threadIdx.x + (unsigned)k * BLOCK;
-}
+// a b + c, rounded once: in FP64, products and sums are written with it wherever
+// more than one way of fusing them exists, so that every shape computes the
+// same bits.  (In FP32 they are left as the compiler fuses them.)
+__device__ __forceinline__ float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+__device__ __forceinline__ float mul_add(float a, float b, float c, float d) { return a * b + c * d; }
+__device__ __forceinline__ float mul_sub(float a, float b, float c, float d) { return a * b - c * d; }
+__device__ __forceinline__ double mul_add(double a, double b, double c, double d) { return fm(a, b, c * d); }
+__device__ __forceinline__ double mul_sub(double a, double b, double c, double d) { return fm(a, b, -(c * d)); }
+
+// Shape of a workgroup.  A network has VB KBT bus positions (nr_shape); with a
+// split of S, S VB threads hold KB = KBT / S bus slots each: group g of VB
+// threads (whole waves) takes slots g KB .. g KB + KB - 1 of each of its VB
+// columns.  More waves per scenario shorten every phase, which is worth having
+// as long as the batch leaves the CUs room for them (nr_split).
+//
+// Sums over a scenario come out the same for every split.  In FP64 they are formed per
+// unit of U slots and column, over the lanes of a wave, then over a wave's
+// units and last over the VB / 64 waves of the unsplit shape.  In FP32, where
+// the number of Arnoldi (and Newton) steps follows the sums' rounding, they keep the
+// unsplit kernel's order, slot after slot in each column: a split workgroup
+// hands the vector to its first group through LDS for them.
+constexpr int nr_split_max(int VB, int KBT) { return KBT == 1 || VB >= 1024 ? 1 : VB >= 512 ? 2 : KBT >= 4 ? 4 : KBT; }
+
+template <int VB_, int KBT_, int S_>
+struct Shape {
+  static constexpr int VB = VB_, KBT = KBT_, S = S_;
+  static constexpr int BLOCK = VB * S, KB = KBT / S, NW = BLOCK / WAVE, NWV = VB / WAVE;
+  static constexpr unsigned NBP = (unsigned)VB * KBT;
+  static constexpr int SMAX = nr_split_max(VB, KBT), U = KBT / SMAX, NU = KB / U;
+  static_assert(KBT % S == 0 && SMAX % S == 0 && (KB % 2 == 0 || KB == 1), "shape");
+  static __device__ __forceinline__ int group() { return S == 1 ? 0 : wave_id() / NWV; }
+  static __device__ __forceinline__ unsigned col() { return S == 1 ? threadIdx.x : threadIdx.x % VB; }
+  // internal bus of this thread's slot k, and the 64-row slice it lies in
+  static __device__ __forceinline__ unsigned row(int k) { return col() + (unsigned)(group() * KB + k) * VB; }
+  static __device__ __forceinline__ int slice(int k) {
+    return S == 1 ? k * NW + wave_id() : (group() * KB + k) * NWV + wave_id() % NWV;
+  }
+};
 
 struct NrLayout {
-  int xs, tmp, red, redn, H, cs, sn, gres, gfin, y, total;
+  int xs, tmp, red, redn, H, cs, sn, gres, gfin, y, w, total;
 };
 
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
@@ -57,7 +93,7 @@ __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 // Column j of the packed Hessenberg matrix holds rows 0..j at offset j(j+1)/2.
 __host__ __device__ inline int hcol(int j) { return j * (j + 1) / 2; }
 
-__host__ __device__ inline NrLayout nr_layout(int nbp, int nth, int npq, int kmax, int R, int NW, int ts) {
+__host__ __device__ inline NrLayout nr_layout(int nbp, int nth, int npq, int kmax, int R, int NW, bool split, int ts) {
   NrLayout L;
   int o = 0;
   int xs_bytes = 2 * nbp * 8;                          // V (FP64 pairs) in the mismatch
@@ -72,7 +108,7 @@ __host__ __device__ inline NrLayout nr_layout(int nbp, int nth, int npq, int kma
   // the preconditioner runs (each phase in between ends with a barrier).
   const int red_bytes = 2 * (R + 2) * NW * 8;
   L.red = o;  o += align16(red_bytes);
-  const int tmp_bytes = ((kmax > 0 ? kmax : 1) + 3) / 4 * 4 * ts;   // whole packs of the dense core
+  const int tmp_bytes = (kmax + 4 * 16 / ts) * ts;   // four parts of whole packs of the dense core
   if (tmp_bytes <= red_bytes) {
     L.tmp = L.red;
   } else {
@@ -86,6 +122,8 @@ __host__ __device__ inline NrLayout nr_layout(int nbp, int nth, int npq, int kma
   L.gres = o; o += align16((R + 1) * ts);
   L.gfin = o; o += align16(R * ts);
   L.y = o;    o += align16(R * ts);
+  L.w = o;    // a split FP32 workgroup's vector for its sums
+  if (split && ts == 4) o += align16(2 * nbp * ts);
   L.total = o;
   return L;
 }
@@ -104,6 +142,7 @@ struct Smem {
   T* gres;
   T* gfin;
   T* yv;
+  T* wv;
 };
 
 template <typename T>
@@ -121,6 +160,7 @@ __device__ Smem<T> carve(unsigned char* smem, const NrLayout& L) {
   s.gres = reinterpret_cast<T*>(smem + L.gres);
   s.gfin = reinterpret_cast<T*>(smem + L.gfin);
   s.yv = reinterpret_cast<T*>(smem + L.y);
+  s.wv = reinterpret_cast<T*>(smem + L.w);
   return s;
 }
 
@@ -170,21 +210,30 @@ __device__ __forceinline__ void bst(const Buf& b, float x, unsigned voff, unsign
   __builtin_amdgcn_raw_buffer_store_b32(v, b.r, (int)voff, (int)soff, CP);
 }
 
-// One scenario's FP64 workspace: 13 planes of NBP = KB BLOCK doubles.  Plane
+// One scenario's FP64 workspace: 13 planes of NBP = KBT VB doubles.  Plane
 // F and DX span two planes each (angle plane, then magnitude plane).  With an
 // even slot count a thread's slots 2j and 2j + 1 of a plane are adjacent
 // (slot k of thread t at (k / G) G BLOCK + G t + k % G, G = 2), so that the
 // pair is read or written with one 16-byte access.
 enum WsPlane { TH = 0, VM, IVM, VRE, VIM, IRE, IIM, PIN, QIN, FP = 9, DXP = 11, WS_PLANES = 13 };
 
-template <int BLOCK, int KB>
+template <class Sh>
 struct Ws {
-  static constexpr unsigned NBP = (unsigned)KB * BLOCK;
-  static constexpr int G = KB % 2 == 0 ? 2 : 1;
+  static constexpr int KB = Sh::KB, VB = Sh::VB;
+  static constexpr unsigned NBP = Sh::NBP;
+  static constexpr int GL = Sh::KBT % 2 == 0 ? 2 : 1;   // slots side by side in the layout
+  static constexpr int G = KB % 2 == 0 ? 2 : 1;         // and in one thread
   Buf b;
-  static __device__ __forceinline__ unsigned vo() { return threadIdx.x * (8u * G); }
+  static __device__ __forceinline__ unsigned vo() { return Sh::col() * (8u * GL); }
+  // slot k of this thread (k >= KB: slot k - KB of the next plane) is slot g KB + k of its column
   static __device__ __forceinline__ unsigned so(int a, int k) {
-    return (unsigned)(a * (int)NBP + (k / G) * (G * BLOCK) + k % G) * 8u;
+    const int j = k % KB, pl = a + k / KB;
+    if constexpr (KB == 1 && Sh::S > 1) {
+      const int c = Sh::group();
+      return (unsigned)(pl * (int)NBP + (c / GL) * (GL * VB) + c % GL) * 8u;
+    } else {
+      return (unsigned)(pl * (int)NBP + Sh::group() * (KB * VB) + (j / G) * (G * VB) + j % G) * 8u;
+    }
   }
   // plane a, bus slot k (k < 2 KB for the two-plane vectors F and DX)
   __device__ __forceinline__ double ld(int a, int k) const { return bld<double, WS_POLICY>(b, vo(), so(a, k)); }
@@ -344,18 +393,37 @@ struct Ws {
 // bytes in all where the slot count allows), so that the compiler reads and
 // writes a run with one wide access: slot k of thread t sits at
 // (k / G) G BLOCK + G t + k % G.
-template <typename T, int BLOCK, int KB>
+template <typename T, class Sh>
 struct Basis {
+  static constexpr int BLOCK = Sh::BLOCK, KB = Sh::KB;
   static constexpr unsigned MP = 2u * KB * BLOCK;
   static constexpr int G = (16 / (int)sizeof(T) <= 2 * KB && (2 * KB) % (16 / (int)sizeof(T)) == 0)
                                ? 16 / (int)sizeof(T) : 2;
   Buf b;
+  // The first nl vectors live in LDS (thread-private runs, like the rest): a
+  // split workgroup has LDS to spare, and the vectors that every later step
+  // reads again then leave L2 to the network's data.
+  T* lds;
+  int nl;
   static __device__ __forceinline__ unsigned off(int i, int k) {
     return ((unsigned)i * MP + (unsigned)(k / G) * (G * BLOCK) + (unsigned)(k % G)) * (unsigned)sizeof(T);
   }
-  // run g (slots g G .. g G + G - 1) of vector i: one load or store of G sizeof(T) bytes
+  // run g (slots g G .. g G + G - 1) of vector i: one load or store of G
+  // sizeof(T) bytes; L: vector i < nl, in LDS
+  template <bool L = false>
   __device__ __forceinline__ void ldg(int i, int g, T* e) const {
-    const unsigned vo = threadIdx.x * (unsigned)(G * sizeof(T)), so = off(i, g * G);
+    ldg_of<L>(i, g, e, threadIdx.x);
+  }
+  // thread's run
+  template <bool L>
+  __device__ __forceinline__ void ldg_of(int i, int g, T* e, unsigned thread) const {
+    if constexpr (L) {
+      typedef T TV __attribute__((ext_vector_type(G)));
+      const TV v = reinterpret_cast<const TV*>(lds + (unsigned)i * MP + (unsigned)g * (G * BLOCK))[thread];
+      __builtin_memcpy(e, &v, G * sizeof(T));
+      return;
+    }
+    const unsigned vo = thread * (unsigned)(G * sizeof(T)), so = off(i, g * G);
     if constexpr (G * sizeof(T) == 16) {
       const auto v = __builtin_amdgcn_raw_buffer_load_b128(b.r, (int)vo, (int)so, BASIS_POLICY);
       __builtin_memcpy(e, &v, 16);
@@ -365,6 +433,13 @@ struct Basis {
     }
   }
   __device__ __forceinline__ void stg(int i, int g, const T* e) const {
+    if (Sh::S > 1 && i < nl) {
+      typedef T TV __attribute__((ext_vector_type(G)));
+      TV v;
+      __builtin_memcpy(&v, e, G * sizeof(T));
+      reinterpret_cast<TV*>(lds + (unsigned)i * MP + (unsigned)g * (G * BLOCK))[threadIdx.x] = v;
+      return;
+    }
     const unsigned vo = threadIdx.x * (unsigned)(G * sizeof(T)), so = off(i, g * G);
     if constexpr (G * sizeof(T) == 16) {
       decltype(__builtin_amdgcn_raw_buffer_load_b128(b.r, 0, 0, 0)) v;
@@ -378,12 +453,32 @@ struct Basis {
   }
 };
 
-// One group of four entries of a packed sliced layout (group index g) into
-// v[0..3] and c[0..3]: one 8-byte load of the columns and sizeof(V) / 4
-// 16-byte loads of the values.
+// V, I and 1/|V| of the thread's buses.  With few slots per thread they stay in
+// registers through a linear solve; otherwise each use reads the workspace.
+template <typename T, class Sh>
+struct Held {
+  static constexpr bool on = Sh::S > 1 && Sh::KB <= 2;
+  static constexpr int N = on ? Sh::KB : 1;
+  T vr[N], vi[N], ir[N], ii[N], iv[N];
+  __device__ __forceinline__ void load(const Ws<Sh>& ws) {
+    if constexpr (on) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        ws.template get_v<T>(k, vr[k], vi[k]);
+        ws.template get_i<T>(k, ir[k], ii[k]);
+        iv[k] = ws.template get_ivm<T>(k);
+      }
+    }
+  }
+};
+
+// This lane's four entries of group block gb (64 groups, one per lane) of a
+// packed sliced layout into v[0..3] and c[0..3]: one 8-byte load of the columns
+// and sizeof(V) / 4 16-byte loads of the values.
 template <typename V>
-__device__ __forceinline__ void pgroup(const PSell<V>& a, unsigned g, V* v, int* c) {
-  const int2 cc = cld(reinterpret_cast<const int2*>(a.col), g);
+__device__ __forceinline__ void pgroup(const PSell<V>& a, int gb, V* v, int* c) {
+  const unsigned lane = lane_id();
+  const int2 cc = cld(reinterpret_cast<const int2*>(a.col) + gb, lane);
   c[0] = cc.x & 0xffff;
   c[1] = (int)((unsigned)cc.x >> 16);
   c[2] = cc.y & 0xffff;
@@ -391,7 +486,7 @@ __device__ __forceinline__ void pgroup(const PSell<V>& a, unsigned g, V* v, int*
   constexpr int NL = (int)sizeof(V) / 4;
 #pragma unroll
   for (int u = 0; u < NL; ++u) {
-    const int4 q = cld(reinterpret_cast<const int4*>(a.val), (unsigned)NL * g + u);
+    const int4 q = cld(reinterpret_cast<const int4*>(a.val) + (gb * NL + u * WAVE), lane);
     __builtin_memcpy(reinterpret_cast<char*>(v) + 16 * u, &q, 16);
   }
 }
@@ -399,97 +494,81 @@ __device__ __forceinline__ void pgroup(const PSell<V>& a, unsigned g, V* v, int*
 // One row (slice s, this lane) of a packed layout, a group per round.
 template <typename V, typename Body>
 __device__ __forceinline__ void psell_row(const PSell<V>& a, int s, Body&& body) {
-  const int lane = lane_id();
   const int o = cld(a.off, (unsigned)s);
   const int wd = cld(a.width, (unsigned)s);
   for (int p = 0; p < wd; ++p) {
     V v[4];
     int c[4];
-    pgroup(a, (unsigned)(o + p * WAVE + lane), v, c);
+    pgroup(a, o + p * WAVE, v, c);
 #pragma unroll
     for (int u = 0; u < 4; ++u) body(v[u], c[u]);
   }
 }
 
 // Rows by bus slot of a packed layout: the thread's bus slots k < KB are rows
-// of slices k NW + wave.  body(k, val, col) accumulates one entry of slot k;
+// of slices Sh::slice(k).  body(k, val, col) accumulates one entry of slot k;
 // after a slot's row, done(k) runs.
-template <int KB, int NW, typename V, typename Body, typename Done>
+template <class Sh, typename V, typename Body, typename Done>
 __device__ __forceinline__ void psell_slots(const PSell<V>& a, Body&& body, Done&& done) {
-  const int wv = wave_id();
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    psell_row(a, k * NW + wv, [&](V v, int c) { body(k, v, c); });
+  for (int k = 0; k < Sh::KB; ++k) {
+    psell_row(a, Sh::slice(k), [&](V v, int c) { body(k, v, c); });
     done(k);
   }
 }
 
+// s + sum of val * x[col] over groups p0 .. wd - 1 of one row (this lane's) of a packed
+// layout whose slice starts at group o; rounds of two groups, then one.
+template <typename T>
+__device__ __forceinline__ T pgroups_dot(const PSell<T>& a, int o, int wd, const T* x) {
+  T s = 0;
+  int p = 0;
+  for (; p + 2 <= wd; p += 2) {
+    T v[8];
+    int c[8];
+    pgroup(a, o + p * WAVE, v, c);
+    pgroup(a, o + (p + 1) * WAVE, v + 4, c + 4);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = fm(v[u], x[c[u]], s);
+  }
+  if (p < wd) {
+    T v[4];
+    int c[4];
+    pgroup(a, o + p * WAVE, v, c);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s = fm(v[u], x[c[u]], s);
+  }
+  return s;
+}
+
 // dst[r] = sum over row r of val * x[col] for the rows of a by-length packed
-// layout (rid gives each lane's row, -1 for padding); rows in rounds of two
-// groups (eight entries), then one group.
-template <int KB, int NW, typename T>
-__device__ __forceinline__ void sell_slots_store(const PSell<T>& a, const int* rid, const T* x, T* dst) {
+// layout dealt to (slot, wave) positions k NW + wave: (group offset, width,
+// first row id) per position, and the row of each lane (-1 for padding).
+template <class Sh, typename T>
+__device__ __forceinline__ void sell_slots_store(const PSell<T>& a, const int* pos, const int* rid, const T* x, T* dst) {
   const int wv = wave_id(), lane = lane_id();
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    const unsigned sl = (unsigned)(k * NW + wv);
-    const int o = cld(a.off, sl);
-    const int wd = cld(a.width, sl);
-    const int r = cld(rid, sl * WAVE + lane);
-    T acc = 0;
-    int p = 0;
-    for (; p + 2 <= wd; p += 2) {
-      T v[8];
-      int c[8];
-      pgroup(a, (unsigned)(o + p * WAVE + lane), v, c);
-      pgroup(a, (unsigned)(o + (p + 1) * WAVE + lane), v + 4, c + 4);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc += v[u] * x[c[u]];
-    }
-    if (p < wd) {
-      T v[4];
-      int c[4];
-      pgroup(a, (unsigned)(o + p * WAVE + lane), v, c);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc += v[u] * x[c[u]];
-    }
+  for (int k = 0; k < Sh::KB; ++k) {
+    const int4 t = cld(reinterpret_cast<const int4*>(pos), (unsigned)(k * Sh::NW + wv));
+    const int r = cld(rid, (unsigned)(t.z + lane));
+    const T acc = pgroups_dot(a, t.x, t.y, x);
     if (r >= 0) dst[r] = acc;
   }
 }
 
 // acc[k] = sum over slot k's row of val * x[col] for a packed layout by bus
-// slot (slices k NW + wave); rows in rounds of two groups, then one group.
-template <int KB, int NW, typename T>
-__device__ __forceinline__ void psell_slots_dot(const PSell<T>& a, const T* x, T (&acc)[KB]) {
-  const int wv = wave_id(), lane = lane_id();
+// slot (slices Sh::slice(k)).
+template <class Sh, typename T>
+__device__ __forceinline__ void psell_slots_dot(const PSell<T>& a, const T* x, T (&acc)[Sh::KB]) {
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    const unsigned sl = (unsigned)(k * NW + wv);
-    const int o = cld(a.off, sl);
-    const int wd = cld(a.width, sl);
-    T s = 0;
-    int p = 0;
-    for (; p + 2 <= wd; p += 2) {
-      T v[8];
-      int c[8];
-      pgroup(a, (unsigned)(o + p * WAVE + lane), v, c);
-      pgroup(a, (unsigned)(o + (p + 1) * WAVE + lane), v + 4, c + 4);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u] * x[c[u]];
-    }
-    if (p < wd) {
-      T v[4];
-      int c[4];
-      pgroup(a, (unsigned)(o + p * WAVE + lane), v, c);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) s += v[u] * x[c[u]];
-    }
-    acc[k] = s;
+  for (int k = 0; k < Sh::KB; ++k) {
+    const unsigned sl = (unsigned)Sh::slice(k);
+    acc[k] = pgroups_dot(a, cld(a.off, sl), cld(a.width, sl), x);
     settle(acc[k]);
   }
 }
 
-// out[OFF + k] = (A^-1 x)_i for the bus slots i = t + k BLOCK (zero past N), by
+// out[OFF + k] = (A^-1 x)_i for the bus slots (Shape::row; zero past N), by
 // the explicit factor passes E1 (rows into `aux` / the core right-hand side
 // into `tmp`), E2 (dense core into aux past c), E3 (rows in matrix order, read
 // from aux).  x holds the right-hand side in matrix order; aux (N entries)
@@ -500,88 +579,129 @@ __device__ __forceinline__ void psell_slots_dot(const PSell<T>& a, const T* x, T
 // With TO_LDS (not for a direct factor) E3 takes the by-length layout and
 // stores x_i to dst[i] (i < N) instead of filling out; dst may be x itself,
 // since x is no longer read by then.
-template <typename T, int BLOCK, int KB, int OFF, int K, bool TO_LDS = false>
+template <typename T, class Sh, int OFF, int K, bool TO_LDS = false>
 __device__ void efac_apply(const EfDev<T>& f, const T* x, T* aux, T* tmp, T (&out)[K], T* dst = nullptr) {
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int KB = Sh::KB;
   if (f.direct) {  // one sliced pass over A^-1 itself; no barrier, x read throughout
     T acc[KB];
-    psell_slots_dot<KB, NW>(f.inv, x, acc);
+    psell_slots_dot<Sh>(f.inv, x, acc);
 #pragma unroll
     for (int k = 0; k < KB; ++k) out[OFF + k] = acc[k];
     return;
   }
   const int lane = lane_id(), wv = wave_id();
   // (kept rolled: the loop indexes no register array, and its body is large)
-  const int nq = f.e1_nq;
+  // (group offset, width in groups, first row, split) of this wave's slices; width 0 past its list
+  const int nq = f.e1_nq[Sh::S / 2];
+  const int4* list = reinterpret_cast<const int4*>(f.e1_wave[Sh::S / 2]) + wv * nq;
+  auto put = [&](const int4& t, int r, T acc) {
+    if (t.w) acc = quad_total(acc);   // a long row lies on four lanes
+    if (r >= f.c) tmp[r - f.c] = acc;
+    else if (r >= 0) aux[r] = acc;
+  };
 #pragma unroll 1
   for (int q = 0; q < nq; ++q) {
-    // (group offset, width in groups, first row) of this wave's q-th slice; width 0 past its list
-    const int4 t = cld(reinterpret_cast<const int4*>(f.e1_wave), (unsigned)(wv * nq + q));
-    if (t.y > 0) {
-      const int r = cld(f.e1_row, (unsigned)(t.z + lane));
-      T acc = 0;
-      int p = 0;
-      for (; p + 2 <= t.y; p += 2) {  // two groups (eight entries) in flight per round while they last
-        T v[8];
-        int c[8];
-        pgroup(f.e1, (unsigned)(t.x + p * WAVE + lane), v, c);
-        pgroup(f.e1, (unsigned)(t.x + (p + 1) * WAVE + lane), v + 4, c + 4);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u] * x[c[u]];
-      }
-      if (p < t.y) {
-        T v[4];
-        int c[4];
-        pgroup(f.e1, (unsigned)(t.x + p * WAVE + lane), v, c);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc += v[u] * x[c[u]];
-      }
-      if (r >= f.c) tmp[r - f.c] = acc;
-      else if (r >= 0) aux[r] = acc;
-    }
+    const int4 t = cld(list, (unsigned)q);
+    if (t.y > 0) put(t, cld(f.e1_row, (unsigned)(t.z + lane)), pgroups_dot(f.e1, t.x, t.y, x));
   }
-  {  // the dense core reads whole packs: zero the core right-hand side past k
-    constexpr int P = 16 / (int)sizeof(T);
-    const int pad = (f.k + P - 1) / P * P - f.k;
-    if ((int)threadIdx.x < pad) tmp[f.k + threadIdx.x] = 0;
-  }
+  // The dense core reads whole packs, in FP64 in four parts of `qn` packs: zero
+  // the core right-hand side past k.
+  constexpr int P = 16 / (int)sizeof(T);
+  const int qn = ((f.k + P - 1) / P + 3) / 4;
+  if ((int)threadIdx.x < 4 * qn * P - f.k) tmp[f.k + threadIdx.x] = 0;
   __syncthreads();
   // S^-1 is stored in packs of P = 16 / sizeof(T) consecutive columns per row
-  // ([l / P][i][P], zero-padded), so each lane reads P entries with one
-  // 16-byte load.
-  constexpr int P = 16 / (int)sizeof(T);
-  const int kp = (f.k + P - 1) / P;
-  for (int i = threadIdx.x; i < f.k; i += BLOCK) {
-    T acc[4] = {0, 0, 0, 0};
-    int lp = 0;
-    for (; lp + 7 < kp; lp += 8) {
-      int4 v[8];
+  // ([l / P][i][P], zero-padded to 4 qn packs), so each lane reads P entries
+  // with one 16-byte load.  In FP64 a row's sum is that of its four quarters,
+  // each in column order: one thread forms all four, or, in a split workgroup,
+  // four lanes one each.  In FP32 one thread forms it as four sums over every
+  // fourth column.
+  if constexpr (sizeof(T) == 4) {
+    const int kp = (f.k + P - 1) / P;
+    for (int i = threadIdx.x; i < f.k; i += Sh::BLOCK) {
+      T acc[4] = {0, 0, 0, 0};
+      auto round = [&](int lp, auto n) {
+        constexpr int N = decltype(n)::value;
+        int4 v[N];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((lp + u) * f.k + i));
+        for (int u = 0; u < N; ++u) v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((lp + u) * f.k + i));
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        T e[P];
-        __builtin_memcpy(e, &v[u], 16);
+        for (int u = 0; u < N; ++u) {
+          T e[P];
+          __builtin_memcpy(e, &v[u], 16);
 #pragma unroll
-        for (int q = 0; q < P; ++q) acc[q & 3] += e[q] * tmp[(lp + u) * P + q];
+          for (int q = 0; q < P; ++q) acc[q & 3] = fm(e[q], tmp[(lp + u) * P + q], acc[q & 3]);
+        }
+      };
+      int lp = 0;
+      for (; lp + 8 <= kp; lp += 8) round(lp, std::integral_constant<int, 8>{});
+      for (; lp < kp; ++lp) round(lp, std::integral_constant<int, 1>{});
+      aux[f.c + i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    }
+  } else if constexpr (Sh::S == 1) {
+    for (int i = threadIdx.x; i < f.k; i += Sh::BLOCK) {
+      T acc[4] = {0, 0, 0, 0};
+      auto round = [&](int l, auto n) {   // n packs of each quarter
+        constexpr int N = 4 * decltype(n)::value;
+        int4 v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+          v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)(((u & 3) * qn + l + (u >> 2)) * f.k + i));
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+          T e[P];
+          __builtin_memcpy(e, &v[u], 16);
+#pragma unroll
+          for (int q = 0; q < P; ++q)
+            acc[u & 3] = fm(e[q], tmp[((u & 3) * qn + l + (u >> 2)) * P + q], acc[u & 3]);
+        }
+      };
+      int l = 0;
+      for (; l + 2 <= qn; l += 2) round(l, std::integral_constant<int, 2>{});
+      if (l < qn) round(l, std::integral_constant<int, 1>{});
+      aux[f.c + i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    }
+  } else {
+    // lanes 16 p .. 16 p + 15 take part p of sixteen rows (the lanes of a quad
+    // read one line: with a part per lane of a quad, this pass took 4 times as long)
+    const int part = lane / 16;
+    for (int i0 = wv * 16; i0 < f.k; i0 += Sh::NW * 16) {
+      const int i = i0 + lane % 16;
+      T acc = 0;
+      if (i < f.k) {
+        int l = 0;
+        for (; l + 8 <= qn; l += 8) {
+          int4 v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((part * qn + l + u) * f.k + i));
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            T e[P];
+            __builtin_memcpy(e, &v[u], 16);
+#pragma unroll
+            for (int q = 0; q < P; ++q) acc = fm(e[q], tmp[(part * qn + l + u) * P + q], acc);
+          }
+        }
+        for (; l < qn; ++l) {
+          const int4 v = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((part * qn + l) * f.k + i));
+          T e[P];
+          __builtin_memcpy(e, &v, 16);
+#pragma unroll
+          for (int q = 0; q < P; ++q) acc = fm(e[q], tmp[(part * qn + l) * P + q], acc);
+        }
       }
+      acc = row_pair_sum<true>(row_pair_sum<false>(acc));
+      if (i < f.k && part == 0) aux[f.c + i] = acc;
     }
-    for (; lp < kp; ++lp) {
-      const int4 v = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)(lp * f.k + i));
-      T e[P];
-      __builtin_memcpy(e, &v, 16);
-#pragma unroll
-      for (int q = 0; q < P; ++q) acc[q & 3] += e[q] * tmp[lp * P + q];
-    }
-    aux[f.c + i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   }
   if (f.k > 0) __syncthreads();  // with no core, E3 reads only what E1 wrote
   if constexpr (TO_LDS) {
-    sell_slots_store<KB, NW>(f.e3s, f.e3s_row, aux, dst);
+    sell_slots_store<Sh>(f.e3s, f.e3s_pos[Sh::S / 2], f.e3s_row, aux, dst);
     return;
   }
   T acc[KB];
-  psell_slots_dot<KB, NW>(f.e3, aux, acc);
+  psell_slots_dot<Sh>(f.e3, aux, acc);
 #pragma unroll
   for (int k = 0; k < KB; ++k) out[OFF + k] = acc[k];
 }
@@ -595,36 +715,40 @@ __device__ void efac_apply(const EfDev<T>& f, const T* x, T* aux, T* tmp, T (&ou
 // and each thread reads its own entries back); the B'' right-hand side at
 // [nth, nth + npq) with its passes at [0, npq).  The caller guarantees that
 // no thread still reads the LDS vector area.
-template <typename T, int BLOCK, int KB>
-__device__ void precond(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 * KB], const Smem<T>& s) {
-  constexpr int NW = BLOCK / WAVE;
+template <typename T, class Sh>
+__device__ void precond(const TxDev<T>* netp, const Ws<Sh>& ws, const Held<T, Sh>& held, T (&w)[2 * Sh::KB],
+                        const Smem<T>& s) {
+  constexpr int KB = Sh::KB;
   const TxDev<T> net = load_desc(netp);
   const unsigned nth = net.nth, npq = net.npq;
   T* X = s.xs;
   T* Y = s.xs + nth;
-  constexpr int G = Ws<BLOCK, KB>::G;
+  constexpr int G = Ws<Sh>::G;
 #pragma unroll
   for (int k = 0; k < KB; k += G) {
     T iv[2];
-    if constexpr (G == 2) ws.template get_ivm2<T>(k, iv);
+    if constexpr (Held<T, Sh>::on) {
+#pragma unroll
+      for (int u = 0; u < G; ++u) iv[u] = held.iv[k + u];
+    } else if constexpr (G == 2) ws.template get_ivm2<T>(k, iv);
     else iv[0] = ws.template get_ivm<T>(k);
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const unsigned i = row<BLOCK>(k + u);
+      const unsigned i = Sh::row(k + u);
       const T v = w[k + u] * iv[u];
       if (i < nth) X[i] = v;
     }
   }
   __syncthreads();
   if (net.bp.direct) {
-    efac_apply<T, BLOCK, KB, 0>(net.bp, X, Y, s.tmp, w);
+    efac_apply<T, Sh, 0>(net.bp, X, Y, s.tmp, w);
     if (npq > 0) {
       // the direct pass read X throughout; the barrier after the stores also
       // orders its reads of Y before Y is written again
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
-        const unsigned i = row<BLOCK>(k);
+        const unsigned i = Sh::row(k);
         if (i < nth) X[i] = w[k];
       }
       __syncthreads();
@@ -633,11 +757,11 @@ __device__ void precond(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 
     // X was last read before the first barrier of the B' passes, so their
     // E3 pass stores z_Theta over it; the barrier also orders the passes'
     // reads of Y before Y is written again.
-    efac_apply<T, BLOCK, KB, 0, 2 * KB, true>(net.bp, X, Y, s.tmp, w, X);
+    efac_apply<T, Sh, 0, 2 * KB, true>(net.bp, X, Y, s.tmp, w, X);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       w[k] = i < nth ? X[i] : (T)0;
     }
   }
@@ -647,7 +771,10 @@ __device__ void precond(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 
     T iv[KB];
 #pragma unroll
     for (int k = 0; k < KB; k += G) {
-      if constexpr (G == 2) {
+      if constexpr (Held<T, Sh>::on) {
+#pragma unroll
+        for (int u = 0; u < G; ++u) iv[k + u] = held.iv[k + u];
+      } else if constexpr (G == 2) {
         T t[2];
         ws.template get_ivm2<T>(k, t);
         iv[k] = t[0];
@@ -657,38 +784,45 @@ __device__ void precond(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 
       }
     }
     T gz[KB];
-    psell_slots_dot<KB, NW>(nt.g, X, gz);
+    psell_slots_dot<Sh>(nt.g, X, gz);
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       const T t = (w[KB + k] - gz[k]) * iv[k];
       if (i < npq) Y[i] = t;
     }
     __syncthreads();
-    efac_apply<T, BLOCK, KB, KB>(nt.bpp, Y, X, s.tmp, w);
+    efac_apply<T, Sh, KB>(nt.bpp, Y, X, s.tmp, w);
   }
 }
 
 // w <- J w, the Jacobian of the mismatch at the current V (with I = Ybus V).
 // yv: the scenario's own Ybus values (layout of net.yT), or null for the
 // network's.  Ends with a barrier.
-template <typename T, int BLOCK, int KB>
-__device__ void jvp(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 * KB], T* lds,
+template <typename T, class Sh>
+__device__ void jvp(const TxDev<T>* netp, const Ws<Sh>& ws, const Held<T, Sh>& held, T (&w)[2 * Sh::KB], T* lds,
                     const typename Vec2<T>::type* yv) {
   using T2 = typename Vec2<T>::type;
   TxDev<T> net = load_desc(netp);
   if (yv) net.yT.val = yv;
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int KB = Sh::KB;
   const unsigned nth = net.nth, npq = net.npq;
   T2* dv = reinterpret_cast<T2*>(lds);
   // dV_i = V_i (j p_theta + p_|V| / |V|).  The input w is dead after this
   // loop, so the own buses' V stays in its registers for the second phase.
-  constexpr int G = Ws<BLOCK, KB>::G;
+  constexpr int G = Ws<Sh>::G;
   T vre[KB], vim[KB];
 #pragma unroll
   for (int k = 0; k < KB; k += G) {
     T iv[2];
-    if constexpr (G == 2) {
+    if constexpr (Held<T, Sh>::on) {
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        iv[u] = held.iv[k + u];
+        vre[k + u] = held.vr[k + u];
+        vim[k + u] = held.vi[k + u];
+      }
+    } else if constexpr (G == 2) {
       ws.template get_ivm2<T>(k, iv);
       T re[2], im[2];
       ws.template get_v2<T>(k, re, im);
@@ -702,20 +836,25 @@ __device__ void jvp(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 * KB
     }
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const unsigned i = row<BLOCK>(k + u);
+      const unsigned i = Sh::row(k + u);
       const T a = w[KB + k + u] * iv[u];
       T2 d;
-      d.x = vre[k + u] * a - vim[k + u] * w[k + u];
-      d.y = vim[k + u] * a + vre[k + u] * w[k + u];
+      d.x = mul_sub(vre[k + u], a, vim[k + u], w[k + u]);
+      d.y = mul_add(vim[k + u], a, vre[k + u], w[k + u]);
       dv[i] = d;
     }
   }
   __syncthreads();
   // The own buses' I is fetched one slot pair ahead, so its HBM latency
   // overlaps the previous slots' rows.
-  const int wv = wave_id();
   T cIr[2], cIi[2], nIr[2], nIi[2];
-  if constexpr (G == 2) ws.template get_i2<T>(0, nIr, nIi);
+  if constexpr (Held<T, Sh>::on) {
+#pragma unroll
+    for (int u = 0; u < KB; ++u) {   // (every slot: KB <= 2)
+      nIr[u] = held.ir[u];
+      nIi[u] = held.ii[u];
+    }
+  } else if constexpr (G == 2) ws.template get_i2<T>(0, nIr, nIi);
   else ws.template get_i<T>(0, nIr[0], nIi[0]);
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
@@ -731,138 +870,361 @@ __device__ void jvp(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, T (&w)[2 * KB
     }
     const T Ir = cIr[k % G], Ii = cIi[k % G], vr = vre[k], vi = vim[k];
     T dIr = 0, dIi = 0;
-    psell_row(net.yT, k * NW + wv, [&](T2 y, int c) {
+    psell_row(net.yT, Sh::slice(k), [&](T2 y, int c) {
       const T2 d = dv[c];
-      dIr += y.x * d.x - y.y * d.y;
-      dIi += y.x * d.y + y.y * d.x;
+      if constexpr (sizeof(T) == 4) {
+        dIr += mul_sub(y.x, d.x, y.y, d.y);
+        dIi += mul_add(y.x, d.y, y.y, d.x);
+      } else {
+        dIr = fm(-y.y, d.y, fm(y.x, d.x, dIr));
+        dIi = fm(y.y, d.x, fm(y.x, d.y, dIi));
+      }
     });
-    const unsigned i = row<BLOCK>(k);
+    const unsigned i = Sh::row(k);
     const T2 d = dv[i];
     // dS = dV conj(I) + V conj(dI): real part on Theta, imaginary part on Q
-    w[k] = i < nth ? d.x * Ir + d.y * Ii + vr * dIr + vi * dIi : (T)0;
-    w[KB + k] = i < npq ? d.y * Ir - d.x * Ii + vi * dIr - vr * dIi : (T)0;
+    if constexpr (sizeof(T) == 4) {
+      w[k] = i < nth ? d.x * Ir + d.y * Ii + vr * dIr + vi * dIi : (T)0;
+      w[KB + k] = i < npq ? d.y * Ir - d.x * Ii + vi * dIr - vr * dIi : (T)0;
+    } else {
+      w[k] = i < nth ? fm(vi, dIi, fm(vr, dIr, fm(d.y, Ii, d.x * Ir))) : (T)0;
+      w[KB + k] = i < npq ? fm(-vr, dIi, fm(vi, dIr, fm(-d.x, Ii, d.y * Ir))) : (T)0;
+    }
     settle(w[k]);
     settle(w[KB + k]);
   }
   __syncthreads();
 }
 
-// Writes part[i NW + wave] = the wave's share of <basis_i, w> for i < nv and
-// part[nv NW + wave] = the wave's share of ss; ends with a barrier.
-template <typename T, int BLOCK, int KB>
-__device__ void multi_dot(const Basis<T, BLOCK, KB>& basis, int nv, const T (&w)[2 * KB], T ss, T* part) {
-  constexpr int NW = BLOCK / WAVE;
-  const int lane = lane_id(), wid = wave_id();
-  int i = 0;
-  constexpr int G = Basis<T, BLOCK, KB>::G;
-  for (; i + 1 < nv; i += 2) {  // two vectors per round: twice the loads in flight
-    T a0 = 0, a1 = 0;
-#pragma unroll
-    for (int g = 0; g < 2 * KB / G; ++g) {
-      T e0[G], e1[G];
-      basis.ldg(i, g, e0);
-      basis.ldg(i + 1, g, e1);
-#pragma unroll
-      for (int q = 0; q < G; ++q) {
-        a0 += e0[q] * w[g * G + q];
-        a1 += e1[q] * w[g * G + q];
-      }
-    }
-    a0 = wave_total(a0);
-    a1 = wave_total(a1);
-    if (lane == 0) {
-      part[i * NW + wid] = a0;
-      part[(i + 1) * NW + wid] = a1;
-    }
-  }
-  if (i < nv) {
-    T a0 = 0;
-#pragma unroll
-    for (int g = 0; g < 2 * KB / G; ++g) {
-      T e0[G];
-      basis.ldg(i, g, e0);
-#pragma unroll
-      for (int q = 0; q < G; ++q) a0 += e0[q] * w[g * G + q];
-    }
-    a0 = wave_total(a0);
-    if (lane == 0) part[i * NW + wid] = a0;
-  }
-  ss = wave_total(ss);
-  if (lane == 0) part[nv * NW + wid] = ss;
-  __syncthreads();
+// The wave's total of a thread's per-unit sums (see Shape), in every lane.
+template <typename T, int NU>
+__device__ __forceinline__ T units_total(T (&a)[NU]) {
+  if constexpr (NU == 1) return wave_total(a[0]);
+  else return wave_total_units<NU>(a);
 }
 
-template <typename T, int NW>
-__device__ __forceinline__ T part_sum(const T* part, int i) {
+// unit of a thread's slot k (angles, then magnitudes)
+template <class Sh>
+__device__ __forceinline__ constexpr int unit_of(int k) {
+  return k % Sh::KB / Sh::U;
+}
+
+// sum over waves and units of one reduction's partials, part[w S + g] of
+// virtual wave w and group g
+template <class Sh, typename T>
+__device__ __forceinline__ T part_sum(const T* part) {
   T s = 0;
 #pragma unroll
-  for (int u = 0; u < NW; ++u) s += part[i * NW + u];
+  for (int w = 0; w < Sh::NWV; ++w) {
+    if constexpr (Sh::S == 1) s += part[w];
+    else if constexpr (Sh::S == 2) s += part[2 * w] + part[2 * w + 1];
+    else s += (part[4 * w] + part[4 * w + 1]) + (part[4 * w + 2] + part[4 * w + 3]);
+  }
   return s;
 }
 
-// w -= sum_i h_i basis_i with h_i from the partials; returns sum_i h_i^2.
-template <typename T, int BLOCK, int KB>
-__device__ T subtract_proj(const Basis<T, BLOCK, KB>& basis, int nv, T (&w)[2 * KB], const T* part) {
-  constexpr int NW = BLOCK / WAVE;
-  constexpr int G = Basis<T, BLOCK, KB>::G;
+// this wave's place among a reduction's partials
+template <class Sh>
+__device__ __forceinline__ int part_slot() {
+  return Sh::S == 1 ? wave_id() : (wave_id() % Sh::NWV) * Sh::S + Sh::group();
+}
+
+// Workgroup sum of per-unit sums, into every thread.  `part` (NW entries) must
+// not be written again before the next barrier: callers alternate between two buffers.
+template <class Sh, typename T>
+__device__ T block_sum_units(T (&a)[Sh::NU], T* part) {
+  const T v = units_total(a);
+  if (lane_id() == 0) part[part_slot<Sh>()] = v;
+  __syncthreads();
+  return part_sum<Sh>(part);
+}
+
+// per-unit sums of squares of w
+template <class Sh, typename T>
+__device__ __forceinline__ void squares(const T (&w)[2 * Sh::KB], T (&a)[Sh::NU]) {
+#pragma unroll
+  for (int u = 0; u < Sh::NU; ++u) a[u] = 0;
+#pragma unroll
+  for (int k = 0; k < 2 * Sh::KB; ++k) a[unit_of<Sh>(k)] = fm(w[k], w[k], a[unit_of<Sh>(k)]);
+}
+
+// FP32 sums (see Shape).  x[k] = slot k of the whole column this thread of the
+// first group sums over (angles, then magnitudes): its own slots unsplit, else from
+// LDS, where every thread has put its slots (hand_over; the caller's barrier orders it).
+template <class Sh>
+__device__ __forceinline__ void hand_over(const float (&w)[2 * Sh::KB], float* area) {
+  if constexpr (Sh::S > 1) {
+#pragma unroll
+    for (int k = 0; k < 2 * Sh::KB; ++k)
+      area[(k / Sh::KB * Sh::KBT + Sh::group() * Sh::KB + k % Sh::KB) * Sh::VB + (int)Sh::col()] = w[k];
+  }
+}
+template <class Sh>
+__device__ __forceinline__ void column(const float (&w)[2 * Sh::KB], const float* area, float (&x)[2 * Sh::KBT]) {
+#pragma unroll
+  for (int k = 0; k < 2 * Sh::KBT; ++k) {
+    if constexpr (Sh::S > 1) x[k] = area[k * Sh::VB + (int)Sh::col()];
+    else x[k] = w[k];
+  }
+}
+// the same column of basis vector i
+template <class Sh, bool L>
+__device__ __forceinline__ void basis_column(const Basis<float, Sh>& basis, int i, float (&e)[2 * Sh::KBT]) {
+  constexpr int G = Basis<float, Sh>::G, KB = Sh::KB;
+#pragma unroll
+  for (int gr = 0; gr < Sh::S; ++gr) {
+#pragma unroll
+    for (int g = 0; g < 2 * KB / G; ++g) {
+      float r[G];
+      basis.template ldg_of<L>(i, g, r, (unsigned)(gr * Sh::VB) + Sh::col());
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const int k = g * G + q;
+        e[k / KB * Sh::KBT + gr * KB + k % KB] = r[q];
+      }
+    }
+  }
+}
+
+// Workgroup sum of squares of w, into every thread: in FP64 by units, in FP32
+// in column order.  `part` (NW entries) must not be written again before the
+// next barrier; `area` (FP32, split) not while another wave may read it.
+template <class Sh>
+__device__ double block_squares(const double (&w)[2 * Sh::KB], double* part, double*) {
+  double ss[Sh::NU];
+  squares<Sh>(w, ss);
+  return block_sum_units<Sh>(ss, part);
+}
+template <class Sh>
+__device__ float block_squares(const float (&w)[2 * Sh::KB], float* part, float* area) {
+  if constexpr (Sh::S > 1) {
+    hand_over<Sh>(w, area);
+    __syncthreads();
+  }
+  if (Sh::group() == 0) {
+    float x[2 * Sh::KBT], ss = 0;
+    column<Sh>(w, area, x);
+#pragma unroll
+    for (int k = 0; k < 2 * Sh::KBT; ++k) ss += x[k] * x[k];
+    ss = wave_total(ss);
+    if (lane_id() == 0) part[wave_id()] = ss;
+  }
+  __syncthreads();
+  float s = 0;
+#pragma unroll
+  for (int v = 0; v < Sh::NWV; ++v) s += part[v];
+  return s;
+}
+
+// Dot products h_i = <basis_i, w> (i < nv), returned in lane i of every wave,
+// and <w, w> in *total, by one reduction over part[i NW ..].
+template <class Sh>
+__device__ float multi_dot(const Basis<float, Sh>& basis, int nv, const float (&w)[2 * Sh::KB], float* part,
+                           float* area, float* total) {
+  constexpr int NWV = Sh::NWV, K = 2 * Sh::KBT;
+  const int lane = lane_id(), wv = wave_id();
+  if constexpr (Sh::S > 1) {
+    hand_over<Sh>(w, area);
+    __syncthreads();
+  }
+  if (Sh::group() == 0) {
+    float x[K];
+    column<Sh>(w, area, x);
+    auto dots = [&](int i, int i1, auto where) {
+      constexpr bool L = decltype(where)::value;
+      for (; i + 1 < i1; i += 2) {  // two vectors per round: twice the loads in flight
+        float a0 = 0, a1 = 0, e0[K], e1[K];
+        basis_column<Sh, L>(basis, i, e0);
+        basis_column<Sh, L>(basis, i + 1, e1);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          a0 += e0[k] * x[k];
+          a1 += e1[k] * x[k];
+        }
+        a0 = wave_total(a0);
+        a1 = wave_total(a1);
+        if (lane == 0) {
+          part[i * NWV + wv] = a0;
+          part[(i + 1) * NWV + wv] = a1;
+        }
+      }
+      if (i < i1) {
+        float a0 = 0, e0[K];
+        basis_column<Sh, L>(basis, i, e0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) a0 += e0[k] * x[k];
+        a0 = wave_total(a0);
+        if (lane == 0) part[i * NWV + wv] = a0;
+      }
+    };
+    int in_lds = 0;
+    if constexpr (Sh::S > 1) {
+      in_lds = nv < basis.nl ? nv : basis.nl;
+      dots(0, in_lds, std::true_type{});
+    }
+    dots(in_lds, nv, std::false_type{});
+    float ss = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) ss += x[k] * x[k];
+    ss = wave_total(ss);
+    if (lane == 0) part[nv * NWV + wv] = ss;
+  }
+  __syncthreads();
+  auto sum = [&](int i) {
+    float s = 0;
+#pragma unroll
+    for (int v = 0; v < NWV; ++v) s += part[i * NWV + v];
+    return s;
+  };
+  *total = sum(nv);
+  return sum(lane < nv ? lane : nv);
+}
+
+template <class Sh>
+__device__ double multi_dot(const Basis<double, Sh>& basis, int nv, const double (&w)[2 * Sh::KB], double* part,
+                            double*, double* total) {
+  using T = double;
+  constexpr int NW = Sh::NW, KB = Sh::KB, NU = Sh::NU;
+  const int lane = lane_id(), slot = part_slot<Sh>();
+  constexpr int G = Basis<T, Sh>::G;
+  // Two vectors per round: twice the loads in flight.  (Not with four units:
+  // their sums for two vectors cost 20 more spilled registers, and the
+  // 2000-bus batch of 1024 ran 2.28 against 1.99 ms.)
+  constexpr bool TWO = NU < 4;
+  auto dots = [&](int i, int i1, auto where) {
+    constexpr bool L = decltype(where)::value;
+    for (; TWO && i + 1 < i1; i += 2) {
+      T a0[NU] = {}, a1[NU] = {};
+#pragma unroll
+      for (int g = 0; g < 2 * KB / G; ++g) {
+        T e0[G], e1[G];
+        basis.template ldg<L>(i, g, e0);
+        basis.template ldg<L>(i + 1, g, e1);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+          const int u = unit_of<Sh>(g * G + q);
+          a0[u] = fm(e0[q], w[g * G + q], a0[u]);
+          a1[u] = fm(e1[q], w[g * G + q], a1[u]);
+        }
+      }
+      const T t0 = units_total(a0), t1 = units_total(a1);
+      if (lane == 0) {
+        part[i * NW + slot] = t0;
+        part[(i + 1) * NW + slot] = t1;
+      }
+    }
+    for (; i < i1; ++i) {
+      T a0[NU] = {};
+#pragma unroll
+      for (int g = 0; g < 2 * KB / G; ++g) {
+        T e0[G];
+        basis.template ldg<L>(i, g, e0);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+          const int u = unit_of<Sh>(g * G + q);
+          a0[u] = fm(e0[q], w[g * G + q], a0[u]);
+        }
+      }
+      const T t0 = units_total(a0);
+      if (lane == 0) part[i * NW + slot] = t0;
+    }
+  };
+  int in_lds = 0;
+  if constexpr (Sh::S > 1) {
+    in_lds = nv < basis.nl ? nv : basis.nl;
+    dots(0, in_lds, std::true_type{});
+  }
+  dots(in_lds, nv, std::false_type{});
+  T ss[NU];
+  squares<Sh>(w, ss);
+  const T t = units_total(ss);
+  if (lane == 0) part[nv * NW + slot] = t;
+  __syncthreads();
+  *total = part_sum<Sh>(part + nv * NW);
+  return part_sum<Sh>(part + (lane < nv ? lane : nv) * NW);
+}
+
+// w -= sum_i h_i basis_i with h_i in lane i of h; returns sum_i h_i^2.
+template <typename T, class Sh>
+__device__ T subtract_proj(const Basis<T, Sh>& basis, int nv, T (&w)[2 * Sh::KB], T h) {
+  constexpr int KB = Sh::KB;
+  constexpr int G = Basis<T, Sh>::G;
   T hh = 0;
-  int i = 0;
-  for (; i + 1 < nv; i += 2) {
-    const T h0 = part_sum<T, NW>(part, i), h1 = part_sum<T, NW>(part, i + 1);
-    hh += h0 * h0 + h1 * h1;
+  auto part = [&](int i, int i1, auto where) {
+    constexpr bool L = decltype(where)::value;
+    for (; i + 1 < i1; i += 2) {
+      const T h0 = lane_value(h, i), h1 = lane_value(h, i + 1);
+      if constexpr (sizeof(T) == 4) hh += h0 * h0 + h1 * h1;
+      else hh = fm(h1, h1, fm(h0, h0, hh));
 #pragma unroll
-    for (int g = 0; g < 2 * KB / G; ++g) {
-      T e0[G], e1[G];
-      basis.ldg(i, g, e0);
-      basis.ldg(i + 1, g, e1);
+      for (int g = 0; g < 2 * KB / G; ++g) {
+        T e0[G], e1[G];
+        basis.template ldg<L>(i, g, e0);
+        basis.template ldg<L>(i + 1, g, e1);
 #pragma unroll
-      for (int q = 0; q < G; ++q) w[g * G + q] -= h0 * e0[q] + h1 * e1[q];
+        for (int q = 0; q < G; ++q) {
+          if constexpr (sizeof(T) == 4) w[g * G + q] -= h0 * e0[q] + h1 * e1[q];
+          else w[g * G + q] = fm(-h1, e1[q], fm(-h0, e0[q], w[g * G + q]));
+        }
+      }
     }
-  }
-  if (i < nv) {
-    const T h0 = part_sum<T, NW>(part, i);
-    hh += h0 * h0;
+    if (i < i1) {
+      const T h0 = lane_value(h, i);
+      hh = fm(h0, h0, hh);
 #pragma unroll
-    for (int g = 0; g < 2 * KB / G; ++g) {
-      T e0[G];
-      basis.ldg(i, g, e0);
+      for (int g = 0; g < 2 * KB / G; ++g) {
+        T e0[G];
+        basis.template ldg<L>(i, g, e0);
 #pragma unroll
-      for (int q = 0; q < G; ++q) w[g * G + q] -= h0 * e0[q];
+        for (int q = 0; q < G; ++q) w[g * G + q] = fm(-h0, e0[q], w[g * G + q]);
+      }
     }
+  };
+  int in_lds = 0;
+  if constexpr (Sh::S > 1) {
+    in_lds = nv < basis.nl ? nv : basis.nl;
+    part(0, in_lds, std::true_type{});
   }
+  part(in_lds, nv, std::false_type{});
   return hh;
 }
 
 // Mismatch at the current (theta, |V|): writes V, 1/|V|, I and F to the
 // workspace and returns max |F| (NaN if any entry is NaN).  yv: the scenario's
 // own Ybus values (layout of net.y64), or null.  Ends with a barrier.
-template <typename T, int BLOCK, int KB>
-__device__ double mismatch(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, double2* vs, double* part,
+template <typename T, class Sh>
+__device__ double mismatch(const TxDev<T>* netp, const Ws<Sh>& ws, double2* vs, double* part,
                            const double2* yv) {
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int KB = Sh::KB;
   TxDev<T> net = load_desc(netp);
   if (yv) net.y64.val = yv;
   const unsigned nth = net.nth, npq = net.npq;
-  // every slot's angle and magnitude requested at once (in pairs), then one
-  // slot at a time through sincos
-  double th[KB], vmag[KB];
-  ws.ld_all(TH, th);
-  ws.ld_all(VM, vmag);
+  // Every slot's angle and magnitude requested at once, put into the slot's
+  // own place in LDS, then slot by slot through sincos.  (That loop stays rolled: the
+  // constants of sincos stay in registers, where eight inlined copies of it
+  // spilled them; 2000-bus batch of 1024 1998 -> 1956 us.)
+  {
+    double th[KB], vmag[KB];
+    ws.ld_all(TH, th);
+    ws.ld_all(VM, vmag);
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    slot_fence();
-    const unsigned i = row<BLOCK>(k);
-    double sn, cs;
-    sincos(th[k], &sn, &cs);
-    const double vm = vmag[k];
-    double2 v;
-    v.x = vm * cs;
-    v.y = vm * sn;
-    ws.template put_vi<T>(k, v.x, v.y, 1.0 / vm);
-    vs[i] = v;
+    for (int k = 0; k < KB; ++k) vs[Sh::row(k)] = make_double2(th[k], vmag[k]);
+    constexpr int UNROLL = KB <= 2 ? KB : 1;
+#pragma unroll UNROLL
+    for (int k = 0; k < KB; ++k) {
+      const unsigned i = Sh::row(k);
+      const double2 tv = vs[i];
+      double sn, cs;
+      sincos(tv.x, &sn, &cs);
+      const double vm = tv.y;
+      double2 v;
+      v.x = vm * cs;
+      v.y = vm * sn;
+      ws.template put_vi<T>(k, v.x, v.y, 1.0 / vm);
+      vs[i] = v;
+    }
   }
   __syncthreads();
-  const int wv = wave_id();
   double fmax = 0.0;
   double pin[KB], qin[KB];
   ws.ld_all(PIN, pin);
@@ -871,22 +1233,33 @@ __device__ double mismatch(const TxDev<T>* netp, const Ws<BLOCK, KB>& ws, double
   for (int k = 0; k < KB; ++k) {
     const double pk = pin[k], qk = qin[k];
     double Ir = 0.0, Ii = 0.0;
-    psell_row(net.y64, k * NW + wv, [&](double2 y, int c) {
+    psell_row(net.y64, Sh::slice(k), [&](double2 y, int c) {
       const double2 v = vs[c];
-      Ir += y.x * v.x - y.y * v.y;
-      Ii += y.x * v.y + y.y * v.x;
+      if constexpr (sizeof(T) == 4) {
+        Ir += y.x * v.x - y.y * v.y;
+        Ii += y.x * v.y + y.y * v.x;
+      } else {
+        Ir = fm(-y.y, v.y, fm(y.x, v.x, Ir));
+        Ii = fm(y.y, v.x, fm(y.x, v.y, Ii));
+      }
     });
-    const unsigned i = row<BLOCK>(k);
+    const unsigned i = Sh::row(k);
     const double2 v = vs[i];
     ws.template put_i<T>(k, Ir, Ii);
-    const double ft = i < nth ? v.x * Ir + v.y * Ii - pk : 0.0;
-    const double fv = i < npq ? v.y * Ir - v.x * Ii - qk : 0.0;
+    double ft, fv;
+    if constexpr (sizeof(T) == 4) {
+      ft = i < nth ? v.x * Ir + v.y * Ii - pk : 0.0;
+      fv = i < npq ? v.y * Ir - v.x * Ii - qk : 0.0;
+    } else {
+      ft = i < nth ? fm(v.y, Ii, v.x * Ir) - pk : 0.0;
+      fv = i < npq ? fm(-v.x, Ii, v.y * Ir) - qk : 0.0;
+    }
     ws.st(FP, k, ft);
     ws.st(FP, KB + k, fv);
     fmax = nanmax(fmax, nanmax(fabs(ft), fabs(fv)));
     settle(fmax);
   }
-  return block_nanmax<BLOCK>(fmax, part);
+  return block_nanmax<Sh::BLOCK>(fmax, part);
 }
 
 // Algorithmic HBM bytes of one scenario (the byte model reported with the
@@ -926,13 +1299,13 @@ struct ByteModel {
 // rotations to the new Hessenberg column itself (same data, same operations),
 // so no barrier is needed after them; thread 0 alone stores H, the rotations
 // and the rotated right-hand side for later steps.
-template <typename T, int BLOCK, int KB, typename ApplyA, typename ApplyM>
-__device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, KB>& ws, int bpl, int xpl,
-                           const Basis<T, BLOCK, KB>& basis, int R, int max_restarts, T rtol, const Smem<T>& s,
+template <typename T, class Sh, typename ApplyA, typename ApplyM>
+__device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<Sh>& ws, int bpl, int xpl,
+                           const Basis<T, Sh>& basis, int R, int max_restarts, T rtol, const Smem<T>& s,
                            bool* converged, const ByteModel& bm, double* work) {
-  constexpr int NW = BLOCK / WAVE;
-  constexpr int K = 2 * KB;
-  constexpr int G = Basis<T, BLOCK, KB>::G;
+  constexpr int NW = Sh::NW;
+  constexpr int K = 2 * Sh::KB;
+  constexpr int G = Basis<T, Sh>::G;
   const unsigned pstride = (unsigned)(R + 2) * NW;
   int par = 0;
   auto next_part = [&]() {
@@ -969,10 +1342,7 @@ __device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, K
       }
       apply_m(w);
       if (j < 0) {
-        T ss = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) ss += w[k] * w[k];
-        const T beta = sqrt(block_sum<T, BLOCK>(ss, next_part()));
+        const T beta = sqrt(block_squares<Sh>(w, next_part(), s.wv));
         if (cycle == 0) beta0 = beta;
         if (!(beta > rtol * beta0) || beta == (T)0) {
           done = !(beta > rtol * beta0);
@@ -988,13 +1358,9 @@ __device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, K
         res = beta;
         continue;
       }
-      T ss0 = 0;
-#pragma unroll
-      for (int k = 0; k < K; ++k) ss0 += w[k] * w[k];
-      T* p1 = next_part();
-      multi_dot<T, BLOCK, KB>(basis, j + 1, w, ss0, p1);
-      const T hh1 = subtract_proj<T, BLOCK, KB>(basis, j + 1, w, p1);
-      const T wn2 = part_sum<T, NW>(p1, j + 1);
+      T wn2;
+      T h = multi_dot<Sh>(basis, j + 1, w, next_part(), s.wv, &wn2);
+      const T hh1 = subtract_proj<T, Sh>(basis, j + 1, w, h);
       // ||w'||^2 = ||w||^2 - sum h_i^2, unless that difference has cancelled
       // below tau ||w||^2 (its relative error is then above eps / tau): then
       // by its own reduction.  The identity assumes an orthonormal basis; its
@@ -1003,37 +1369,35 @@ __device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, K
       // 2.7 times the steps), so below rtol 1e-6 the norm is always reduced.
       // Every thread takes the same branch (the same partials, summed in the
       // same order, and the same rtol).
-      T s1 = 0;
-#pragma unroll
-      for (int k = 0; k < K; ++k) s1 += w[k] * w[k];
       T nrm2 = wn2 - hh1;
       constexpr T tau = sizeof(T) == 8 ? (T)1e-4 : (T)1e-3;
-      if (!(rtol >= (T)1e-6) || !(nrm2 >= tau * wn2)) nrm2 = block_sum<T, BLOCK>(s1, s.redn);
+      if (!(rtol >= (T)1e-6) || !(nrm2 >= tau * wn2)) nrm2 = block_squares<Sh>(w, s.redn, s.wv);
       // Second pass only when the projection removed all but 1/64 of the
       // norm: the first pass's rounding then leaves the new vector orthogonal
       // to about 64 ulp, far below the GMRES tolerance, and a pass is saved in
       // most steps.
       const bool again = nrm2 < (T)(1.0 / 4096.0) * wn2;
-      T* p2 = p1;
       if (again) {
-        p2 = next_part();
-        multi_dot<T, BLOCK, KB>(basis, j + 1, w, s1, p2);
-        const T hh2 = subtract_proj<T, BLOCK, KB>(basis, j + 1, w, p2);
+        T wn;
+        const T h2 = multi_dot<Sh>(basis, j + 1, w, next_part(), s.wv, &wn);
+        const T hh2 = subtract_proj<T, Sh>(basis, j + 1, w, h2);
+        h += h2;
         nrm2 = nrm2 - hh2;   // the second pass removes only a small remainder
       }
       *work += bm.jvp() + bm.pre() + (again ? 2 : 1) * bm.orth_pass(j);
       const T hn = sqrt(nrm2 > (T)0 ? nrm2 : (T)0);
       // Hessenberg column j: h_i (+ second-pass h_i), rotated by the previous Givens rotations
       T* Hj = s.H + hcol(j);
-      T cur = part_sum<T, NW>(p1, 0) + (again ? part_sum<T, NW>(p2, 0) : (T)0);
+      T cur = lane_value(h, 0);
       for (int i = 0; i < j; ++i) {
-        const T nxt = part_sum<T, NW>(p1, i + 1) + (again ? part_sum<T, NW>(p2, i + 1) : (T)0);
+        const T nxt = lane_value(h, i + 1);
         const T c = s.cs[i], sn = s.sn[i];
-        const T a = c * cur + sn * nxt;
-        cur = -sn * cur + c * nxt;
+        const T a = mul_add(c, cur, sn, nxt);
+        if constexpr (sizeof(T) == 4) cur = -sn * cur + c * nxt;
+        else cur = fm(c, nxt, -(sn * cur));
         if (threadIdx.x == 0) Hj[i] = a;
       }
-      const T d = sqrt(cur * cur + hn * hn);
+      const T d = sqrt(mul_add(cur, cur, hn, hn));
       const T c = d == (T)0 ? (T)1 : cur / d;
       const T sn = d == (T)0 ? (T)0 : hn / d;
       const T gj = s.gres[j];
@@ -1061,7 +1425,7 @@ __device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, K
     if (threadIdx.x == 0) {
       for (int i = steps - 1; i >= 0; --i) {
         T a = s.gfin[i];
-        for (int l = i + 1; l < steps; ++l) a -= s.H[hcol(l) + i] * s.yv[l];
+        for (int l = i + 1; l < steps; ++l) a = fm(-s.H[hcol(l) + i], s.yv[l], a);
         const T d = s.H[hcol(i) + i];
         s.yv[i] = d != (T)0 ? a / d : (T)0;
       }
@@ -1072,31 +1436,37 @@ __device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, K
     {
       double acc[K];
       ws.ld_all(xpl, acc);
-      int i = 0;
-      for (; i + 1 < steps; i += 2) {  // two vectors' loads in flight per round
-        const double y0 = (double)s.yv[i], y1 = (double)s.yv[i + 1];
+      auto part = [&](int i, int i1, auto where) {
+        constexpr bool L = decltype(where)::value;
+        for (; i + 1 < i1; i += 2) {  // two vectors' loads in flight per round
+          const double y0 = (double)s.yv[i], y1 = (double)s.yv[i + 1];
 #pragma unroll
-        for (int g = 0; g < K / G; ++g) {
-          T e0[G], e1[G];
-          basis.ldg(i, g, e0);
-          basis.ldg(i + 1, g, e1);
+          for (int g = 0; g < K / G; ++g) {
+            T e0[G], e1[G];
+            basis.template ldg<L>(i, g, e0);
+            basis.template ldg<L>(i + 1, g, e1);
 #pragma unroll
-          for (int q = 0; q < G; ++q) {
-            acc[g * G + q] += y0 * (double)e0[q];
-            acc[g * G + q] += y1 * (double)e1[q];
+            for (int q = 0; q < G; ++q)
+              acc[g * G + q] = fm(y1, (double)e1[q], fm(y0, (double)e0[q], acc[g * G + q]));
           }
         }
-      }
-      if (i < steps) {
-        const double yi = (double)s.yv[i];
+        if (i < i1) {
+          const double yi = (double)s.yv[i];
 #pragma unroll
-        for (int g = 0; g < K / G; ++g) {
-          T e[G];
-          basis.ldg(i, g, e);
+          for (int g = 0; g < K / G; ++g) {
+            T e[G];
+            basis.template ldg<L>(i, g, e);
 #pragma unroll
-          for (int q = 0; q < G; ++q) acc[g * G + q] += yi * (double)e[q];
+            for (int q = 0; q < G; ++q) acc[g * G + q] = fm(yi, (double)e[q], acc[g * G + q]);
+          }
         }
+      };
+      int in_lds = 0;
+      if constexpr (Sh::S > 1) {
+        in_lds = steps < basis.nl ? steps : basis.nl;
+        part(0, in_lds, std::true_type{});
       }
+      part(in_lds, steps, std::false_type{});
       ws.st_all(xpl, acc);
     }
     done = !(res > rtol * beta0);
@@ -1105,12 +1475,12 @@ __device__ int gmres_solve(ApplyA&& apply_a, ApplyM&& apply_m, const Ws<BLOCK, K
   return total;
 }
 
-template <typename T, int BLOCK, int KB>
+template <typename T, class Sh>
 // Four waves per SIMD: with about 40 KB of LDS per scenario, four workgroups
 // (four scenarios) share a CU; registers are capped to match.
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void nr_kernel(
+__global__ __launch_bounds__(Sh::BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void nr_kernel(
     const TxDev<T>* __restrict__ netp, NRLaunch a) {
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int NW = Sh::NW, KB = Sh::KB;
   constexpr int K = 2 * KB;
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = a.slots ? a.slots[blockIdx.x] : (int)blockIdx.x;
@@ -1128,11 +1498,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     return;
   }
   const int R = a.restart;
-  const NrLayout L = nr_layout(KB * BLOCK, n - 1, npq, kmax, R, NW, (int)sizeof(T));
+  const NrLayout L = nr_layout((int)Sh::NBP, n - 1, npq, kmax, R, NW, Sh::S > 1, (int)sizeof(T));
   const Smem<T> s = carve<T>(smem, L);
 
-  const Ws<BLOCK, KB> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
-  const Basis<T, BLOCK, KB> basis{make_buf(reinterpret_cast<T*>(a.ws_basis) + (int64_t)b * a.ws_b_stride)};
+  const Ws<Sh> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
+  const Basis<T, Sh> basis{make_buf(reinterpret_cast<T*>(a.ws_basis) + (int64_t)b * a.ws_b_stride),
+                           reinterpret_cast<T*>(smem + L.total), a.lds_vecs};
   const Buf P = make_buf(a.p_inj + (int64_t)b * a.ld);
   const Buf Q = make_buf(a.q_inj + (int64_t)b * a.ld);
   const Buf VS = make_buf(a.vm_set + (int64_t)b * a.ld);
@@ -1146,7 +1517,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     double p[KB], q[KB], vs[KB];
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       p[k] = 0.0;
       q[k] = 0.0;
       vs[k] = 1.0;
@@ -1169,8 +1540,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   using T2 = typename Vec2<T>::type;
   const double2* yv64 = a.yv64 ? a.yv64 + (int64_t)b * a.yv_stride : nullptr;
   const T2* yvT = a.yvT ? reinterpret_cast<const T2*>(a.yvT) + (int64_t)b * a.yv_stride : nullptr;
-  auto apply_j = [&](T (&w)[K]) { jvp<T, BLOCK, KB>(netp, ws, w, s.xs, yvT); };
-  auto apply_m = [&](T (&w)[K]) { precond<T, BLOCK, KB>(netp, ws, w, s); };
+  Held<T, Sh> held;
+  auto apply_j = [&](T (&w)[K]) { jvp<T, Sh>(netp, ws, held, w, s.xs, yvT); };
+  auto apply_m = [&](T (&w)[K]) { precond<T, Sh>(netp, ws, held, w, s); };
 
   int newton = 0, gtotal = 0;
   bool conv = false;
@@ -1195,7 +1567,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     const ByteModel bm{(double)sizeof(T) * net.m, 8.0 * net.m, 8.0 * n, 4.0 * sizeof(T) * n,
                        2.0 * sizeof(T) * a.yv_nnz, 16.0 * a.yv_nnz};
     if (!resume) {
-      fnorm = mismatch<T, BLOCK, KB>(netp, ws, s.vs, s.redd + par * NW, yv64);
+      fnorm = mismatch<T, Sh>(netp, ws, s.vs, s.redd + par * NW, yv64);
       work += bm.mismatch();
       par ^= 1;
       if (!(fnorm <= a.diverge)) break;
@@ -1250,8 +1622,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       for (int k = 0; k < K; ++k) f[k] = -f[k];
       ws.st_all(FP, f);
     }
+    held.load(ws);
     bool lin_ok;
-    gtotal += gmres_solve<T, BLOCK, KB>(apply_j, apply_m, ws, FP, DXP, basis, R, a.max_restarts, (T)rt, s,
+    gtotal += gmres_solve<T, Sh>(apply_j, apply_m, ws, FP, DXP, basis, R, a.max_restarts, (T)rt, s,
                                         &lin_ok, bm, &work);
     // Newton update (eq. (3)), FP64, own buses
     {
@@ -1276,9 +1649,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   const Buf vout = make_buf(a.v_out + 2 * (int64_t)b * a.ld);
   {
     const TxDev<T> net = load_desc(netp);
-#pragma unroll
+#pragma unroll 2
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if ((int)i < n) {
         const unsigned e = (unsigned)cld(net.int2ext, i) * 16u;
         // V of the last iterate, formed exactly as the last mismatch formed it
@@ -1332,10 +1705,10 @@ __host__ __device__ inline size_t direct_stage_bytes(const DirectDev& d) {
 // VG: the factor values live in device memory (a.ws_dval, per scenario)
 // instead of LDS, for factors larger than the LDS can hold; the level
 // barriers order their reads and writes within the workgroup as before.
-template <int BLOCK, int KB, bool STAGE, bool VG>
-__global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* __restrict__ netp, DirectDev d,
+template <class Sh, bool STAGE, bool VG>
+__global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double>* __restrict__ netp, DirectDev d,
                                                           NRLaunch a) {
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int NW = Sh::NW, KB = Sh::KB, BLOCK = Sh::BLOCK;
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x, tid = threadIdx.x;
   int n, npq, nth;
@@ -1383,7 +1756,7 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
   auto FPH = [&](int q) { if constexpr (STAGE) return lfp[q]; else return cld(d.fph, (unsigned)q); };
   auto BPH = [&](int q) { if constexpr (STAGE) return lbp[q]; else return cld(d.bph, (unsigned)q); };
 
-  const Ws<BLOCK, KB> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
+  const Ws<Sh> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
   const Buf P = make_buf(a.p_inj + (int64_t)b * a.ld);
   const Buf Q = make_buf(a.q_inj + (int64_t)b * a.ld);
   const Buf VS = make_buf(a.vm_set + (int64_t)b * a.ld);
@@ -1391,7 +1764,7 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
     const TxDev<double> net = load_desc(netp);
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       double p = 0.0, q = 0.0, vsp = 1.0;
       if ((int)i < n) {
         const unsigned e = (unsigned)cld(net.int2ext, i) * 8u;
@@ -1412,7 +1785,7 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
   double fnorm = 0.0, work = 0.0;
   int par = 0;
   for (;;) {
-    fnorm = mismatch<double, BLOCK, KB>(netp, ws, vs, red + par * NW, yv);
+    fnorm = mismatch<double, Sh>(netp, ws, vs, red + par * NW, yv);
     work += 32.0 * n + 16.0 * m + 16.0 * a.yv_nnz;
     par ^= 1;
     if (!(fnorm <= a.diverge)) break;
@@ -1424,7 +1797,7 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
     // own buses' I and -F into LDS (F in factor order); factor values cleared
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       is[i] = make_double2(ws.ld(IRE, k), ws.ld(IIM, k));
       if ((int)i < nth) rhs[cld(d.fpos, i)] = -ws.ld(FP, k);
       if ((int)i < npq) rhs[cld(d.fpos, (unsigned)NBP + i)] = -ws.ld(FP, KB + k);
@@ -1496,7 +1869,7 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
     // Newton update (eq. (3)), own buses
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if ((int)i < nth) ws.st(TH, k, ws.ld(TH, k) + xs[cld(d.fpos, i)]);
       if ((int)i < npq) ws.st(VM, k, ws.ld(VM, k) + xs[cld(d.fpos, (unsigned)NBP + i)]);
     }
@@ -1509,7 +1882,7 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
     const TxDev<double> net = load_desc(netp);
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if ((int)i < n) {
         const unsigned e = (unsigned)cld(net.int2ext, i) * 16u;
         double sn, cs;
@@ -1533,46 +1906,50 @@ __global__ __launch_bounds__(BLOCK) void nr_direct_kernel(const TxDev<double>* _
 // Adjoint.  For w = [w_P on Theta ; w_Q on Q] and c = w_P + j w_Q (zero where
 // undefined), w^T dF = Re sum_k g_k dV_k with g = conj(c I) + Ybus^T (c conj V),
 // so (J^T w) = [-Im(g V) on Theta ; Re(g V) / |V| on Q].  Ends with a barrier.
-template <int BLOCK, int KB>
-__device__ void vjp(const TxDev<double>* netp, const Ws<BLOCK, KB>& ws, double (&w)[2 * KB], double* lds) {
-  constexpr int NW = BLOCK / WAVE;
+template <class Sh>
+__device__ void vjp(const TxDev<double>* netp, const Ws<Sh>& ws, const Held<double, Sh>& held, double (&w)[2 * Sh::KB],
+                    double* lds) {
+  constexpr int KB = Sh::KB;
   const TxDev<double> net = load_desc(netp);
   const unsigned nth = net.nth, npq = net.npq;
   double2* u = reinterpret_cast<double2*>(lds);
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    const unsigned i = row<BLOCK>(k);
+    const unsigned i = Sh::row(k);
     const double cr = w[k], ci = w[KB + k];
-    const double vr = ws.ld(VRE, k), vi = ws.ld(VIM, k);
+    double vr, vi;
+    if constexpr (Held<double, Sh>::on) vr = held.vr[k], vi = held.vi[k];
+    else vr = ws.ld(VRE, k), vi = ws.ld(VIM, k);
     double2 t;  // c conj(V)
-    t.x = cr * vr + ci * vi;
-    t.y = ci * vr - cr * vi;
+    t.x = fm(cr, vr, ci * vi);
+    t.y = fm(ci, vr, -(cr * vi));
     u[i] = t;
   }
   __syncthreads();
-  const int wv = wave_id();
-  double nIr = ws.ld(IRE, 0), nIi = ws.ld(IIM, 0), nvr = ws.ld(VRE, 0), nvi = ws.ld(VIM, 0), niv = ws.ld(IVM, 0);
+  double nIr, nIi, nvr, nvi, niv;
+  auto fetch = [&](int k) {
+    if constexpr (Held<double, Sh>::on) {
+      nIr = held.ir[k], nIi = held.ii[k], nvr = held.vr[k], nvi = held.vi[k], niv = held.iv[k];
+    } else {
+      nIr = ws.ld(IRE, k), nIi = ws.ld(IIM, k), nvr = ws.ld(VRE, k), nvi = ws.ld(VIM, k), niv = ws.ld(IVM, k);
+    }
+  };
+  fetch(0);
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
     const double Ir = nIr, Ii = nIi, vr = nvr, vi = nvi, iv = niv;
-    if (k + 1 < KB) {
-      nIr = ws.ld(IRE, k + 1);
-      nIi = ws.ld(IIM, k + 1);
-      nvr = ws.ld(VRE, k + 1);
-      nvi = ws.ld(VIM, k + 1);
-      niv = ws.ld(IVM, k + 1);
-    }
+    if (k + 1 < KB) fetch(k + 1);
     double gr = 0.0, gi = 0.0;  // (Y^T (c conj V))_i
-    psell_row(net.yt, k * NW + wv, [&](double2 y, int c) {
+    psell_row(net.yt, Sh::slice(k), [&](double2 y, int c) {
       const double2 t = u[c];
-      gr += y.x * t.x - y.y * t.y;
-      gi += y.x * t.y + y.y * t.x;
+      gr = fm(-y.y, t.y, fm(y.x, t.x, gr));
+      gi = fm(y.y, t.x, fm(y.x, t.y, gi));
     });
-    const unsigned i = row<BLOCK>(k);
+    const unsigned i = Sh::row(k);
     const double cr = w[k], ci = w[KB + k];
-    const double hr = gr + cr * Ir - ci * Ii;  // + conj(c I)
-    const double hi = gi - (cr * Ii + ci * Ir);
-    const double pr = hr * vr - hi * vi, pi = hr * vi + hi * vr;  // g V
+    const double hr = fm(-ci, Ii, fm(cr, Ir, gr));  // + conj(c I)
+    const double hi = fm(-ci, Ir, fm(-cr, Ii, gi));
+    const double pr = fm(hr, vr, -(hi * vi)), pi = fm(hr, vi, hi * vr);  // g V
     w[k] = i < nth ? -pi : 0.0;
     w[KB + k] = i < npq ? pr * iv : 0.0;
     settle(w[k]);
@@ -1584,57 +1961,62 @@ __device__ void vjp(const TxDev<double>* netp, const Ws<BLOCK, KB>& ws, double (
 // z = M^-T w: z_Q = diag(|V_Q|)^-1 (B'' + eps I)^-1 w_Q,
 //             z_Theta = diag(|V_Theta|)^-1 (B' + eps I)^-1 (w_Theta - G^T z_Q).
 // LDS use as in precond, with the roles of the two solves swapped.
-template <int BLOCK, int KB>
-__device__ void precond_t(const TxDev<double>* netp, const Ws<BLOCK, KB>& ws, double (&w)[2 * KB],
+template <class Sh>
+__device__ void precond_t(const TxDev<double>* netp, const Ws<Sh>& ws, const Held<double, Sh>& held,
+                          double (&w)[2 * Sh::KB],
                           const Smem<double>& s) {
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int KB = Sh::KB;
   const TxDev<double> net = load_desc(netp);
   const unsigned nth = net.nth, npq = net.npq;
+  auto ivm = [&](int k) {
+    if constexpr (Held<double, Sh>::on) return held.iv[k];
+    else return ws.ld(IVM, k);
+  };
   double* X = s.xs;
   double* Y = s.xs + nth;
   if (npq > 0) {
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if (i < npq) Y[i] = w[KB + k];
     }
     __syncthreads();
-    efac_apply<double, BLOCK, KB, KB>(net.bpp, Y, X, s.tmp, w);
+    efac_apply<double, Sh, KB>(net.bpp, Y, X, s.tmp, w);
 #pragma unroll
-    for (int k = 0; k < KB; ++k) w[KB + k] *= ws.ld(IVM, k);
+    for (int k = 0; k < KB; ++k) w[KB + k] *= ivm(k);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if (i < npq) Y[i] = w[KB + k];
     }
     __syncthreads();
     const TxDev<double> nt = load_desc(netp);
     double gz[KB];
-    psell_slots_dot<KB, NW>(nt.gt, Y, gz);
+    psell_slots_dot<Sh>(nt.gt, Y, gz);
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if (i < nth) X[i] = w[k] - gz[k];
     }
   } else {
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if (i < nth) X[i] = w[k];
     }
   }
   __syncthreads();
   const TxDev<double> nb = load_desc(netp);
-  efac_apply<double, BLOCK, KB, 0>(nb.bp, X, Y, s.tmp, w);
+  efac_apply<double, Sh, 0>(nb.bp, X, Y, s.tmp, w);
 #pragma unroll
-  for (int k = 0; k < KB; ++k) w[k] *= ws.ld(IVM, k);
+  for (int k = 0; k < KB; ++k) w[k] *= ivm(k);
 }
 
-template <int BLOCK, int KB>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void adjoint_kernel(
+template <class Sh>
+__global__ __launch_bounds__(Sh::BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void adjoint_kernel(
     const TxDev<double>* __restrict__ netp, AdjLaunch a) {
-  constexpr int NW = BLOCK / WAVE;
+  constexpr int NW = Sh::NW, KB = Sh::KB;
   constexpr int K = 2 * KB;
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
@@ -1647,10 +2029,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     kmax = net.bp.k > net.bpp.k ? net.bp.k : net.bpp.k;
   }
   const int R = a.restart;
-  const NrLayout L = nr_layout(KB * BLOCK, nth, npq, kmax, R, NW, 8);
+  const NrLayout L = nr_layout((int)Sh::NBP, nth, npq, kmax, R, NW, Sh::S > 1, 8);
   const Smem<double> s = carve<double>(smem, L);
-  const Ws<BLOCK, KB> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
-  const Basis<double, BLOCK, KB> basis{make_buf(a.ws_basis + (int64_t)b * a.ws_b_stride)};
+  const Ws<Sh> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
+  const Basis<double, Sh> basis{make_buf(a.ws_basis + (int64_t)b * a.ws_b_stride),
+                                reinterpret_cast<double*>(smem + L.total), a.lds_vecs};
   const Buf V = make_buf(a.v + 2 * (int64_t)b * a.ld);
   const Buf tg = make_buf(a.dl_dv + 2 * (int64_t)b * a.ld);
 
@@ -1659,7 +2042,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     const TxDev<double> net = load_desc(netp);
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       double2 v;
       v.x = 1.0;
       v.y = 0.0;
@@ -1668,7 +2051,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
         v.x = bld<double>(V, e, 0);
         v.y = bld<double>(V, e, 8);
       }
-      const double vm = sqrt(v.x * v.x + v.y * v.y);
+      const double vm = sqrt(fm(v.x, v.x, v.y * v.y));
       ws.st(VRE, k, v.x);
       ws.st(VIM, k, v.y);
       ws.st(VM, k, vm);
@@ -1684,17 +2067,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     double Ir[KB], Ii[KB];
 #pragma unroll
     for (int k = 0; k < KB; ++k) Ir[k] = Ii[k] = 0.0;
-    psell_slots<KB, NW>(
+    psell_slots<Sh>(
         net.y64,
         [&](int k, double2 y, int c) {
           const double2 v = s.vs[c];
-          Ir[k] += y.x * v.x - y.y * v.y;
-          Ii[k] += y.x * v.y + y.y * v.x;
+          Ir[k] = fm(-y.y, v.y, fm(y.x, v.x, Ir[k]));
+          Ii[k] = fm(y.y, v.x, fm(y.x, v.y, Ii[k]));
         },
         [&](int) {});
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       ws.st(IRE, k, Ir[k]);
       ws.st(IIM, k, Ii[k]);
       double ft = 0.0, fv = 0.0;
@@ -1702,8 +2085,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
         const unsigned e = (unsigned)cld(net.int2ext, i) * 16u;
         const double tr = bld<double>(tg, e, 0), ti = bld<double>(tg, e, 8);
         const double2 v = s.vs[i];
-        if ((int)i < nth) ft = ti * v.x - tr * v.y;
-        if ((int)i < npq) fv = (tr * v.x + ti * v.y) * ws.ld(IVM, k);
+        if ((int)i < nth) ft = fm(ti, v.x, -(tr * v.y));
+        if ((int)i < npq) fv = fm(tr, v.x, ti * v.y) * ws.ld(IVM, k);
       }
       ws.st(FP, k, ft);
       ws.st(FP, KB + k, fv);
@@ -1711,15 +2094,17 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   }
   __syncthreads();
 
-  auto apply_jt = [&](double (&w)[K]) { vjp<BLOCK, KB>(netp, ws, w, s.xs); };
-  auto apply_mt = [&](double (&w)[K]) { precond_t<BLOCK, KB>(netp, ws, w, s); };
+  Held<double, Sh> held;
+  held.load(ws);
+  auto apply_jt = [&](double (&w)[K]) { vjp<Sh>(netp, ws, held, w, s.xs); };
+  auto apply_mt = [&](double (&w)[K]) { precond_t<Sh>(netp, ws, held, w, s); };
   double work = 0.0;
   bool ok;
   int its;
   {
     const TxDev<double> net = load_desc(netp);
     const ByteModel bm{8.0 * net.m, 8.0 * net.m, 8.0 * n, 32.0 * n};
-    its = gmres_solve<double, BLOCK, KB>(apply_jt, apply_mt, ws, FP, DXP, basis, R, a.max_restarts, a.rtol, s,
+    its = gmres_solve<double, Sh>(apply_jt, apply_mt, ws, FP, DXP, basis, R, a.max_restarts, a.rtol, s,
                                          &ok, bm, &work);
   }
   const Buf gp = make_buf(a.grad_p + (int64_t)b * a.ld);
@@ -1729,7 +2114,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     const TxDev<double> net = load_desc(netp);
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const unsigned i = row<BLOCK>(k);
+      const unsigned i = Sh::row(k);
       if ((int)i < n) {
         const unsigned e = (unsigned)cld(net.int2ext, i) * 8u;
         bst(gp, (int)i < nth ? ws.ld(DXP, k) : 0.0, e, 0);
@@ -1743,35 +2128,77 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   }
 }
 
-// Shapes: BLOCK threads, KB bus slots per thread, n <= BLOCK * KB.
+// Shapes: VB columns of KBT bus slots, n <= VB KBT, the split at most `split`.
+template <int VB, int KBT, typename Launch>
+void dispatch_split(int split, Launch&& go) {
+  constexpr int most = nr_split_max(VB, KBT);
+  if constexpr (most >= 4) {
+    if (split >= 4) return go.template operator()<Shape<VB, KBT, 4>>();
+  }
+  if constexpr (most >= 2) {
+    if (split >= 2) return go.template operator()<Shape<VB, KBT, 2>>();
+  }
+  go.template operator()<Shape<VB, KBT, 1>>();
+}
+
 template <typename Launch>
-void dispatch_shape(int n, Launch&& go) {
-  if (n <= 64) go.template operator()<64, 1>();
-  else if (n <= 256) go.template operator()<64, 4>();
-  else if (n <= 1024) go.template operator()<256, 4>();
-  else if (n <= 2048) go.template operator()<256, 8>();
-  else if (n <= 4096) go.template operator()<512, 8>();
-  else if (n <= 8192) go.template operator()<1024, 8>();
+void dispatch_shape(int n, int split, Launch&& go) {
+  if (n <= 64) dispatch_split<64, 1>(split, go);
+  else if (n <= 256) dispatch_split<64, 4>(split, go);
+  else if (n <= 1024) dispatch_split<256, 4>(split, go);
+  else if (n <= 2048) dispatch_split<256, 8>(split, go);
+  else if (n <= 4096) dispatch_split<512, 8>(split, go);
+  else if (n <= 8192) dispatch_split<1024, 8>(split, go);
   else fail(PF_INVALID_ARG, "networks above 8192 buses are not supported");
 }
 
 struct ShapeOf {
   int* block;
   int* kb;
-  template <int BLOCK, int KB>
+  template <class Sh>
   void operator()() const {
-    *block = BLOCK;
-    *kb = KB;
+    *block = Sh::VB;
+    *kb = Sh::KBT;
   }
 };
 
-size_t lds_bytes(const TxNetwork& net, int R, int ts) {
+// The split of a launch: the largest whose waves all find room at once, at four
+// per SIMD.  A scenario's phases are chains of dependent loads, and with few
+// scenarios per CU only more waves of the same one can overlap them: unsplit
+// against split, 2000 buses with per-scenario Ybus values, batch 200 1.67 ->
+// 0.99 ms; a training step of 256 2.12 -> 1.22 ms; 118 buses, batch 1000, mixed
+// 204 -> 135 us.  Once the unsplit waves fill the CUs (2000 buses, batch 1024)
+// the split ones would only queue.
+int nr_split(const TxNetwork& net, int batch) {
+  const int64_t room = 16 * (int64_t)net.ctx->cu_count, waves = (int64_t)batch * (net.block / WAVE);
+  return waves * 4 <= room ? 4 : waves * 2 <= room ? 2 : 1;
+}
+
+size_t lds_bytes(const TxNetwork& net, int split, int R, int ts) {
   const int kmax = std::max(net.bp.host.k, net.bpp.host.k);
-  const NrLayout L = nr_layout(net.nbp, net.nth, net.npq, kmax, R, net.block / WAVE, ts);
+  const NrLayout L = nr_layout(net.nbp, net.nth, net.npq, kmax, R, split * net.block / WAVE, split > 1, ts);
   if (L.total > 160 * 1024)
     fail(PF_INVALID_ARG, "network too large for the per-scenario LDS layout (" + std::to_string(L.total) +
                              " bytes)");
   return (size_t)L.total;
+}
+
+// Basis vectors that fit in LDS beside a split workgroup's `lds` bytes when the
+// batch's workgroups share out the CUs' 160 KB evenly; an even number, since
+// the projection takes vectors off in pairs.
+template <class Sh, typename T>
+int lds_vectors(const TxNetwork& net, int batch, int R, size_t lds) {
+  if (Sh::S == 1) return 0;
+  const size_t per_cu = (batch + net.ctx->cu_count - 1) / net.ctx->cu_count;
+  const size_t room = (160 * 1024 - 1024) / std::max<size_t>(per_cu, 1), vec = 2 * Sh::NBP * sizeof(T);
+  return room <= lds ? 0 : std::min<int>(R, (int)((room - lds) / vec)) & ~1;
+}
+
+template <typename Kernel>
+void allow_lds(Kernel kernel, size_t lds) {
+  if (lds > 64 * 1024)
+    PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds));
 }
 
 template <typename T>
@@ -1779,14 +2206,15 @@ struct NrGo {
   const TxNetwork& net;
   const NRLaunch& a;
   hipStream_t s;
-  template <int BLOCK, int KB>
+  template <class Sh>
   void operator()() const {
-    const size_t lds = lds_bytes(net, a.restart, (int)sizeof(T));
-    auto kernel = nr_kernel<T, BLOCK, KB>;
-    if (lds > 64 * 1024)
-      PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(BLOCK), lds, s, net.desc<T>(), a);
+    NRLaunch b = a;
+    const size_t base = lds_bytes(net, Sh::S, a.restart, (int)sizeof(T));
+    b.lds_vecs = lds_vectors<Sh, T>(net, a.batch, a.restart, base);
+    const size_t lds = base + b.lds_vecs * 2 * Sh::NBP * sizeof(T);
+    auto kernel = nr_kernel<T, Sh>;
+    allow_lds(kernel, lds);
+    hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<T>(), b);
     PFX_HIP(hipGetLastError());
   }
 };
@@ -1795,36 +2223,36 @@ struct NrDirectGo {
   const TxNetwork& net;
   const NRLaunch& a;
   hipStream_t s;
-  template <int BLOCK, int KB>
+  template <class Sh>
   void operator()() const {
     const DirectDev& d = net.direct;
-    const size_t lds0 = (size_t)2 * KB * BLOCK * 16 + 2 * (BLOCK / WAVE) * 8 + ((size_t)d.n_val + 2 * d.m) * 8;
+    const size_t lds0 = (size_t)2 * Sh::NBP * 16 + 2 * Sh::NW * 8 + ((size_t)d.n_val + 2 * d.m) * 8;
     if (lds0 > 160 * 1024) {
       // factor values in device memory; V, I, the right-hand side and x stay in LDS
-      const size_t ldsg = (size_t)2 * KB * BLOCK * 16 + 2 * (BLOCK / WAVE) * 8 + (size_t)2 * d.m * 8;
+      const size_t ldsg = (size_t)2 * Sh::NBP * 16 + 2 * Sh::NW * 8 + (size_t)2 * d.m * 8;
       if (ldsg > 160 * 1024)
         fail(PF_INVALID_ARG, "network too large for the direct Newton step (" + std::to_string(ldsg) +
                                  " bytes of LDS)");
       if (!a.ws_dval) fail(PF_INVALID_ARG, "direct Newton step without its factor workspace");
-      auto kernel = nr_direct_kernel<BLOCK, KB, false, true>;
+      auto kernel = nr_direct_kernel<Sh, false, true>;
       if (ldsg > 64 * 1024)
         PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsg));
-      hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(BLOCK), ldsg, s, net.desc<double>(), d, a);
+      hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), ldsg, s, net.desc<double>(), d, a);
       PFX_HIP(hipGetLastError());
       return;
     }
     // stage the schedule tables when the total stays within 64 KB, or, when
     // the batch has no more scenarios than the chip has CUs (one workgroup
     // per CU, occupancy moot), within the CU's 160 KB
-    const size_t lds1 = direct_stage_offset(KB * BLOCK, BLOCK / WAVE, d) + direct_stage_bytes(d);
+    const size_t lds1 = direct_stage_offset((int)Sh::NBP, Sh::NW, d) + direct_stage_bytes(d);
     const bool stage = lds1 <= (a.batch <= net.ctx->cu_count ? 160 : 64) * 1024;
     const size_t lds = stage ? lds1 : lds0;
-    auto kernel = stage ? nr_direct_kernel<BLOCK, KB, true, false> : nr_direct_kernel<BLOCK, KB, false, false>;
+    auto kernel = stage ? nr_direct_kernel<Sh, true, false> : nr_direct_kernel<Sh, false, false>;
     if (lds > 64 * 1024)
       PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(BLOCK), lds, s, net.desc<double>(), d, a);
+    hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<double>(), d, a);
     PFX_HIP(hipGetLastError());
   }
 };
@@ -1833,21 +2261,22 @@ struct AdjGo {
   const TxNetwork& net;
   const AdjLaunch& a;
   hipStream_t s;
-  template <int BLOCK, int KB>
+  template <class Sh>
   void operator()() const {
-    const size_t lds = lds_bytes(net, a.restart, 8);
-    auto kernel = adjoint_kernel<BLOCK, KB>;
-    if (lds > 64 * 1024)
-      PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(BLOCK), lds, s, net.desc<double>(), a);
+    AdjLaunch b = a;
+    const size_t base = lds_bytes(net, Sh::S, a.restart, 8);
+    b.lds_vecs = lds_vectors<Sh, double>(net, a.batch, a.restart, base);
+    const size_t lds = base + b.lds_vecs * 2 * Sh::NBP * sizeof(double);
+    auto kernel = adjoint_kernel<Sh>;
+    allow_lds(kernel, lds);
+    hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<double>(), b);
     PFX_HIP(hipGetLastError());
   }
 };
 
 }  // namespace
 
-void nr_shape(int n, int* block, int* kb) { dispatch_shape(n, ShapeOf{block, kb}); }
+void nr_shape(int n, int* block, int* kb) { dispatch_shape(n, 1, ShapeOf{block, kb}); }
 
 int64_t nr_padded_rows(const TxNetwork& net) { return 2 * (int64_t)net.nbp; }
 int64_t nr_ws_doubles(const TxNetwork& net) { return 13 * (int64_t)net.nbp; }
@@ -1868,7 +2297,7 @@ __global__ __launch_bounds__(256) void y_gather_kernel(const int* sptr, const in
       im += src[2 * e + 1];
     }
     out64[t] = make_double2(re, im);
-    if (out32) out32[t] = make_float2((float)re, (float)im);
+    if (out32) out32[b * E + psell_at<float2>(psell_entry<double2>(q))] = make_float2((float)re, (float)im);
   }
 }
 
@@ -1884,8 +2313,8 @@ void launch_y_gather(const TxNetwork& net, int batch, int64_t ldy, const double*
 
 void launch_nr(const TxNetwork& net, bool mixed, const NRLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
-  if (mixed) dispatch_shape(net.n, NrGo<float>{net, a, s});
-  else dispatch_shape(net.n, NrGo<double>{net, a, s});
+  if (mixed) dispatch_shape(net.n, nr_split(net, a.batch), NrGo<float>{net, a, s});
+  else dispatch_shape(net.n, nr_split(net, a.batch), NrGo<double>{net, a, s});
 }
 
 bool direct_lds_fits(const TxNetwork& net) {
@@ -1897,12 +2326,12 @@ bool direct_lds_fits(const TxNetwork& net) {
 void launch_nr_direct(const TxNetwork& net, const NRLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
   if (!net.direct_ready) fail(PF_INVALID_ARG, "direct Newton step used before its analysis was built");
-  dispatch_shape(net.n, NrDirectGo{net, a, s});
+  dispatch_shape(net.n, 1, NrDirectGo{net, a, s});
 }
 
 void launch_adjoint(const TxNetwork& net, const AdjLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
-  dispatch_shape(net.n, AdjGo{net, a, s});
+  dispatch_shape(net.n, nr_split(net, a.batch), AdjGo{net, a, s});
 }
 
 // ---------------------------------------------------------------------------

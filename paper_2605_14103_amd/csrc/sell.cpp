@@ -104,16 +104,23 @@ std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const s
     std::vector<double> v64(2 * val.size());
     std::vector<float> v32(2 * val.size());
     for (size_t i = 0; i < val.size(); ++i) {
-      v64[2 * i] = val[i];
-      v64[2 * i + 1] = vim[i];
-      v32[2 * i] = (float)val[i];
-      v32[2 * i + 1] = (float)vim[i];
+      const size_t p = psell_at<double2>(i), q = psell_at<float2>(i);
+      v64[2 * p] = val[i];
+      v64[2 * p + 1] = vim[i];
+      v32[2 * q] = (float)val[i];
+      v32[2 * q + 1] = (float)vim[i];
     }
     b.val64 = upload(ctx, v64);
     b.val32 = upload(ctx, v32);
   } else {
-    b.val64 = upload(ctx, val);
-    b.val32 = upload(ctx, std::vector<float>(val.begin(), val.end()));
+    std::vector<double> v64(val.size());
+    std::vector<float> v32(val.size());
+    for (size_t i = 0; i < val.size(); ++i) {
+      v64[psell_at<double>(i)] = val[i];
+      v32[psell_at<float>(i)] = (float)val[i];
+    }
+    b.val64 = upload(ctx, v64);
+    b.val32 = upload(ctx, v32);
   }
   return {off, width};
 }

@@ -25,11 +25,32 @@ struct Sell {
 
 // Packed sliced layout: the slices of Sell, but each lane's entries are
 // grouped in fours.  Group g of the row on lane l of slice s is group index
-// off[s] + 64 g + l; it holds four values (val[4 index ..]) and four 16-bit
-// columns (col[4 index ..]), so a group is one 8-byte column load and
-// sizeof(V) / 4 16-byte value loads.  Offsets and widths count groups;
-// padding entries have column 0 and value 0.  Entry p of that row is entry
-// 4 (off[s] + 64 (p / 4) + l) + p % 4 of the value array.
+// off[s] + 64 g + l; it holds four 16-bit columns at col[4 index ..] and four
+// values.  The values of the 64 groups of one (slice, g) lie in sizeof(V) / 4
+// planes of 16 bytes per lane, so a group is one 8-byte column load and
+// sizeof(V) / 4 16-byte value loads, and each load of a wave covers
+// consecutive addresses.  (With a lane's values side by side instead, four
+// lanes of a complex FP64 load touch two lines, and the address unit takes
+// twice as long: the Jacobian-vector product of the 2000-bus grid took 29 k
+// cycles against 24 k with four scenarios per CU.)  Offsets and widths count
+// groups; padding entries have column 0 and value 0.  Entry
+// p of that row is entry number 4 (off[s] + 64 (p / 4) + l) + p % 4, with its value
+// at psell_at of that number.
+template <typename V>
+__host__ __device__ inline int64_t psell_at(int64_t entry) {
+  constexpr int per = 16 / (int)sizeof(V);   // values in 16 bytes
+  const int64_t g = entry / 4, block = g / 64, lane = g % 64, u = entry % 4;
+  return block * 256 + u / per * (64 * per) + lane * per + u % per;
+}
+
+// the entry number of a value index (the inverse of psell_at)
+template <typename V>
+__host__ __device__ inline int64_t psell_entry(int64_t at) {
+  constexpr int per = 16 / (int)sizeof(V);
+  const int64_t block = at / 256, r = at % 256, plane = r / (64 * per), lane = r % (64 * per) / per;
+  return 4 * (64 * block + lane) + plane * per + r % per;
+}
+
 template <typename V>
 struct PSell {
   const int* off;

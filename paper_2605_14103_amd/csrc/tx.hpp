@@ -24,10 +24,11 @@ namespace pfx {
 
 // Device view of one explicit factor (factor.hpp, ExplicitFactor) laid out for
 // one workgroup of `block` threads.
-//   E1: rows sorted by length into slices; slice lists per wave (at most kb
-//       slices each, resolved to entry offset and width), row ids per lane
-//       (factor position, -1 for none); input
-//       columns are positions of the matrix order (the permutation is folded in).
+//   E1: rows sorted by length into slices, in FP64 the long ones over four lanes
+//       each (every fourth group of entries to a lane); slice lists per wave
+//       (resolved to group offset and width), row ids per lane (factor
+//       position, -1 for none); input columns are positions of the matrix
+//       order (the permutation is folded in).
 //   E3: one row per matrix row i (bus order), slices = consecutive 64 rows;
 //       columns are factor positions.
 template <typename T>
@@ -35,15 +36,21 @@ struct EfDev {
   int N, c, k;
   PSell<T> e1;
   const int* e1_row;     // [n_slices * 64]
-  const int* e1_wave;    // [n_waves * e1_nq][4]: group offset, width in groups, first row id index, 0
-  int e1_nq;             // entries per wave in e1_wave
+  // For each split s = 1, 2, 4 of the workgroup (index s / 2): per wave e1_nq entries of
+  // (group offset, width in groups, first row id index, rows split over four lanes)
+  const int* e1_wave[3];
+  int e1_nq[3];
   PSell<T> e3;
-  // The same E3 rows sorted by length into slices dealt to (slot, wave)
-  // positions k NW + w with balanced rounds; e3s_row[slice * 64 + lane] is
-  // the row's matrix row (-1 for padding).  Used where the result goes to LDS.
+  // The same E3 rows sorted by length into slices; e3s_row[slice * 64 + lane]
+  // is the row's matrix row (-1 for padding).  For each split they are dealt to
+  // (slot, wave) positions k NW + w with balanced rounds: e3s_pos holds (group
+  // offset, width, first row id index, 0) per position.  Used where the result
+  // goes to LDS.
   PSell<T> e3s;
   const int* e3s_row;
-  const T* sinv;         // S^-1 (k x k) in packs [l / P][i][P], P = 16 / sizeof(T)
+  const int* e3s_pos[3];
+  const T* sinv;         // S^-1 (k x k) in packs [l / P][i][P], P = 16 / sizeof(T),
+                         // zero-padded to four parts of as many packs
   // With no dense core the inverse itself may be sparse enough to apply in one
   // pass: then `direct` is 1 and `inv` holds A^-1 by rows in bus order, with
   // columns in matrix order (E1, E2 and E3 are not used).
@@ -91,9 +98,14 @@ struct EfBuffers {
   ExplicitFactor host;
   bool direct = false;
   PSellBuffers inv;
-  PSellBuffers e1, e3, e3s;
-  DeviceBuffer e1_row, e1_wave, e3s_row, sinv64, sinv32;
-  int e1_nq = 0;
+  struct E1 {
+    PSellBuffers val;
+    DeviceBuffer row, wave[3];
+    int nq[3] = {0, 0, 0};
+  };
+  E1 e1[2];   // for the FP64 and the FP32 kernels
+  PSellBuffers e3, e3s;
+  DeviceBuffer e3s_row, e3s_pos[3], sinv64, sinv32;
   template <typename T>
   EfDev<T> view() const;
 };
@@ -191,6 +203,7 @@ struct NRLaunch {
   NrSlotState* state;
   int step_iters;
   uint8_t* step_done;
+  int lds_vecs;   // basis vectors kept in LDS (set by the launcher)
   // Direct Newton step whose factor does not fit LDS: each scenario's factor
   // values at ws_dval + b * ws_dval_stride (device memory).
   double* ws_dval;
@@ -239,6 +252,7 @@ struct AdjLaunch {
   int64_t ws_d_stride;
   double* ws_basis;
   int64_t ws_b_stride;
+  int lds_vecs;   // basis vectors kept in LDS (set by the launcher)
 };
 int64_t adj_ws_doubles(const TxNetwork& net);
 void launch_adjoint(const TxNetwork& net, const AdjLaunch& a, hipStream_t s);

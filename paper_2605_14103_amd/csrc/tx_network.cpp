@@ -25,47 +25,69 @@ using Row = SellRow;
 void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
   const ExplicitFactor& E = f.host;
   const int N = E.N, nw = block / SLICE;
-  // E1: rows by decreasing length, columns in matrix order.
+  // E1: rows by decreasing length, columns in matrix order.  Rows of more than
+  // `split_row` entries lie on four lanes (a lane's groups are every fourth of the
+  // row's), sixteen rows to a slice: a wave then no longer spends most of the
+  // pass on the longest row.  (FP64; FP32 keeps whole rows, see Shape in
+  // nr_kernels.hip.)
   std::vector<int> order(N);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return E.e1[a].size() > E.e1[b].size(); });
-  const int ns1 = (N + SLICE - 1) / SLICE;
-  std::vector<Row> rows1((size_t)ns1 * SLICE);
-  std::vector<int> rid((size_t)ns1 * SLICE, -1);
-  for (int q = 0; q < N; ++q) {
-    const int r = order[q];
-    rid[q] = r;
-    for (auto [j, v] : E.e1[r]) rows1[q].push_back({E.perm[j], v, 0.0});
-  }
-  const auto [off1, width1] = upload_psell(ctx, rows1, f.e1);   // widths in groups of four entries
-  // Slices to waves: longest first, each to the least loaded wave with room.
-  std::vector<int> sl(ns1);
-  std::iota(sl.begin(), sl.end(), 0);
-  std::stable_sort(sl.begin(), sl.end(), [&](int a, int b) { return width1[a] > width1[b]; });
-  // (the slice list is longest first, so the greedy assignment balances the
-  // longest slices first; a wave may take any number of slices, so the one
-  // with the longest slice takes few others)
-  // Per wave, e1_nq entries: (group offset, width, first row of the slice, 0);
-  // width 0 past the wave's list.
-  std::vector<int> load(nw, 0), cnt(nw, 0), owner(ns1, 0), slot(ns1, 0);
-  for (int s : sl) {
-    int best = 0;
-    for (int w = 1; w < nw; ++w)
-      if (load[w] < load[best]) best = w;
-    owner[s] = best;
-    slot[s] = cnt[best]++;
-    load[best] += (width1[s] + 1) / 2 + 1;   // rounds of up to two groups, plus the slice's own overhead
-  }
-  const int nq1 = std::max(1, *std::max_element(cnt.begin(), cnt.end()));
-  std::vector<int> wave_list((size_t)nw * nq1 * 4, 0);
-  for (int s = 0; s < ns1; ++s) {
-    int* e = &wave_list[((size_t)owner[s] * nq1 + slot[s]) * 4];
-    e[0] = off1[s];
-    e[1] = width1[s];
-    e[2] = s * SLICE;
-  }
-  f.e1_nq = nq1;
+  auto lay_out_e1 = [&](EfBuffers::E1& f1, size_t split_row) {
+    const int n_split = (int)(std::find_if(order.begin(), order.end(), [&](int r) { return E.e1[r].size() <= split_row; }) -
+                              order.begin());
+    const int ns_split = (n_split + 15) / 16, ns1 = ns_split + (N - n_split + SLICE - 1) / SLICE;
+    std::vector<Row> rows1((size_t)ns1 * SLICE);
+    std::vector<int> rid((size_t)ns1 * SLICE, -1);
+    for (int q = 0; q < N; ++q) {
+      const int r = order[q];
+      const bool split = q < n_split;
+      const int at = split ? q / 16 * SLICE + q % 16 * 4 : ns_split * SLICE + q - n_split;
+      rid[at] = r;
+      int e = 0;
+      for (auto [j, v] : E.e1[r]) {
+        rows1[at + (split ? e / 4 % 4 : 0)].push_back({E.perm[j], v, 0.0});
+        ++e;
+      }
+    }
+    const auto [off1, width1] = upload_psell(ctx, rows1, f1.val);   // widths in groups of four entries
+    // Slices to waves, for each split of the workgroup: longest first, each to
+    // the least loaded wave (a wave may take any number of slices, so the one
+    // with the longest slice takes few others).  Per wave, e1_nq entries; width 0
+    // past the wave's list.
+    std::vector<int> sl(ns1);
+    std::iota(sl.begin(), sl.end(), 0);
+    std::stable_sort(sl.begin(), sl.end(), [&](int a, int b) { return width1[a] > width1[b]; });
+    for (int v = 0; v < 3; ++v) {
+      const int nws = nw << v;
+      std::vector<int> load(nws, 0), cnt(nws, 0), owner(ns1, 0), slot(ns1, 0);
+      for (int s : sl) {
+        int best = 0;
+        for (int w = 1; w < nws; ++w)
+          if (load[w] < load[best]) best = w;
+        owner[s] = best;
+        slot[s] = cnt[best]++;
+        load[best] += (width1[s] + 1) / 2 + 1;   // rounds of up to two groups, plus the slice's own overhead
+      }
+      const int nq1 = std::max(1, *std::max_element(cnt.begin(), cnt.end()));
+      std::vector<int> wave_list((size_t)nws * nq1 * 4, 0);
+      for (int s = 0; s < ns1; ++s) {
+        int* e = &wave_list[((size_t)owner[s] * nq1 + slot[s]) * 4];
+        e[0] = off1[s];
+        e[1] = width1[s];
+        e[2] = s * SLICE;
+        e[3] = s < ns_split ? 1 : 0;
+      }
+      f1.nq[v] = nq1;
+      f1.wave[v] = upload(ctx, wave_list);
+    }
+    f1.row = upload(ctx, rid);
+    return 4 * SLICE * (long)std::accumulate(width1.begin(), width1.end(), 0);   // stored entries
+  };
+  constexpr size_t SPLIT_ROW = 16;
+  lay_out_e1(f.e1[0], SPLIT_ROW);
+  const long padded1 = lay_out_e1(f.e1[1], (size_t)N);
   // E3: one row per matrix row (bus order), padded to nbp rows.
   std::vector<Row> rows3(nbp);
   for (int i = 0; i < N; ++i)
@@ -83,22 +105,32 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
     });
     const int ns = (N + SLICE - 1) / SLICE;
     if (ns > nw * kb) fail(PF_INVALID_ARG, "factor does not fit the workgroup layout");
-    std::vector<Row> rows3s((size_t)nw * kb * SLICE);
-    std::vector<int> rid3((size_t)nw * kb * SLICE, -1), load3(nw, 0), cnt3(nw, 0);
-    for (int s = 0; s < ns; ++s) {
-      const int w4 = std::max(4, ((int)E.e3[E.pinv[ord[(size_t)s * SLICE]]].size() + 3) / 4 * 4);
-      int best = -1;
-      for (int w = 0; w < nw; ++w)
-        if (cnt3[w] < kb && (best < 0 || load3[w] < load3[best])) best = w;
-      const int pos = cnt3[best]++ * nw + best;
-      load3[best] += (w4 + 7) / 8;   // rounds of eight entries, then one of four
-      for (int l = 0; l < SLICE && s * SLICE + l < N; ++l) {
-        const int i = ord[(size_t)s * SLICE + l];
-        for (auto [p, v] : E.e3[E.pinv[i]]) rows3s[(size_t)pos * SLICE + l].push_back({p, v, 0.0});
-        rid3[(size_t)pos * SLICE + l] = i;
-      }
+    std::vector<Row> rows3s((size_t)ns * SLICE);
+    std::vector<int> rid3((size_t)ns * SLICE, -1);
+    for (int q = 0; q < N; ++q) {
+      for (auto [p, v] : E.e3[E.pinv[ord[q]]]) rows3s[q].push_back({p, v, 0.0});
+      rid3[q] = ord[q];
     }
-    upload_psell(ctx, rows3s, f.e3s);
+    const auto [off3, width3] = upload_psell(ctx, rows3s, f.e3s);
+    for (int v = 0; v < 3 && kb % (1 << v) == 0; ++v) {
+      const int nws = nw << v, kbs = kb >> v;
+      std::vector<int> load3(nws, 0), cnt3(nws, 0), pos((size_t)nws * kbs * 4, 0);
+      for (int s = 0; s < ns; ++s) {
+        int best = -1;
+        for (int w = 0; w < nws; ++w)
+          if (cnt3[w] < kbs && (best < 0 || load3[w] < load3[best])) best = w;
+        int* e = &pos[((size_t)cnt3[best]++ * nws + best) * 4];
+        e[0] = off3[s];
+        e[1] = width3[s];
+        e[2] = s * SLICE;
+        load3[best] += (width3[s] + 1) / 2;   // rounds of two groups, then one
+      }
+      // (positions without a slice: width 0, the rows of none)
+      for (size_t q = 0; q < pos.size(); q += 4)
+        if (pos[q + 1] == 0) pos[q + 2] = ns * SLICE;
+      f.e3s_pos[v] = upload(ctx, pos);
+    }
+    rid3.resize((size_t)(ns + 1) * SLICE, -1);
     f.e3s_row = upload(ctx, rid3);
   }
   // With no core, A^-1 = E3 E1 (times the permutation) may stay sparse: if its
@@ -126,18 +158,16 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
       }
       return t;
     };
-    if (2 * padded(rowsd) <= 3 * (padded(rows1) + padded(rows3))) {
+    if (2 * padded(rowsd) <= 3 * (padded1 + padded(rows3))) {
       upload_psell(ctx, rowsd, f.inv);
       f.direct = true;
     }
   }
-  f.e1_row = upload(ctx, rid);
-  f.e1_wave = upload(ctx, wave_list);
   // S^-1 in packs of P columns per row, [l / P][i][P], zero-padded (P = 2 in
-  // FP64, 4 in FP32: one 16-byte load per pack)
+  // FP64, 4 in FP32: one 16-byte load per pack), to four parts of as many packs
   const int k = E.k;
   auto packed = [&](int P) {
-    const int kp = (k + P - 1) / P;
+    const int kp = ((k + P - 1) / P + 3) / 4 * 4;
     std::vector<double> out((size_t)std::max(1, kp * k * P), 0.0);
     for (int lp = 0; lp < kp; ++lp)
       for (int i = 0; i < k; ++i)
@@ -211,10 +241,14 @@ EfDev<T> EfBuffers::view() const {
   d.N = host.N;
   d.c = host.c;
   d.k = host.k;
-  d.e1 = e1.view<T>();
-  d.e1_row = e1_row.as<int>();
-  d.e1_wave = e1_wave.as<int>();
-  d.e1_nq = e1_nq;
+  const E1& f1 = e1[f64 ? 0 : 1];
+  d.e1 = f1.val.view<T>();
+  d.e1_row = f1.row.as<int>();
+  for (int v = 0; v < 3; ++v) {
+    d.e1_wave[v] = f1.wave[v].as<int>();
+    d.e1_nq[v] = f1.nq[v];
+    d.e3s_pos[v] = e3s_pos[v].as<int>();
+  }
   d.e3 = e3.view<T>();
   d.e3s = e3s.view<T>();
   d.e3s_row = e3s_row.as<int>();
@@ -374,11 +408,11 @@ TxNetwork* tx_network_create(Context* ctx, int n_bus, int nnz, const int32_t* ro
     }
   const auto hy = upload_psell(ctx, yr, net->y, true);
   {
-    // Layout entry of each caller CSR entry: row i's p-th (sorted) internal
-    // entry sits at 4 (off[i / 64] + 64 (p / 4) + i % 64) + p % 4.
+    // Place in the FP64 layout of each caller CSR entry: row i's p-th (sorted)
+    // internal entry.
     const std::vector<int>& yoff = hy.first;
     auto ypos = [&](int i, int p) {
-      return 4 * ((int64_t)yoff[i / 64] + 64 * (int64_t)(p / 4) + i % 64) + p % 4;
+      return psell_at<double2>(4 * ((int64_t)yoff[i / 64] + 64 * (int64_t)(p / 4) + i % 64) + p % 4);
     };
     int64_t E = 0;
     for (int w : hy.second) E += 4 * 64 * (int64_t)w;

@@ -159,6 +159,13 @@ __device__ __forceinline__ double wave_prefix(double v) {
   return v;
 }
 
+// the value of the lane before, 0 in lane 0
+__device__ __forceinline__ double wave_shr1(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, true));
+}
+
 // max over the wave of values that are not negative, NaN if any is (every lane gets it)
 __device__ __forceinline__ double wave_nanmax_pos(double v) {
   const bool bad = __any(v != v);

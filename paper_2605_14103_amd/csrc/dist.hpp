@@ -24,15 +24,16 @@ namespace pfx {
 // in depth-first preorder, so a bus's subtree is the positions q .. last(q).
 // Entering and leaving a bus are events e of the same traversal.
 struct TreeDev {
-  int nb, nbp;             // buses below the slack; rounded up to 64
+  int nb, nbp;             // buses below the slack; rounded up to the kernel's threads
   const int4* bus;         // [nbp] x: caller's index of phase a | phases with a wye load << 24 |
                            //       (delta load ? 1 << 27 : 0), y: free index of phase a,
                            //       z: parent's position (-1: the slack), w: last(q)
-  const int4* link;        // [nbp] first eight children as 16-bit positions (0x8000: none)
+  const int4* link;        // [nbp] first eight children as 16-bit positions (64 (E | 1), E = nbp / 64: none)
   const int2* rest;        // [nbp] x: first entry of the other children in `more`, y: their count
   const int* more;
   const int* kids;         // [nbp / 64] most children (up to eight) of a wave's buses
-  const int2* event;       // [nbp] events 2 q and 2 q + 1: position entered, or ~position left
+  const int* event;        // [nbp] events 2 q and 2 q + 1 as 16 bits each: 8 times the place (E | 1) (p / E) + p % E
+                           //       of position p, + 1 if it is left (past the last event: position nb, left)
   const double2* y;        // [6][nbp] the segment above: admittance aa, bb, cc, ab, bc, ca
   const double2* z;        // [6][nbp] and its inverse
   int slack;               // caller's index of the slack's phase a
@@ -90,7 +91,7 @@ struct DistNetwork {
                            // row-major, W64 in K blocks of ZB_BK: (k, n) at
                            // ((k / ZB_BK) Np + n) ZB_BK + k % ZB_BK
   // Tree form (nb > 0: the feeder is a tree of at most ZB_TREE_MAX buses, see build_tree)
-  int tree_nb = 0, tree_nbp = 0;
+  int tree_nb = 0, tree_nbp = 0, tree_waves = 0;
   DeviceBuffer tr_bus, tr_link, tr_rest, tr_more, tr_kids, tr_event, tr_y, tr_z;
   DeviceBuffer slack_d;    // 3 slack node indices
   DeviceBuffer vslack_d;   // 6 doubles

@@ -165,9 +165,13 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
       todo.push_back({*it, false});
     }
   }
-  const int nb = (int)order.size(), nbp = round_up(nb, 64);
+  const int nb = (int)order.size();
   if (nb != nbus - 1) return;
-  std::vector<int> bus(4 * (size_t)nbp, 0), link(4 * (size_t)nbp, (int)0x80008000u), more, ev(2 * (size_t)nbp, 0);
+  int waves = 16;   // of the numbers that zb_tree is built for, the least that fits
+  for (int w : {13, 10, 8, 6, 5, 4, 3, 2, 1})
+    if (64 * w >= nb) waves = w;
+  const int nbp = 64 * waves, none = 64 * (waves | 1);
+  std::vector<int> bus(4 * (size_t)nbp, 0), link(4 * (size_t)nbp, none | none << 16), more, ev(nbp, 0);
   std::vector<int> rest(2 * (size_t)nbp, 0), kids(nbp / 64, 0);
   std::vector<double> y(12 * (size_t)nbp, 0.0), z(12 * (size_t)nbp, 0.0);
   for (int q = 0; q < nb; ++q) {
@@ -182,7 +186,7 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
     std::vector<int> ch;
     for (auto& [c, B] : rows[b])
       if (c != b && c != parent[b]) ch.push_back(pos[c]);
-    auto at = [&](size_t k) { return k < ch.size() ? ch[k] : 0x8000; };
+    auto at = [&](size_t k) { return k < ch.size() ? ch[k] : none; };
     for (size_t k = 0; k < 4; ++k) link[4 * (size_t)q + k] = at(2 * k) | at(2 * k + 1) << 16;
     rest[2 * (size_t)q] = (int)more.size();
     rest[2 * (size_t)q + 1] = ch.size() > 8 ? (int)ch.size() - 8 : 0;
@@ -206,10 +210,16 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
       z[o + 1] = zs[k].imag();
     }
   }
-  for (int e = 0; e < 2 * nb; ++e) ev[e] = event[e] >= 0 ? pos[event[e]] : ~pos[~event[e]];
+  for (int e = 0; e < 2 * nbp; ++e) {
+    const bool real = e < 2 * nb;
+    const int q = !real ? nb : pos[event[e] >= 0 ? event[e] : ~event[e]];
+    const int w = 8 * ((waves | 1) * (q / waves) + q % waves) + (!real || event[e] < 0 ? 1 : 0);
+    ev[e / 2] |= w << 16 * (e % 2);
+  }
   if (more.empty()) more.push_back(0);
   net.tree_nb = nb;
   net.tree_nbp = nbp;
+  net.tree_waves = waves;
   net.tr_bus = upload(ctx, bus);
   net.tr_link = upload(ctx, link);
   net.tr_rest = upload(ctx, rest);
@@ -231,7 +241,7 @@ TreeDev DistNetwork::tree_view() const {
   d.rest = tr_rest.as<int2>();
   d.more = tr_more.as<int>();
   d.kids = tr_kids.as<int>();
-  d.event = tr_event.as<int2>();
+  d.event = tr_event.as<int>();
   d.y = tr_y.as<double2>();
   d.z = tr_z.as<double2>();
   d.slack = slack[0];

@@ -635,38 +635,55 @@ __global__ __launch_bounds__(ZB_THREADS) void zb_finish(DistDev net, ZbusLaunch 
 // currents y (v_parent - v_q), which is the same sum as Y_NN v + c without its
 // cancellation.
 //
-// Bound: seven short phases between barriers per iteration (LDS latency, the
-// two scans and the complex divisions, about 500 FP64 instructions a wave);
-// HBM is touched for the loads and the result only.  Against this, the general
-// forms pay two launches, a read-back and a pass of v and r through HBM per
-// iteration, and a dense product or a few hundred dependent factor levels.
-// Measured, 300 buses: one scenario 1222 -> 32 us, 4096 scenarios 2843 (dense)
-// -> 364 us, 1000 in mixed precision 1038 -> 111 us; 600 buses, 1024 scenarios
-// 1059 (sparse factor) -> 215 us.  So it is taken for every such feeder.
+// Prefix sums: a wave takes a component (phase, real or imaginary part) of the
+// whole scenario, a lane E consecutive places, so that a sum over 64 E places
+// costs E additions and one wave scan.  (With a scan of all six components in
+// every wave and the waves' totals added after a barrier, as first built, the scans were a
+// third of the kernel's instructions.)
+//
+// Bound: instruction issue for large batches, else six short phases between
+// barriers per iteration; HBM is touched for the loads and the result only.
+// Against this, the general forms pay two launches, a read-back and a pass of
+// v and r through HBM per iteration, and a dense product or a few hundred
+// dependent factor levels.  Measured against them, 300 buses: one scenario 1222
+// -> 27 us, 4096 scenarios 2852 (dense) -> 312 us, 1000 in mixed precision 1038
+// -> 95 us; 600 buses, 1024 scenarios 1059 (sparse factor) -> 190 us.  So it is
+// taken for every such feeder.  (All components scanned in every wave: 29, 352, 107 and 212 us.)
 //
 // STEP: an engine's step (a.slots): v, the statistics and the flags come from
 // and go back to the slot's state, `steps` residuals at most; otherwise the
 // solve runs from v0 to its end and writes the outputs.
-template <bool STEP>
-__global__ __launch_bounds__(ZB_TREE_MAX) void zb_tree(TreeDev net, const double* v0, int Kp, ZbusLaunch a,
-                                                       int steps) {
+// Registers: 128 (four waves per SIMD), or 168 where that leaves as many
+// workgroups on a CU (6 waves: two, 10 waves: one).
+template <bool STEP, int E>
+__global__ __launch_bounds__(64 * E) __attribute__((amdgpu_waves_per_eu(E == 6 || E == 10 ? 3 : 4))) void zb_tree(
+    TreeDev net, const double* v0, int Kp, ZbusLaunch a, int steps) {
   extern __shared__ D2 tsm[];
-  constexpr int MAXW = ZB_TREE_MAX / WAVE;
-  __shared__ double red[2][MAXW], tot[2][MAXW][8];
-  const int nbp = net.nbp, nw = nbp / WAVE;
-  D2* A = tsm;             // [nbp][3] v, then the prefixes of r, then the path sums
-  D2* B = tsm + 3 * nbp;   // [nbp][3] segment currents, then u
+  constexpr int NW = E, NBP = WAVE * E;
+  constexpr int EP = E | 1, PITCH = WAVE * EP;   // an odd stride between lanes: no bank conflicts
+  __shared__ double red[2][NW];
+  D2* A = tsm;                 // [NBP][3] v; then as components (below) r and its prefixes
+  D2* B = tsm + 3 * PITCH;     // [NBP][3] segment currents, and the absent child's zero at PITCH; then u and its path sums
+  // component c of place x (position q at EP (q / E) + q % E): a[PITCH c + x]
+  double* Ac = reinterpret_cast<double*>(A);
+  double* Bc = reinterpret_cast<double*>(B);
   const int g = blockIdx.x, b = STEP ? a.slots[g] : g;
   if (STEP && a.active[b] == 0) {
     if (threadIdx.x == 0) a.step_done[g] = 1;
     return;
   }
   const int q = threadIdx.x, wv = wave_id(), lane = lane_id();
+  auto place = [](int x) { return EP * (x / E) + x % E; };
+  if (q < 3) B[3 * PITCH + q] = D2{0.0, 0.0};
   const bool live = q < net.nb;
   const int4 bus = cld(net.bus, (unsigned)q);
   int4 link = cld(net.link, (unsigned)q);
-  int2 ev = cld(net.event, (unsigned)q);
   const int2 rest = cld(net.rest, (unsigned)q);
+  // the scanning waves' events, 2 E per lane
+  unsigned ev[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) ev[e] = wv < 6 ? (unsigned)cld(net.event, (unsigned)(lane * E + e)) : 0u;
+  const int own = place(q), end = place(bus.w);
   const int kids = __builtin_amdgcn_readfirstlane(cld(net.kids, (unsigned)wv));
   const unsigned ext = (unsigned)bus.x & 0xffffffu;
   const bool delta = (bus.x >> 27) & 1;
@@ -692,40 +709,20 @@ __global__ __launch_bounds__(ZB_TREE_MAX) void zb_tree(TreeDev net, const double
   double sprev = STEP ? a.st[3 * (int64_t)b + 1] : 0.0;
   double mm = 0.0, sabs = 0.0, change = STEP ? a.st[3 * (int64_t)b + 2] : 0.0;
   bool conv = false, more = true;
-  // workgroup prefix sums of six values per thread, in two halves around a barrier
-  auto totals = [&](double (&x)[6], int buf) {
-#pragma unroll
-    for (int c = 0; c < 6; ++c) x[c] = wave_prefix(x[c]);
-    if (lane == WAVE - 1) {
-#pragma unroll
-      for (int c = 0; c < 6; ++c) tot[buf][wv][c] = x[c];
-    }
-  };
-  // (lane c sums component c over the waves before this one)
-  auto offsets = [&](double (&x)[6], int buf) {
-    double o = 0.0;
-    for (int w = 0; w < wv; w += 4) {
-      double t[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) t[u] = tot[buf][w + u][lane & 7];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) o += w + u < wv ? t[u] : 0.0;
-    }
-#pragma unroll
-    for (int c = 0; c < 6; ++c) x[c] += lane_value(o, c);
-  };
   for (int k = 0;; ++k) {
     // the segment's y and z are read again in each iteration, and what follows
-    // from link and ev is formed again (hiding their values keeps some 80
+    // from link and ev is formed again (hiding their values keeps some 90
     // registers from being held throughout)
     const double2 *yp = net.y, *zp = net.z;
-    asm volatile("" : "+s"(yp), "+s"(zp), "+v"(link.x), "+v"(link.y), "+v"(link.z), "+v"(link.w), "+v"(ev.x), "+v"(ev.y));
+    asm volatile("" : "+s"(yp), "+s"(zp), "+v"(link.x), "+v"(link.y), "+v"(link.z), "+v"(link.w));
+#pragma unroll
+    for (int e = 0; e < E; ++e) asm volatile("" : "+v"(ev[e]));
 #pragma unroll
     for (int p = 0; p < 3; ++p) A[3 * q + p] = v[p];
     D2 y[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-      const double2 t = cld(yp, (unsigned)(c * nbp + q));
+      const double2 t = cld(yp, (unsigned)(c * NBP + q));
       y[c] = D2{t.x, t.y};
     }
     __syncthreads();
@@ -766,70 +763,75 @@ __global__ __launch_bounds__(ZB_TREE_MAX) void zb_tree(TreeDev net, const double
     // r = i(v) + current from above - currents into the children
 #pragma unroll
     for (int p = 0; p < 3; ++p) r[p] += cur[p];
-    // (children by pairs, as many as the wave's buses have; absent ones read position 0's and count 0)
-    auto child = [&](int c) {   // c constant
-      const int w = c < 2 ? link.x : c < 4 ? link.y : c < 6 ? link.z : link.w;
-      return (c & 1 ? w >> 16 : w) & 0xffff;
-    };
-    auto pair = [&](int c) {
-      const int c0 = child(c), c1 = child(c + 1);
-      D2 i0[3], i1[3];
+    // (children by pairs, as many as the wave's buses have; absent ones read zero)
+    auto pair = [&](int w) {
+      const int c0 = w & 0xffff, c1 = (unsigned)w >> 16;
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        i0[p] = B[3 * (c0 & 0x7fff) + p];
-        i1[p] = B[3 * (c1 & 0x7fff) + p];
-      }
-      const double f0 = c0 & 0x8000 ? 0.0 : 1.0, f1 = c1 & 0x8000 ? 0.0 : 1.0;
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        r[p] -= f0 * i0[p];
-        r[p] -= f1 * i1[p];
+        r[p] -= B[3 * c0 + p];
+        r[p] -= B[3 * c1 + p];
       }
     };
-    if (kids > 0) pair(0);
-    if (kids > 2) pair(2);
-    if (kids > 4) pair(4);
-    if (kids > 6) pair(6);
+    if (kids > 0) pair(link.x);
+    if (kids > 2) pair(link.y);
+    if (kids > 4) pair(link.z);
+    if (kids > 6) pair(link.w);
     for (int c = 0; c < rest.y; ++c) {
       const int ch = cld(net.more, (unsigned)(rest.x + c));
 #pragma unroll
       for (int p = 0; p < 3; ++p) r[p] -= B[3 * ch + p];
     }
-    double x[6];
     double m1 = 0.0, s1 = 0.0;
+    bool nan = false;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       if (!live) r[p] = D2{0.0, 0.0};
       const double dr = v[p].x * r[p].x + v[p].y * r[p].y, di = v[p].y * r[p].x - v[p].x * r[p].y;  // v conj(r)
-      m1 = nanmax(m1, dr * dr + di * di);
+      const double m = dr * dr + di * di;
+      nan |= m != m;
+      m1 = __builtin_fmax(m1, m);
       s1 += live ? sqrt(v[p].x * v[p].x + v[p].y * v[p].y) : 0.0;
-      x[2 * p] = r[p].x;
-      x[2 * p + 1] = r[p].y;
+      Ac[PITCH * (2 * p) + own] = r[p].x;
+      Ac[PITCH * (2 * p + 1) + own] = r[p].y;
     }
+    if (nan) m1 = __builtin_nan("");
     m1 = wave_nanmax_pos(m1);
     s1 = wave_total(s1);
     if (lane == 0) {
       red[0][wv] = m1;
       red[1][wv] = s1;
     }
-    totals(x, 0);
     __syncthreads();
-    // (lane w takes wave w's partials)
-    mm = sqrt(wave_nanmax_pos(lane < nw ? red[0][lane & (MAXW - 1)] : 0.0));
-    sabs = wave_total(lane < nw ? red[1][lane & (MAXW - 1)] : 0.0);
+    mm = red[0][0];
+    sabs = red[1][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      mm = nanmax(mm, red[0][w]);
+      sabs += red[1][w];
+    }
+    mm = sqrt(mm);
     if (it > 0) change = fabs(sabs - sprev);
     sprev = sabs;
     conv = mm <= a.tol;
     more = !conv && mm == mm && it < a.max_iter;
     if (!more) break;
     ++it;
-    offsets(x, 0);
+    // r -> its prefixes, in place
+    for (int c = wv; c < 6; c += NW) {
+      double* at = Ac + PITCH * c + EP * lane;
+      double x[E], t = 0.0;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) A[3 * q + p] = D2{x[2 * p], x[2 * p + 1]};
+      for (int e = 0; e < E; ++e) x[e] = at[e];
+#pragma unroll
+      for (int e = 0; e < E; ++e) t += x[e];
+      t = wave_shr1(wave_prefix(t));
+#pragma unroll
+      for (int e = 0; e < E; ++e) at[e] = t += x[e];
+    }
     D2 z[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-      const double2 t = cld(zp, (unsigned)(c * nbp + q));
+      const double2 t = cld(zp, (unsigned)(c * NBP + q));
       z[c] = D2{t.x, t.y};
     }
     __syncthreads();
@@ -837,40 +839,48 @@ __global__ __launch_bounds__(ZB_TREE_MAX) void zb_tree(TreeDev net, const double
     {
       D2 J[3], u[3];
 #pragma unroll
-      for (int p = 0; p < 3; ++p) J[p] = A[3 * bus.w + p] - D2{x[2 * p], x[2 * p + 1]} + r[p];
+      for (int p = 0; p < 3; ++p) {
+        J[p].x = Ac[PITCH * (2 * p) + end] - Ac[PITCH * (2 * p) + own] + r[p].x;
+        J[p].y = Ac[PITCH * (2 * p + 1) + end] - Ac[PITCH * (2 * p + 1) + own] + r[p].y;
+      }
       sym3(z, J, u);
 #pragma unroll
-      for (int p = 0; p < 3; ++p) B[3 * q + p] = u[p];
-    }
-    __syncthreads();
-    // this thread's two events
-    const int e0 = ev.x >= 0 ? ev.x : ~ev.x, e1 = ev.y >= 0 ? ev.y : ~ev.y;
-    const double g0 = !live ? 0.0 : ev.x < 0 ? -1.0 : 1.0, g1 = !live ? 0.0 : ev.y < 0 ? -1.0 : 1.0;
-    double h[6];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const D2 t0 = B[3 * e0 + p], t1 = g1 * B[3 * e1 + p];
-      x[2 * p] = g0 * t0.x + t1.x;
-      x[2 * p + 1] = g0 * t0.y + t1.y;
-      h[2 * p] = t1.x;
-      h[2 * p + 1] = t1.y;
-    }
-    totals(x, 1);
-    __syncthreads();
-    offsets(x, 1);
-    // prefix at the second event, and at the first (less the second's term)
-    if (live) {
-#pragma unroll
       for (int p = 0; p < 3; ++p) {
-        const D2 t = {x[2 * p], x[2 * p + 1]};
-        if (ev.y >= 0) A[3 * e1 + p] = t;
-        if (ev.x >= 0) A[3 * e0 + p] = t - D2{h[2 * p], h[2 * p + 1]};
+        Bc[PITCH * (2 * p) + own] = u[p].x;
+        Bc[PITCH * (2 * p + 1) + own] = u[p].y;
+      }
+    }
+    __syncthreads();
+    // u -> the prefix of the events at each bus's entry, in place (every u is
+    // read before the first sum is written: one wave has the component)
+    for (int c = wv; c < 6; c += NW) {
+      unsigned char* at = reinterpret_cast<unsigned char*>(Bc + PITCH * c);
+      auto word = [&](int e) { return e & 1 ? ev[e / 2] >> 16 : ev[e / 2] & 0xffffu; };
+      double x[2 * E], t = 0.0;
+#pragma unroll
+      for (int e = 0; e < 2 * E; ++e) {
+        const unsigned w = word(e);
+        const double u = *reinterpret_cast<const double*>(at + (w & 0xfff8u));
+        x[e] = __hiloint2double(__double2hiint(u) ^ (int)(w << 31), __double2loint(u));   // - if left
+      }
+#pragma unroll
+      for (int e = 0; e < 2 * E; ++e) t += x[e];
+      t = wave_shr1(wave_prefix(t));
+#pragma unroll
+      for (int e = 0; e < 2 * E; ++e) {
+        const unsigned w = word(e);
+        t += x[e];
+        // (a bus left: to a place that nobody reads)
+        *reinterpret_cast<double*>(at + (w & 1 ? (unsigned)(8 * (6 * PITCH + 6) - 8 * PITCH * c) : w & 0xfff8u)) = t;
       }
     }
     __syncthreads();
     if (live) {
 #pragma unroll
-      for (int p = 0; p < 3; ++p) v[p] += A[3 * q + p];
+      for (int p = 0; p < 3; ++p) {
+        v[p].x += Bc[PITCH * (2 * p) + own];
+        v[p].y += Bc[PITCH * (2 * p + 1) + own];
+      }
     }
     if (STEP && k + 1 >= steps) break;
   }
@@ -910,15 +920,33 @@ __global__ __launch_bounds__(ZB_TREE_MAX) void zb_tree(TreeDev net, const double
   }
 }
 
-void launch_tree(DistNetwork& net, const ZbusLaunch& a, int steps, hipStream_t s) {
+template <int E>
+void launch_tree_as(DistNetwork& net, const ZbusLaunch& a, int steps, hipStream_t s) {
   const TreeDev d = net.tree_view();
-  const size_t lds = (size_t)6 * d.nbp * sizeof(D2);
-  auto kernel = a.slots ? zb_tree<true> : zb_tree<false>;
+  // (the absent child's zero, and the place that nobody reads, behind B)
+  const size_t lds = (size_t)(6 * WAVE * (E | 1) + 4) * sizeof(D2);
+  auto kernel = a.slots ? zb_tree<true, E> : zb_tree<false, E>;
   if (lds > 60 * 1024)
     PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds));
-  hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(d.nbp), lds, s, d, net.v0.as<double>(), net.Kp, a, steps);
+  hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(WAVE * E), lds, s, d, net.v0.as<double>(), net.Kp, a, steps);
   PFX_HIP(hipGetLastError());
+}
+
+void launch_tree(DistNetwork& net, const ZbusLaunch& a, int steps, hipStream_t s) {
+  switch (net.tree_waves) {
+    case 1: return launch_tree_as<1>(net, a, steps, s);
+    case 2: return launch_tree_as<2>(net, a, steps, s);
+    case 3: return launch_tree_as<3>(net, a, steps, s);
+    case 4: return launch_tree_as<4>(net, a, steps, s);
+    case 5: return launch_tree_as<5>(net, a, steps, s);
+    case 6: return launch_tree_as<6>(net, a, steps, s);
+    case 8: return launch_tree_as<8>(net, a, steps, s);
+    case 10: return launch_tree_as<10>(net, a, steps, s);
+    case 13: return launch_tree_as<13>(net, a, steps, s);
+    case 16: return launch_tree_as<16>(net, a, steps, s);
+  }
+  fail(PF_INVALID_ARG, "no tree kernel for this many waves");
 }
 
 // The update's GEMM: FP64 without LDS (W in K blocks), FP32 through LDS (W row-major).

@@ -49,15 +49,15 @@ class _PFSolve(torch.autograd.Function):
         if grad_v is None:
             return None, None, None, None, None, None, None
         gp, gq, _, ok = ctx.net.adjoint(v, grad_v.contiguous(), **ctx.adj_opts)
-        fwd_bad = (conv == 0).nonzero().flatten().tolist()
-        adj_bad = (ok == 0).nonzero().flatten().tolist()
-        if fwd_bad or adj_bad:
+        bad = (conv == 0) | (ok == 0)
+        if bad.any():   # the one point where the host waits for the device
+            fwd_bad = (conv == 0).nonzero().flatten().tolist()
+            adj_bad = (ok == 0).nonzero().flatten().tolist()
             msg = (f"power-flow gradient undefined for scenarios: forward solve not converged {fwd_bad[:16]}, "
                    f"adjoint GMRES not converged {adj_bad[:16]}")
             if ctx.on_failure == "raise":
                 raise NonConvergedGradient(msg, fwd_bad, adj_bad)
             warnings.warn(msg + " (their gradient rows are set to zero)", RuntimeWarning, stacklevel=2)
-            bad = (conv == 0) | (ok == 0)
             gp = gp.masked_fill(bad[:, None], 0.0)
             gq = gq.masked_fill(bad[:, None], 0.0)
         return gp, gq, None, None, None, None, None

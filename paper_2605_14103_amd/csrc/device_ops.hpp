@@ -229,10 +229,11 @@ __device__ T block_sum(T v, T* part) {
   return s;
 }
 
+// Workgroup maximum of values that are not negative, NaN if any is.
 template <int BLOCK>
-__device__ double block_nanmax(double v, double* part) {
+__device__ double block_nanmax_pos(double v, double* part) {
   constexpr int NW = BLOCK / WAVE;
-  v = wave_nanmax(v);
+  v = wave_nanmax_pos(v);
   if (lane_id() == 0) part[wave_id()] = v;
   __syncthreads();
   double s = part[0];

@@ -620,22 +620,35 @@ __device__ void efac_apply(const EfDev<T>& f, const T* x, T* aux, T* tmp, T (&ou
     const int kp = (f.k + P - 1) / P;
     for (int i = threadIdx.x; i < f.k; i += Sh::BLOCK) {
       T acc[4] = {0, 0, 0, 0};
-      auto round = [&](int lp, auto n) {
+      int lp = 0;
+      auto add = [&](const int4& v, int l) {
+        T e[P];
+        __builtin_memcpy(e, &v, 16);
+#pragma unroll
+        for (int q = 0; q < P; ++q) acc[q & 3] = fm(e[q], tmp[l * P + q], acc[q & 3]);
+      };
+      auto rounds = [&](auto n) {   // n packs in flight while they last
         constexpr int N = decltype(n)::value;
-        int4 v[N];
+        for (; lp + N <= kp; lp += N) {
+          int4 v[N];
 #pragma unroll
-        for (int u = 0; u < N; ++u) v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((lp + u) * f.k + i));
+          for (int u = 0; u < N; ++u)
+            v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((lp + u) * f.k + i));
 #pragma unroll
-        for (int u = 0; u < N; ++u) {
-          T e[P];
-          __builtin_memcpy(e, &v[u], 16);
-#pragma unroll
-          for (int q = 0; q < P; ++q) acc[q & 3] = fm(e[q], tmp[(lp + u) * P + q], acc[q & 3]);
+          for (int u = 0; u < N; ++u) add(v[u], lp + u);
         }
       };
-      int lp = 0;
-      for (; lp + 8 <= kp; lp += 8) round(lp, std::integral_constant<int, 8>{});
-      for (; lp < kp; ++lp) round(lp, std::integral_constant<int, 1>{});
+      rounds(std::integral_constant<int, 8>{});
+      rounds(std::integral_constant<int, 4>{});
+      if (lp < kp) {   // up to three more at once (past the last the last again, not added)
+        int4 v[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+          v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)(min(lp + u, kp - 1) * f.k + i));
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+          if (lp + u < kp) add(v[u], lp + u);
+      }
       aux[f.c + i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
     }
   } else if constexpr (Sh::S == 1) {
@@ -669,26 +682,23 @@ __device__ void efac_apply(const EfDev<T>& f, const T* x, T* aux, T* tmp, T (&ou
       const int i = i0 + lane % 16;
       T acc = 0;
       if (i < f.k) {
-        int l = 0;
-        for (; l + 8 <= qn; l += 8) {
+        // rounds of eight; past the last pack the last one again, not added (a
+        // tail of single loads took up to seven more round trips: 10 k cycles of 60 k
+        // per Arnoldi step of a split 2000-bus scenario, now 5 k)
+        for (int l = 0; l < qn; l += 8) {
           int4 v[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u)
-            v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((part * qn + l + u) * f.k + i));
+            v[u] = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((part * qn + min(l + u, qn - 1)) * f.k + i));
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
-            T e[P];
-            __builtin_memcpy(e, &v[u], 16);
+            if (l + u < qn) {
+              T e[P];
+              __builtin_memcpy(e, &v[u], 16);
 #pragma unroll
-            for (int q = 0; q < P; ++q) acc = fm(e[q], tmp[(part * qn + l + u) * P + q], acc);
+              for (int q = 0; q < P; ++q) acc = fm(e[q], tmp[(part * qn + l + u) * P + q], acc);
+            }
           }
-        }
-        for (; l < qn; ++l) {
-          const int4 v = cld(reinterpret_cast<const int4*>(f.sinv), (unsigned)((part * qn + l) * f.k + i));
-          T e[P];
-          __builtin_memcpy(e, &v, 16);
-#pragma unroll
-          for (int q = 0; q < P; ++q) acc = fm(e[q], tmp[(part * qn + l) * P + q], acc);
         }
       }
       acc = row_pair_sum<true>(row_pair_sum<false>(acc));
@@ -1259,7 +1269,7 @@ __device__ double mismatch(const TxDev<T>* netp, const Ws<Sh>& ws, double2* vs, 
     fmax = nanmax(fmax, nanmax(fabs(ft), fabs(fv)));
     settle(fmax);
   }
-  return block_nanmax<Sh::BLOCK>(fmax, part);
+  return block_nanmax_pos<Sh::BLOCK>(fmax, part);
 }
 
 // Algorithmic HBM bytes of one scenario (the byte model reported with the
@@ -2335,19 +2345,22 @@ void launch_adjoint(const TxNetwork& net, const AdjLaunch& a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
+constexpr int LOSS_BLOCK = 1024;
 // Branch-current loss L = sum_f |I_f|^2, I_f = (y_s + j b/2) V_f - y_s V_t,
 // and dL/dV in torch's convention conj(g), g_k = dL/dV_k (complex derivative).
 // One workgroup per scenario; the gradient is accumulated per bus by walking
 // each bus's incident branches (no atomics, fixed order).
-__global__ __launch_bounds__(256) void branch_loss_kernel(const TxDev<double>* __restrict__ netp,
+// (1024 threads: with 256, each walked eight buses of a 2000-bus grid one after
+// another, 47 us for 256 scenarios against 30.)
+__global__ __launch_bounds__(LOSS_BLOCK) void branch_loss_kernel(const TxDev<double>* __restrict__ netp,
                                                           const int* inc_ptr, const int* inc_br, LossLaunch a) {
-  __shared__ double red[4];
+  __shared__ double red[LOSS_BLOCK / WAVE];
   const TxDev<double> net = load_desc(netp);
   const int b = blockIdx.x;
   const double* v = a.v + 2 * (int64_t)b * a.ld;
   const int* ext = net.int2ext;
   double acc = 0.0;
-  for (int k = threadIdx.x; k < net.n_branch; k += 256) {
+  for (int k = threadIdx.x; k < net.n_branch; k += LOSS_BLOCK) {
     const int f = ext[net.br_f[k]], t = ext[net.br_t[k]];
     const double ysr = net.br_ys_re[k], ysi = net.br_ys_im[k], hb = 0.5 * net.br_b[k];
     const double vfr = v[2 * f], vfi = v[2 * f + 1], vtr = v[2 * t], vti = v[2 * t + 1];
@@ -2355,11 +2368,11 @@ __global__ __launch_bounds__(256) void branch_loss_kernel(const TxDev<double>* _
     const double ii = ysr * vfi + (ysi + hb) * vfr - (ysr * vti + ysi * vtr);
     acc += ir * ir + ii * ii;
   }
-  const double tot = block_sum<double, 256>(acc, red);
+  const double tot = block_sum<double, LOSS_BLOCK>(acc, red);
   if (threadIdx.x == 0) a.loss[b] = tot;
   if (!a.dl_dv) return;
   double* gout = a.dl_dv + 2 * (int64_t)b * a.ld;
-  for (int i = threadIdx.x; i < net.n; i += 256) {
+  for (int i = threadIdx.x; i < net.n; i += LOSS_BLOCK) {
     double gr = 0.0, gi = 0.0;  // torch gradient dL/dRe + j dL/dIm = 2 sum I_f conj(coef)
     for (int q = inc_ptr[i]; q < inc_ptr[i + 1]; ++q) {
       const int k = inc_br[q];
@@ -2388,7 +2401,7 @@ __global__ __launch_bounds__(256) void branch_loss_kernel(const TxDev<double>* _
 
 void launch_branch_loss(const TxNetwork& net, const LossLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
-  hipLaunchKernelGGL(branch_loss_kernel, dim3(a.batch), dim3(256), 0, s, net.desc<double>(),
+  hipLaunchKernelGGL(branch_loss_kernel, dim3(a.batch), dim3(LOSS_BLOCK), 0, s, net.desc<double>(),
                      net.inc_ptr.as<int>(), net.inc_br.as<int>(), a);
   PFX_HIP(hipGetLastError());
 }

@@ -119,8 +119,8 @@ DirectLuHost build_direct_lu(const TxNetwork& net) {
   }
   D.bph.assign(1, 0);
   for (int l = 0; l < nb; ++l) {
-    D.brow.insert(D.brow.end(), by_b[l].begin(), by_b[l].end());
-    D.bph.push_back((int)D.brow.size());
+    for (int k : by_b[l]) D.brow.insert(D.brow.end(), {k, D.soff[k], D.soff[k + 1], 0});
+    D.bph.push_back((int)D.brow.size() / 4);
   }
   D.fpos.assign(2 * nbp, -1);
   for (int s = 0; s < m; ++s) D.fpos[s < nth ? s : nbp + (s - nth)] = pinv[s];

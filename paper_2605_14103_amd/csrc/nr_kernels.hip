@@ -1694,6 +1694,11 @@ __global__ __launch_bounds__(Sh::BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
 // factorisation (with the forward solve inside it) and the backward solve run
 // one phase per level of the elimination tree, with the phase's targets
 // (rows) spread over the workgroup.
+// Bound by the latency of the phases (a chain of LDS reads of the schedule,
+// of the values, a division and a barrier; 13 + 13 of them on 30 buses): the
+// schedule is read ahead of the values and the loads of several entries are
+// requested together (batch 64: 30 buses 70.0 -> 65.1 us, 118 buses 185 ->
+// 175, 500 buses 482 -> 358).
 //
 // Entries of J for a Ybus entry (i, k), with a = V_i conj(Y_ik V_k) and
 // c = V_i conj(I_i) (the bus power):  i != k: dS_i/dtheta_k = -j a,
@@ -1705,8 +1710,8 @@ __host__ __device__ inline size_t direct_stage_offset(int nbp, int nw, const Dir
   return ((size_t)2 * nbp * 16 + (size_t)2 * nw * 8 + ((size_t)d.n_val + 2 * d.m) * 8 + 15) / 16 * 16;
 }
 __host__ __device__ inline size_t direct_stage_bytes(const DirectDev& d) {
-  return (size_t)16 * (d.n_tg + d.n_ct + d.n_je) +
-         (size_t)4 * ((d.m + 1) + d.n_s + d.m + (d.n_fph + 1) + (d.n_bph + 1));
+  return (size_t)16 * (d.n_tg + d.n_ct + d.n_je + d.m) +
+         (size_t)4 * (d.n_s + (d.n_fph + 1) + (d.n_bph + 1));
 }
 
 // STAGE: the schedule tables (targets, contributions, J entries, S(k) and the
@@ -1736,31 +1741,39 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
   double* rhs = red + 2 * NW + (VG ? 0 : d.n_val);
   double* xs = rhs + m;
   double* val = VG ? a.ws_dval + (int64_t)b * a.ws_dval_stride : red + 2 * NW;
-  int4 *ltg = nullptr, *lct = nullptr, *lje = nullptr;
-  int *lso = nullptr, *lsi = nullptr, *lbr = nullptr, *lfp = nullptr, *lbp = nullptr;
+  int4 *ltg = nullptr, *lct = nullptr, *lje = nullptr, *lbr = nullptr;
+  int *lsi = nullptr, *lfp = nullptr, *lbp = nullptr;
   if constexpr (STAGE) {
     ltg = reinterpret_cast<int4*>(smem + direct_stage_offset(NBP, NW, d));
     lct = ltg + d.n_tg;
     lje = lct + d.n_ct;
-    lso = reinterpret_cast<int*>(lje + d.n_je);
-    lsi = lso + m + 1;
-    lbr = lsi + ns;
-    lfp = lbr + m;
+    lbr = lje + d.n_je;
+    lsi = reinterpret_cast<int*>(lbr + m);
+    lfp = lsi + ns;
     lbp = lfp + d.n_fph + 1;
-    for (int q = tid; q < d.n_tg; q += BLOCK) ltg[q] = cld(d.ftg, (unsigned)q);
-    for (int q = tid; q < d.n_ct; q += BLOCK) lct[q] = cld(d.fct, (unsigned)q);
-    for (int q = tid; q < d.n_je; q += BLOCK) lje[q] = cld(d.je, (unsigned)q);
-    for (int q = tid; q <= m; q += BLOCK) lso[q] = cld(d.soff, (unsigned)q);
-    for (int q = tid; q < ns; q += BLOCK) lsi[q] = cld(d.sidx, (unsigned)q);
-    for (int q = tid; q < m; q += BLOCK) lbr[q] = cld(d.brow, (unsigned)q);
-    for (int q = tid; q <= d.n_fph; q += BLOCK) lfp[q] = cld(d.fph, (unsigned)q);
-    for (int q = tid; q <= d.n_bph; q += BLOCK) lbp[q] = cld(d.bph, (unsigned)q);
+    // eight loads in flight per thread
+    auto copy = [&](auto* dst, const auto* src, int count) {
+      for (int q = tid; q < count; q += 8 * BLOCK) {
+        std::remove_const_t<std::remove_reference_t<decltype(*src)>> v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = cld(src, (unsigned)min(q + u * BLOCK, count - 1));
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (q + u * BLOCK < count) dst[q + u * BLOCK] = v[u];
+      }
+    };
+    copy(ltg, d.ftg, d.n_tg);
+    copy(lct, d.fct, d.n_ct);
+    copy(lje, d.je, d.n_je);
+    copy(lbr, d.brow, m);
+    copy(lsi, d.sidx, ns);
+    copy(lfp, d.fph, d.n_fph + 1);
+    copy(lbp, d.bph, d.n_bph + 1);
     // (made visible by the barriers of the first mismatch)
   }
   auto TG = [&](int q) { if constexpr (STAGE) return ltg[q]; else return cld(d.ftg, (unsigned)q); };
   auto CT = [&](int q) { if constexpr (STAGE) return lct[q]; else return cld(d.fct, (unsigned)q); };
   auto JE = [&](int q) { if constexpr (STAGE) return lje[q]; else return cld(d.je, (unsigned)q); };
-  auto SO = [&](int q) { if constexpr (STAGE) return lso[q]; else return cld(d.soff, (unsigned)q); };
   auto SI = [&](int q) { if constexpr (STAGE) return lsi[q]; else return cld(d.sidx, (unsigned)q); };
   auto BR = [&](int q) { if constexpr (STAGE) return lbr[q]; else return cld(d.brow, (unsigned)q); };
   auto FPH = [&](int q) { if constexpr (STAGE) return lfp[q]; else return cld(d.fph, (unsigned)q); };
@@ -1817,10 +1830,9 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
     {
       const TxDev<double> net = load_desc(netp);
       const double2* yvals = yv ? yv : net.y64.val;
-      for (int e = tid; e < d.n_je; e += BLOCK) {
-        const int4 E = JE(e);
+      auto fill = [&](const int4& E, const double2& y) {
         const int pos = E.x & 0x0fffffff, kind = (int)((unsigned)E.x >> 28);
-        const double2 vi = vs[E.y], vk = vs[E.z], y = cld(yvals, (unsigned)E.w);
+        const double2 vi = vs[E.y], vk = vs[E.z];
         const double tr = y.x * vk.x - y.y * vk.y, ti = y.x * vk.y + y.y * vk.x;  // Y_ik V_k
         double ar = vi.x * tr + vi.y * ti, ai = vi.y * tr - vi.x * ti;            // V_i conj(Y_ik V_k)
         double dtr, dti, dvr, dvi;
@@ -1840,6 +1852,18 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
           dvi = (ai + ci) * ivi;
         }
         val[pos] = kind == 0 ? dtr : kind == 1 ? dvr : kind == 2 ? dti : dvi;
+      };
+      constexpr int U = 4;   // entries per thread whose records and Ybus values are requested together
+      for (int e = tid; e < d.n_je; e += U * BLOCK) {
+        int4 E[U];
+        double2 y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) E[u] = JE(min(e + u * BLOCK, d.n_je - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = cld(yvals, (unsigned)E[u].w);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (e + u * BLOCK < d.n_je) fill(E[u], y[u]);
       }
     }
     __syncthreads();
@@ -1849,31 +1873,70 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
     // the level, in pivot order; x the U entry or rhs[k]).  Pivots of a level
     // read only their own row, column and rhs entry, which no pivot of the
     // level changes, and L stays unscaled (its entries hold L U[k][k]).
-    for (int ph = 0; ph < d.n_fph; ++ph) {
-      const int q1 = FPH(ph + 1);
-      for (int q = FPH(ph) + tid; q < q1; q += BLOCK) {
-        const int4 T = TG(q);
-        double acc = 0.0;
-        for (int c = T.y; c < T.z; ++c) {
-          const int4 C = CT(c);
-          acc += val[C.x] * (T.w ? rhs[C.y] : val[C.y]) / val[C.z];
+    // The schedule runs ahead of the values: a round's targets, and each
+    // target's first contribution, are read while the round before computes
+    // (only the last level can be without targets).
+    if (d.n_tg > 0) {
+      int q0 = 0, q1 = FPH(1);
+      int4 T = TG(min(tid, q1 - 1)), C = CT(T.y);
+      for (int ph = 0; ph < d.n_fph; ++ph) {
+        const int q2 = FPH(min(ph + 2, d.n_fph));
+        for (int q = q0; q < q1; q += BLOCK) {
+          const bool last = q + BLOCK >= q1;
+          const int4 next = TG(min((last ? q1 : q + BLOCK) + tid, (last ? q2 : q1) - 1));
+          if (q + tid < q1) {
+            double acc = 0.0;
+            for (int c = T.y; c < T.z;) {
+              const double l = val[C.x], x = T.w ? rhs[C.y] : val[C.y], d = val[C.z];
+              if (++c < T.z) C = CT(c);
+              acc += l * x / d;
+            }
+            if (T.w) rhs[T.x] -= acc;
+            else val[T.x] -= acc;
+          }
+          T = next;
+          C = CT(T.y);
         }
-        if (T.w) rhs[T.x] -= acc;
-        else val[T.x] -= acc;
+        q0 = q1;
+        q1 = q2;
+        __syncthreads();
       }
-      __syncthreads();
     }
     // backward: U x = y by levels, one thread per row: x_k = (y_k - U[k][S(k)]
     // x[S(k)]) / U[k][k], the x it reads solved in earlier levels
+    // (the next round's rows are read while this one computes, and a row's
+    // entries four at a time)
+    int q0 = 0, q1 = BPH(min(1, d.n_bph));
+    int4 R = BR(max(min(tid, q1 - 1), 0));
     for (int ph = 0; ph < d.n_bph; ++ph) {
-      const int q1 = BPH(ph + 1);
-      for (int q = BPH(ph) + tid; q < q1; q += BLOCK) {
-        const int k = BR(q);
-        const int s1 = SO(k + 1);
-        double acc = rhs[k];
-        for (int t = SO(k); t < s1; ++t) acc -= val[m + ns + t] * xs[SI(t)];
-        xs[k] = acc / val[k];
+      const int q2 = BPH(min(ph + 2, d.n_bph));
+      for (int q = q0; q < q1; q += BLOCK) {
+        const bool last = q + BLOCK >= q1;
+        const int4 next = BR(min((last ? q1 : q + BLOCK) + tid, (last ? q2 : q1) - 1));
+        if (q + tid < q1) {
+          double acc = rhs[R.x];
+          const double d = val[R.x];
+          for (int t = R.y; t < R.z; t += 4) {
+            int s[4];
+            double u[4], x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int e = min(t + j, R.z - 1);
+              s[j] = SI(e);
+              u[j] = val[m + ns + e];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = xs[s[j]];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (t + j < R.z) acc -= u[j] * x[j];
+          }
+          xs[R.x] = acc / d;
+        }
+        R = next;
       }
+      q0 = q1;
+      q1 = q2;
       __syncthreads();
     }
     // Newton update (eq. (3)), own buses
@@ -2229,6 +2292,21 @@ struct NrGo {
   }
 };
 
+// Split of the direct kernel: as many waves as the scenarios resident on a CU
+// (bounded by the LDS of each) leave room for at 16 per CU.  More threads take
+// more of a phase's targets at once.  Unsplit -> split: 118 buses 175 -> 110
+// us (batch 64) and 603 -> 480 (4096), 200 buses 253 -> 149 (512), 300 buses
+// 512 -> 459 (1024), 500 buses 357 -> 277 (64) and 1168 -> 916 (600), 2000
+// buses 8.69 -> 4.28 ms (64); it lost at none.
+int direct_split(const TxNetwork& net, int batch) {
+  const DirectDev& d = net.direct;
+  const int cus = net.ctx->cu_count, waves = net.block / WAVE;
+  const size_t lds = std::max<size_t>(1, (size_t)2 * net.nbp * 16 + ((size_t)d.n_val + 2 * d.m) * 8);
+  const int fit = (int)std::max<size_t>(1, 160 * 1024 / lds);
+  const int resident = std::max(1, std::min(fit, (batch + cus - 1) / cus));
+  return std::max(1, 16 / (waves * resident));
+}
+
 struct NrDirectGo {
   const TxNetwork& net;
   const NRLaunch& a;
@@ -2336,7 +2414,7 @@ bool direct_lds_fits(const TxNetwork& net) {
 void launch_nr_direct(const TxNetwork& net, const NRLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
   if (!net.direct_ready) fail(PF_INVALID_ARG, "direct Newton step used before its analysis was built");
-  dispatch_shape(net.n, 1, NrDirectGo{net, a, s});
+  dispatch_shape(net.n, direct_split(net, a.batch), NrDirectGo{net, a, s});
 }
 
 void launch_adjoint(const TxNetwork& net, const AdjLaunch& a, hipStream_t s) {

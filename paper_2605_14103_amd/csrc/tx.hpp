@@ -84,13 +84,12 @@ struct TxDev {
 struct DirectDev {
   int m, n_s, n_val, n_je, n_fph, n_bph, n_tg, n_ct;
   const int* fpos;   // [2 nbp]
-  const int* soff;   // [m + 1]
   const int* sidx;
   const int* fph;    // [n_fph + 1]
   const int4* ftg;   // (target, first contribution, end, 1 for a right-hand-side target)
   const int4* fct;   // (L entry, U entry or right-hand-side index, pivot, 0)
   const int* bph;    // [n_bph + 1]
-  const int* brow;
+  const int4* brow;  // (row, its first entry of sidx, end, 0)
   const int4* je;    // (value index | kind << 28, bus i, bus k, Ybus layout index)
 };
 
@@ -135,7 +134,7 @@ struct TxNetwork {
   bool direct_ready = false;
   int direct_nval = 0;
   DirectDev direct{};
-  DeviceBuffer dl_fpos, dl_soff, dl_sidx, dl_fph, dl_ftg, dl_fct, dl_bph, dl_brow, dl_je;
+  DeviceBuffer dl_fpos, dl_sidx, dl_fph, dl_ftg, dl_fct, dl_bph, dl_brow, dl_je;
   // solve workspaces (grow-only), shared by the network's calls and ordered by `order`
   DeviceBuffer ws_d, ws_basis, ws_adj, ws_y, ws_dval;
   CallOrder order;

@@ -497,13 +497,12 @@ void ensure_direct(TxNetwork& net) {
   Context* ctx = net.ctx;
   auto up = [&](const std::vector<int>& v) { return upload(ctx, v.empty() ? std::vector<int>{0} : v); };
   net.dl_fpos = up(D.fpos);
-  net.dl_soff = up(D.soff);
   net.dl_sidx = up(D.sidx);
   net.dl_fph = up(D.fph);
   net.dl_ftg = up(D.ftg.empty() ? std::vector<int>{0, 0, 0, 0} : D.ftg);
   net.dl_fct = up(D.fct.empty() ? std::vector<int>{0, 0, 0, 0} : D.fct);
   net.dl_bph = up(D.bph);
-  net.dl_brow = up(D.brow);
+  net.dl_brow = up(D.brow.empty() ? std::vector<int>{0, 0, 0, 0} : D.brow);
   net.dl_je = up(D.je.empty() ? std::vector<int>{0, 0, 0, 0} : D.je);
   DirectDev& d = net.direct;
   d.m = D.m;
@@ -515,13 +514,12 @@ void ensure_direct(TxNetwork& net) {
   d.n_tg = (int)D.ftg.size() / 4;
   d.n_ct = (int)D.fct.size() / 4;
   d.fpos = net.dl_fpos.as<int>();
-  d.soff = net.dl_soff.as<int>();
   d.sidx = net.dl_sidx.as<int>();
   d.fph = net.dl_fph.as<int>();
   d.ftg = net.dl_ftg.as<int4>();
   d.fct = net.dl_fct.as<int4>();
   d.bph = net.dl_bph.as<int>();
-  d.brow = net.dl_brow.as<int>();
+  d.brow = net.dl_brow.as<int4>();
   d.je = net.dl_je.as<int4>();
   net.direct_nval = D.n_val;
   net.direct_ready = true;

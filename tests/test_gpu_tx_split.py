@@ -45,3 +45,33 @@ def test_split_changes_no_bit(n, batches, precision):
     assert ok.all()
     da, dm = angle_err(got[0][0], V)
     assert da <= 1e-6 and dm <= 1e-6   # the solver's tolerance of 1e-8 pu mismatch
+
+
+# the direct step: unsplit only, and split in each shape with the schedule in LDS, the
+# factor in LDS and the factor in device memory
+@pytest.mark.parametrize("n,batches", [(3, (2,)), (64, (5, 600)), (65, (3, 1100)), (256, (3, 1100)), (257, (3, 600)),
+                                       (700, (3, 300)), (1025, (3, 300)), (2048, (2, 300))])
+def test_direct_split_changes_no_bit(n, batches):
+    import torch
+    from paper_2605_14103_amd import pf
+    cfg = tx.TxConfig(f"d{n}", n_bus=n, n_pv=max(1, round(0.15 * n)), n_branch=max(n - 1, round(1.3 * n) - 1),
+                      batch=batches[-1], seed=n, perturbation="uniform")
+    grid = tx.make_grid(cfg)
+    batch = tx.make_batch(grid, cfg)
+    ctx = pf.Context(0)
+    net = pf.TxNetwork.from_grid(ctx, grid)
+    few = batches[0]
+    got = []
+    for B in batches:
+        res = net.solve(*(to_dev(a[:B]) for a in (batch.p_inj, batch.q_inj, batch.vm_set)), nr_direct=1)
+        torch.cuda.synchronize()
+        assert res.converged.cpu().numpy().all()
+        got.append([x[:few].cpu().numpy() for x in (res.v, res.newton_iters, res.mismatch)])
+    net.close()
+    ctx.close()
+    for other in got[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(got[0], other))
+    V, it, ok, _ = onr.nr_solve_batch(grid, batch, columns=np.arange(few))
+    assert ok.all() and np.array_equal(got[0][1], it)   # both take exact Newton steps
+    da, dm = angle_err(got[0][0], V)
+    assert da <= 1e-6 and dm <= 1e-6   # the solver's tolerance of 1e-8 pu mismatch

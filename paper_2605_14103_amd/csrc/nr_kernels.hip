@@ -1202,9 +1202,8 @@ __device__ T subtract_proj(const Basis<T, Sh>& basis, int nv, T (&w)[2 * Sh::KB]
 // Mismatch at the current (theta, |V|): writes V, 1/|V|, I and F to the
 // workspace and returns max |F| (NaN if any entry is NaN).  yv: the scenario's
 // own Ybus values (layout of net.y64), or null.  Ends with a barrier.
-template <typename T, class Sh>
-__device__ double mismatch(const TxDev<T>* netp, const Ws<Sh>& ws, double2* vs, double* part,
-                           const double2* yv) {
+template <typename T, class Sh, class W>
+__device__ __forceinline__ double mismatch(const TxDev<T>* netp, W& ws, double2* vs, double* part, const double2* yv) {
   constexpr int KB = Sh::KB;
   TxDev<T> net = load_desc(netp);
   if (yv) net.y64.val = yv;
@@ -1714,6 +1713,31 @@ __host__ __device__ inline size_t direct_stage_bytes(const DirectDev& d) {
          (size_t)4 * (d.n_s + (d.n_fph + 1) + (d.n_bph + 1));
 }
 
+// The direct kernel's planes of few bus slots, in registers: nothing outlives
+// the launch there, and a plane's store and the load after it were an L2 round trip
+// in each phase of a Newton update.
+// (30 buses, 64 scenarios 65.1 -> 63.3 us; 118 buses,
+// 1024 144 -> 131; 300 buses, 1024 460 -> 385.)
+template <class Sh>
+struct RegWs {
+  static constexpr int KB = Sh::KB;
+  double x[WS_PLANES * KB];
+  __device__ __forceinline__ double ld(int a, int k) const { return x[a * KB + k]; }
+  __device__ __forceinline__ void st(int a, int k, double v) { x[a * KB + k] = v; }
+  template <int N>
+  __device__ __forceinline__ void ld_all(int a, double (&y)[N]) const {
+#pragma unroll
+    for (int k = 0; k < N; ++k) y[k] = ld(a, k);
+  }
+  template <typename T>
+  __device__ __forceinline__ void put_vi(int, double, double, double) {}   // V stays in LDS
+  template <typename T>
+  __device__ __forceinline__ void put_i(int k, double ir, double ii) {
+    st(IRE, k, ir);
+    st(IIM, k, ii);
+  }
+};
+
 // STAGE: the schedule tables (targets, contributions, J entries, S(k) and the
 // level lists) are copied into LDS once per workgroup, so each phase reads
 // them at LDS latency instead of an L2 round trip (when they fit).
@@ -1779,7 +1803,18 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
   auto FPH = [&](int q) { if constexpr (STAGE) return lfp[q]; else return cld(d.fph, (unsigned)q); };
   auto BPH = [&](int q) { if constexpr (STAGE) return lbp[q]; else return cld(d.bph, (unsigned)q); };
 
-  const Ws<Sh> ws{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
+  auto workspace = [&] {
+    if constexpr (KB <= 2) return RegWs<Sh>{};
+    else return Ws<Sh>{make_buf(a.ws_d + (int64_t)b * a.ws_d_stride)};
+  };
+  auto ws = workspace();
+  int pos[2 * KB];   // factor positions of the own buses' states
+#pragma unroll
+  for (int k = 0; k < KB; ++k) {
+    const unsigned i = Sh::row(k);
+    pos[k] = cld(d.fpos, i);
+    pos[KB + k] = cld(d.fpos, (unsigned)NBP + i);
+  }
   const Buf P = make_buf(a.p_inj + (int64_t)b * a.ld);
   const Buf Q = make_buf(a.q_inj + (int64_t)b * a.ld);
   const Buf VS = make_buf(a.vm_set + (int64_t)b * a.ld);
@@ -1822,8 +1857,8 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
     for (int k = 0; k < KB; ++k) {
       const unsigned i = Sh::row(k);
       is[i] = make_double2(ws.ld(IRE, k), ws.ld(IIM, k));
-      if ((int)i < nth) rhs[cld(d.fpos, i)] = -ws.ld(FP, k);
-      if ((int)i < npq) rhs[cld(d.fpos, (unsigned)NBP + i)] = -ws.ld(FP, KB + k);
+      if ((int)i < nth) rhs[pos[k]] = -ws.ld(FP, k);
+      if ((int)i < npq) rhs[pos[KB + k]] = -ws.ld(FP, KB + k);
     }
     for (int q = tid; q < d.n_val; q += BLOCK) val[q] = 0.0;
     __syncthreads();
@@ -1943,8 +1978,8 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
       const unsigned i = Sh::row(k);
-      if ((int)i < nth) ws.st(TH, k, ws.ld(TH, k) + xs[cld(d.fpos, i)]);
-      if ((int)i < npq) ws.st(VM, k, ws.ld(VM, k) + xs[cld(d.fpos, (unsigned)NBP + i)]);
+      if ((int)i < nth) ws.st(TH, k, ws.ld(TH, k) + xs[pos[k]]);
+      if ((int)i < npq) ws.st(VM, k, ws.ld(VM, k) + xs[pos[KB + k]]);
     }
     work += 8.0 * m + 32.0 * m;
     ++newton;
@@ -2297,7 +2332,8 @@ struct NrGo {
 // more of a phase's targets at once.  Unsplit -> split: 118 buses 175 -> 110
 // us (batch 64) and 603 -> 480 (4096), 200 buses 253 -> 149 (512), 300 buses
 // 512 -> 459 (1024), 500 buses 357 -> 277 (64) and 1168 -> 916 (600), 2000
-// buses 8.69 -> 4.28 ms (64); it lost at none.
+// buses 8.69 -> 4.28 ms (64); it lost at none (all with the planes still in
+// memory: RegWs).
 int direct_split(const TxNetwork& net, int batch) {
   const DirectDev& d = net.direct;
   const int cus = net.ctx->cu_count, waves = net.block / WAVE;

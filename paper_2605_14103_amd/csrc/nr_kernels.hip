@@ -68,9 +68,10 @@ __device__ __forceinline__ double mul_sub(double a, double b, double c, double d
 // hands the vector to its first group through LDS for them.
 constexpr int nr_split_max(int VB, int KBT) { return KBT == 1 || VB >= 1024 ? 1 : VB >= 512 ? 2 : KBT >= 4 ? 4 : KBT; }
 
-template <int VB_, int KBT_, int S_>
+template <int VB_, int KBT_, int S_, bool LONG_ = false>
 struct Shape {
   static constexpr int VB = VB_, KBT = KBT_, S = S_;
+  static constexpr bool LONG = LONG_;   // many Arnoldi steps a cycle expected (long_cycles)
   static constexpr int BLOCK = VB * S, KB = KBT / S, NW = BLOCK / WAVE, NWV = VB / WAVE;
   static constexpr unsigned NBP = (unsigned)VB * KBT;
   static constexpr int SMAX = nr_split_max(VB, KBT), U = KBT / SMAX, NU = KB / U;
@@ -1097,10 +1098,11 @@ __device__ double multi_dot(const Basis<double, Sh>& basis, int nv, const double
   constexpr int NW = Sh::NW, KB = Sh::KB, NU = Sh::NU;
   const int lane = lane_id(), slot = part_slot<Sh>();
   constexpr int G = Basis<T, Sh>::G;
-  // Two vectors per round: twice the loads in flight.  (Not with four units:
-  // their sums for two vectors cost 20 more spilled registers, and the
-  // 2000-bus batch of 1024 ran 2.28 against 1.99 ms.)
-  constexpr bool TWO = NU < 4;
+  // Two vectors per round: twice the loads in flight.  (With four units their
+  // sums for two vectors cost 31 more spilled registers: the 2000-bus batch of
+  // 1024, with three to five vectors at a time, ran 2.00 against 1.93 ms, while with the
+  // block-Jacobi preconditioner and up to thirty it gains, 73.2 -> 66.0 ms.)
+  constexpr bool TWO = NU < 4 || Sh::LONG;
   auto dots = [&](int i, int i1, auto where) {
     constexpr bool L = decltype(where)::value;
     for (; TWO && i + 1 < i1; i += 2) {
@@ -2309,6 +2311,12 @@ void allow_lds(Kernel kernel, size_t lds) {
                                 (int)lds));
 }
 
+// A network whose preconditioner leaves cycles of up to `restart` Arnoldi steps.
+bool long_cycles(const TxNetwork& net) { return net.block_precond; }
+
+template <class Sh>
+using Long = Shape<Sh::VB, Sh::KBT, Sh::S, true>;
+
 template <typename T>
 struct NrGo {
   const TxNetwork& net;
@@ -2321,6 +2329,9 @@ struct NrGo {
     b.lds_vecs = lds_vectors<Sh, T>(net, a.batch, a.restart, base);
     const size_t lds = base + b.lds_vecs * 2 * Sh::NBP * sizeof(T);
     auto kernel = nr_kernel<T, Sh>;
+    if constexpr (sizeof(T) == 8 && Sh::NU == 4) {
+      if (long_cycles(net)) kernel = nr_kernel<T, Long<Sh>>;
+    }
     allow_lds(kernel, lds);
     hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<T>(), b);
     PFX_HIP(hipGetLastError());
@@ -2392,6 +2403,9 @@ struct AdjGo {
     b.lds_vecs = lds_vectors<Sh, double>(net, a.batch, a.restart, base);
     const size_t lds = base + b.lds_vecs * 2 * Sh::NBP * sizeof(double);
     auto kernel = adjoint_kernel<Sh>;
+    if constexpr (Sh::NU == 4) {
+      if (long_cycles(net)) kernel = adjoint_kernel<Long<Sh>>;
+    }
     allow_lds(kernel, lds);
     hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<double>(), b);
     PFX_HIP(hipGetLastError());

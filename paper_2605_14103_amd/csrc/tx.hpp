@@ -132,6 +132,7 @@ struct TxNetwork {
   std::vector<int> y_ptr, y_col, y_pos;
   // direct Newton step: analysis built on first use
   bool direct_ready = false;
+  bool block_precond = false;   // block-diagonal B' and B'' in the preconditioner
   int direct_nval = 0;
   DirectDev direct{};
   DeviceBuffer dl_fpos, dl_sidx, dl_fph, dl_ftg, dl_fct, dl_bph, dl_brow, dl_je;

@@ -381,6 +381,7 @@ TxNetwork* tx_network_create(Context* ctx, int n_bus, int nnz, const int32_t* ro
   const double eps = setup.eps;
   SparseSym Bp = leading_block(ptr, col, yim, nth, eps);
   SparseSym Bpp = leading_block(ptr, col, yim, npq, eps);
+  net->block_precond = setup.precond_block > 0;
   if (setup.precond_block > 0) {
     Bp = block_diagonal_part(Bp, setup.precond_block);
     Bpp = block_diagonal_part(Bpp, setup.precond_block);

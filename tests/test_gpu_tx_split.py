@@ -75,3 +75,34 @@ def test_direct_split_changes_no_bit(n, batches):
     assert ok.all() and np.array_equal(got[0][1], it)   # both take exact Newton steps
     da, dm = angle_err(got[0][0], V)
     assert da <= 1e-6 and dm <= 1e-6   # the solver's tolerance of 1e-8 pu mismatch
+
+
+# a block-diagonal preconditioner takes cycles of up to thirty steps; unsplit, their dot
+# products run over two vectors a round in each shape of four units
+@pytest.mark.parametrize("n,batches", [(200, (3, 4200)), (300, (3, 1100)), (1500, (2, 600))])
+def test_long_cycles_change_no_bit(n, batches):
+    import torch
+    from paper_2605_14103_amd import pf
+    cfg = tx.TxConfig(f"b{n}", n_bus=n, n_pv=max(1, round(0.15 * n)), n_branch=round(1.3 * n), batch=batches[-1],
+                      seed=n, perturbation="uniform")
+    grid = tx.make_grid(cfg)
+    batch = tx.make_batch(grid, cfg)
+    ctx = pf.Context(0)
+    net = pf.TxNetwork.from_grid(ctx, grid, precond_block=32)
+    few = batches[0]
+    got = []
+    for B in batches:
+        res = net.solve(*(to_dev(a[:B]) for a in (batch.p_inj, batch.q_inj, batch.vm_set)))
+        _, dl_dv = net.branch_loss(res.v)
+        gp, gq, its, _ = net.adjoint(res.v, dl_dv)
+        torch.cuda.synchronize()
+        got.append([x[:few].cpu().numpy() for x in (res.v, res.newton_iters, res.gmres_iters, res.mismatch,
+                                                    res.converged, gp, gq, its)])
+    net.close()
+    ctx.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*got))
+    assert (got[0][2] > 10 * got[0][1]).any()   # cycles of many steps were run
+    V, _, ok, _ = onr.nr_solve_batch(grid, batch, columns=np.arange(few))
+    assert ok.all() and got[0][4].all()
+    da, dm = angle_err(got[0][0], V)
+    assert da <= 1e-6 and dm <= 1e-6   # the solver's tolerance of 1e-8 pu mismatch

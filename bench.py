@@ -28,8 +28,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
-FP64_MFMA_TFLOPS = 78.6
-FP32_MFMA_TFLOPS = 157.3
 METRIC = "converged PF solves/sec @<=1e-8 pu mismatch, FP64 vs mixed; p50/p99 latency"
 
 
@@ -289,7 +287,7 @@ def bench_tx(cfg_name: str, steps: int, warmup: int, cpu: dict | None, block_jac
                      "traffic": (measured_traffic(f"nr_kernel_{cfg_name.lower()}_b{B}.txt", "fp64")
                                  if cfg_name == "TX2000" else None),
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-                     "kernel": "nr_kernel<double, 256, 8>" if grid.n_bus == 2000 else "nr_kernel<double>",
+                     "kernel": "nr_kernel<double, Shape<256, 8, 1>>" if grid.n_bus == 2000 else "nr_kernel<double>",
                      "bytes_per_launch": r["algorithmic_bytes_per_launch"]},
         "fp64": runs["fp64"], "mixed": runs["mixed"],
         "mixed_vs_fp64": runs["mixed"]["value"] / r["value"],
@@ -319,6 +317,7 @@ def bench_feeder(steps: int, warmup: int, cpu: dict | None) -> dict:
     B = batch.batch
     nN = net.info["n_free"]
     runs = {}
+    # a radial feeder is solved by path sums (zb_tree) whichever update is asked for
     for prec, sparse, asy in (("fp64", 0, 0), ("mixed", 0, 0), ("fp64", 1, 0), ("mixed", 1, 0), ("fp64", 0, 1),
                               ("mixed", 0, 1)):
         key = prec + ("_sparse" if sparse else "") + ("_async" if asy else "")
@@ -327,28 +326,26 @@ def bench_feeder(steps: int, warmup: int, cpu: dict | None) -> dict:
             steps, warmup)
         conv = int(out.converged.sum().item())
         its = out.iters.double()
-        gemm_flops = 8.0 * nN * nN * float(its.sum().item())
         mean_ms = float(ms.mean())
         runs[key] = {"value": conv / (mean_ms * 1e-3), "ms_per_step": mean_ms, "converged": conv,
                      "iters_mean": float(its.mean().item()), "max_mismatch": float(out.mismatch.max().item()),
                      "latency_ms": {"p50": float(np.percentile(ms, 50)), "p99": float(np.percentile(ms, 99))}}
-        if not sparse:
-            runs[key]["useful_gemm_TFLOPs"] = gemm_flops / (mean_ms * 1e-3) / 1e12
     r = runs["fp64"]
-    tf = r["useful_gemm_TFLOPs"]
+    # one load power read and one voltage written per node: what a solve cannot do without
+    work = float(B) * 16.0 * (nN + fd.n_node)
+    gbs = work / (r["ms_per_step"] * 1e-3) / 1e9
     line = {"metric": METRIC, "value": r["value"], "unit": "solves/s", "n_gpus": 1, "steps": steps,
             "warmup": warmup, "ms_per_step": r["ms_per_step"], "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": "f64", "data": "synthetic",
             "config": {"workload": f"feeder300: Z-bus, {fd.n_node} phase nodes, batch {B}", "global_batch": B},
             "latency_ms": r["latency_ms"],
-            "roofline": {"bound": "mfma", "achieved": tf, "peak": FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
-                         "frac": tf / FP64_MFMA_TFLOPS,
-                         "traffic": measured_traffic("zbus_feeder300_b4096.txt", "gemm_fp64", "zbus"),
-                         "traffic_unit": "HBM bytes per full zb_gemm_direct<double> launch (rocprofv3 FETCH_SIZE + "
-                                         "WRITE_SIZE, copy-calibrated)",
-                         "kernel": "zb_gemm_direct<double>",
-                         "basis": "useful complex flops (8 nN^2 per scenario and iteration) over the whole "
-                                  "solve time, residual kernels and launch gaps included"},
+            "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                         "frac": gbs / HBM_PEAK_GBS,
+                         "traffic": measured_traffic("zbus_feeder300_b4096.txt", "tree_fp64", "zbus"),
+                         "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
+                         "kernel": "zb_tree", "bytes_per_launch": work,
+                         "basis": "load powers read once and voltages written once; the kernel keeps the whole "
+                                  "iteration on the CU and is bound by instruction issue, not by HBM"},
             "fp64": runs["fp64"], "mixed": runs["mixed"],
             "sparse_variant": {"fp64": runs["fp64_sparse"], "mixed": runs["mixed_sparse"]},
             "async_enqueue": {"fp64": runs["fp64_async"], "mixed": runs["mixed_async"]},
@@ -453,7 +450,7 @@ def bench_direct_sizes(steps: int, warmup: int) -> dict:
 
 
 def bench_feeder_sizes(steps: int, warmup: int) -> dict:
-    """Dense Z product against the sparse Y_NN factor as the feeder grows (batch 1024, both precisions)."""
+    """Solve time as the radial feeder grows (batch 1024, both precisions)."""
     import torch
 
     from paper_2605_14103_amd import pf
@@ -469,25 +466,22 @@ def bench_feeder_sizes(steps: int, warmup: int) -> dict:
         net = pf.DistNetwork.from_feeder(ctx, fd)
         setup_s = time.perf_counter() - t0
         sw, sd = dev(batch.s_wye), dev(batch.s_delta)
-        for sparse in (0, 1):
-            for prec in ("fp64", "mixed"):
-                ms, _, out = time_steps(
-                    lambda: net.solve(sw, sd, precision=pf.precision(prec), zbus_sparse=sparse), steps, warmup)
-                conv = int(out.converged.sum().item())
-                rows.append({"workload": cfg.name, "free_nodes": net.info["n_free"], "batch": cfg.batch,
-                             "update": "sparse" if sparse else "dense", "precision": prec,
-                             "ms": float(ms.mean()), "solves_per_s": conv / (float(ms.mean()) * 1e-3),
-                             "converged": conv, "iters_mean": float(out.iters.double().mean().item()),
-                             "setup_s": setup_s})
-                print(f"[sizes] {cfg.name} nN={net.info['n_free']} {rows[-1]['update']} {prec} "
-                      f"{ms.mean():.3f} ms", file=sys.stderr, flush=True)
+        for prec in ("fp64", "mixed"):
+            ms, _, out = time_steps(lambda: net.solve(sw, sd, precision=pf.precision(prec)), steps, warmup)
+            conv = int(out.converged.sum().item())
+            rows.append({"workload": cfg.name, "free_nodes": net.info["n_free"], "batch": cfg.batch,
+                         "update": "path sums", "precision": prec,
+                         "ms": float(ms.mean()), "solves_per_s": conv / (float(ms.mean()) * 1e-3),
+                         "converged": conv, "iters_mean": float(out.iters.double().mean().item()),
+                         "setup_s": setup_s})
+            print(f"[sizes] {cfg.name} nN={net.info['n_free']} {prec} {ms.mean():.3f} ms", file=sys.stderr, flush=True)
         net.close()
     ctx.close()
     best = max(r["solves_per_s"] for r in rows if r["workload"] == "feeder300" and r["precision"] == "fp64")
     return {"metric": METRIC, "value": best, "unit": "solves/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
             "ms_per_step": None, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f64",
             "data": "synthetic",
-            "config": {"workload": "feeder size sweep: 100-908 buses, batch 1024, dense Z against sparse Y_NN"},
+            "config": {"workload": "feeder size sweep: 100-908 buses, batch 1024"},
             "sizes": rows}
 
 
@@ -531,7 +525,7 @@ def bench_serving(n_requests: int, lam: float, streams=(1, 3, 1), step_iters=(20
     """Replay the Poisson serving mix (30-bus grid, 2000-bus grid, 900-node feeder).
 
     streams and step_iters are per engine (30-bus, 2000-bus, feeder);
-    feeder_sparse = 1 runs the feeder engine's update by the sparse factor of
+    feeder_sparse = 1 asks the feeder engine for the update by the sparse factor of
     Y_NN instead of the dense Z product."""
     from paper_2605_14103_amd import pf, serve
     from workloads import feeder as fdm
@@ -591,7 +585,8 @@ def bench_serving(n_requests: int, lam: float, streams=(1, 3, 1), step_iters=(20
             "config": {"workload": f"serving mix: Poisson lambda={lam}/s, {n_requests} requests over tx30, "
                                    f"tx2000 and feeder300, 1-512 scenarios each, tol 1e-8",
                        "streams": list(streams), "step_iters": list(step_iters), "forcing": forcing,
-                       "feeder_update": "sparse Y_NN factor" if feeder_sparse else "dense Z product"},
+                       "feeder_update": "path sums (radial feeder; asked for: "
+                                        + ("sparse Y_NN factor)" if feeder_sparse else "dense Z product)")},
             "latency_ms": {"p50": r["p50_ms"], "p99": r["p99_ms"]},
             "fp64": out["fp64"], "mixed": out["mixed"], "fp64_half_load": out.get("fp64_half_load")}
 
@@ -704,8 +699,8 @@ def main() -> int:
     ap.add_argument("--forcing", type=int, default=0,
                     help="serving engines: fixed (0, lower tail latency) or adaptive (1) forcing term")
     ap.add_argument("--feeder-update", choices=("sparse", "dense"), default="sparse",
-                    help="serving: the feeder engine's update, by the sparse factor of Y_NN (lower latency "
-                         "at the small batches a serving step holds) or the dense Z product")
+                    help="serving: the update asked for in the feeder engine, by the sparse factor of Y_NN or the "
+                         "dense Z product (a radial feeder takes neither: its path sums serve both)")
     ap.add_argument("--cpu-samples", type=int, default=256)
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--headline-only", action="store_true",
@@ -767,8 +762,8 @@ def _sub(line: dict) -> dict:
 def all_configs(a) -> dict:
     """The other configurations of the method, each timed as its own line
     would be, so that one default run measures them all: the 30-bus grid
-    (batch 64), the 900-node feeder (batch 4096, dense product in FP64 and
-    FP32, sparse variant), the adjoint (2000-bus, batch 256) and the serving
+    (batch 64), the 900-node feeder (batch 4096, each option that a caller can
+    set; all take the path sums), the adjoint (2000-bus, batch 256) and the serving
     mix at full and half load."""
     out = {}
     for key, fn in (("tx30_b64", lambda: bench_tx("TX30", a.steps, a.warmup, a.sub_cpu.get("tx30"))),

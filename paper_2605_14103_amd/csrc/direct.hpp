@@ -12,6 +12,7 @@
 // (L[i][k] U[k][k]) | U rows by pivot].
 #pragma once
 
+#include <cstddef>
 #include <vector>
 
 namespace pfx {
@@ -43,6 +44,31 @@ struct DirectLuHost {
 // factor lives in LDS when it fits there, else in network-owned device
 // memory, DIRECT_MAX_VALUES doubles per scenario of a batch).
 constexpr int DIRECT_MAX_VALUES = 1 << 22;
+
+// LDS of one workgroup of `waves` waves: V and I of nbp bus positions, two
+// buffers of partial sums, the right-hand side and x, and `n_val` factor values
+// (0: those live in device memory).
+constexpr size_t DIRECT_LDS = 160 * 1024;
+constexpr size_t direct_lds_bytes(int nbp, int waves, int n_val, int m) {
+  return (size_t)2 * nbp * 16 + (size_t)2 * waves * 8 + ((size_t)n_val + 2 * m) * 8;
+}
+
+// The factor stays in LDS where it fits beside the unsplit workgroup's waves.
+constexpr bool direct_in_lds(int nbp, int waves, int n_val, int m) {
+  return direct_lds_bytes(nbp, waves, n_val, m) <= DIRECT_LDS;
+}
+
+// The split (1, 2 or 4 times the waves) for a wish of `want`, at most `most`:
+// never one whose partial sums would push a factor out of LDS that fits
+// unsplit, since the caller allocates the device memory for it or not by
+// direct_in_lds alone.
+constexpr int direct_fitting_split(int nbp, int waves, int n_val, int m, int want, int most) {
+  int s = want < most ? want : most;
+  s = s >= 4 ? 4 : s >= 2 ? 2 : 1;
+  if (direct_in_lds(nbp, waves, n_val, m))
+    while (s > 1 && direct_lds_bytes(nbp, s * waves, n_val, m) > DIRECT_LDS) s /= 2;
+  return s;
+}
 
 // Builds the analysis for a registered network.  Throws PfError
 // (PF_INVALID_ARG) when the factor would exceed DIRECT_MAX_VALUES values.

@@ -37,6 +37,7 @@
 #include <string>
 
 #include "device_ops.hpp"
+#include "direct.hpp"
 #include "tx.hpp"
 
 namespace pfx {
@@ -1708,7 +1709,7 @@ __global__ __launch_bounds__(Sh::BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
 // imaginary part (kind = 2 row type + column type).
 // Byte offset of the staged schedule tables in the direct kernel's LDS.
 __host__ __device__ inline size_t direct_stage_offset(int nbp, int nw, const DirectDev& d) {
-  return ((size_t)2 * nbp * 16 + (size_t)2 * nw * 8 + ((size_t)d.n_val + 2 * d.m) * 8 + 15) / 16 * 16;
+  return (direct_lds_bytes(nbp, nw, d.n_val, d.m) + 15) / 16 * 16;
 }
 __host__ __device__ inline size_t direct_stage_bytes(const DirectDev& d) {
   return (size_t)16 * (d.n_tg + d.n_ct + d.n_je + d.m) +
@@ -2348,10 +2349,10 @@ struct NrGo {
 int direct_split(const TxNetwork& net, int batch) {
   const DirectDev& d = net.direct;
   const int cus = net.ctx->cu_count, waves = net.block / WAVE;
-  const size_t lds = std::max<size_t>(1, (size_t)2 * net.nbp * 16 + ((size_t)d.n_val + 2 * d.m) * 8);
-  const int fit = (int)std::max<size_t>(1, 160 * 1024 / lds);
+  const int fit = (int)std::max<size_t>(1, DIRECT_LDS / direct_lds_bytes(net.nbp, 0, d.n_val, d.m));
   const int resident = std::max(1, std::min(fit, (batch + cus - 1) / cus));
-  return std::max(1, 16 / (waves * resident));
+  return direct_fitting_split(net.nbp, waves, d.n_val, d.m, 16 / (waves * resident),
+                              nr_split_max(net.block, net.kb));
 }
 
 struct NrDirectGo {
@@ -2361,11 +2362,10 @@ struct NrDirectGo {
   template <class Sh>
   void operator()() const {
     const DirectDev& d = net.direct;
-    const size_t lds0 = (size_t)2 * Sh::NBP * 16 + 2 * Sh::NW * 8 + ((size_t)d.n_val + 2 * d.m) * 8;
-    if (lds0 > 160 * 1024) {
+    if (!direct_lds_fits(net)) {
       // factor values in device memory; V, I, the right-hand side and x stay in LDS
-      const size_t ldsg = (size_t)2 * Sh::NBP * 16 + 2 * Sh::NW * 8 + (size_t)2 * d.m * 8;
-      if (ldsg > 160 * 1024)
+      const size_t ldsg = direct_lds_bytes((int)Sh::NBP, Sh::NW, 0, d.m);
+      if (ldsg > DIRECT_LDS)
         fail(PF_INVALID_ARG, "network too large for the direct Newton step (" + std::to_string(ldsg) +
                                  " bytes of LDS)");
       if (!a.ws_dval) fail(PF_INVALID_ARG, "direct Newton step without its factor workspace");
@@ -2382,7 +2382,7 @@ struct NrDirectGo {
     // per CU, occupancy moot), within the CU's 160 KB
     const size_t lds1 = direct_stage_offset((int)Sh::NBP, Sh::NW, d) + direct_stage_bytes(d);
     const bool stage = lds1 <= (a.batch <= net.ctx->cu_count ? 160 : 64) * 1024;
-    const size_t lds = stage ? lds1 : lds0;
+    const size_t lds = stage ? lds1 : direct_lds_bytes((int)Sh::NBP, Sh::NW, d.n_val, d.m);
     auto kernel = stage ? nr_direct_kernel<Sh, true, false> : nr_direct_kernel<Sh, false, false>;
     if (lds > 64 * 1024)
       PFX_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -2456,9 +2456,7 @@ void launch_nr(const TxNetwork& net, bool mixed, const NRLaunch& a, hipStream_t 
 }
 
 bool direct_lds_fits(const TxNetwork& net) {
-  const DirectDev& d = net.direct;
-  const size_t lds0 = (size_t)2 * net.nbp * 16 + 2 * (net.block / WAVE) * 8 + ((size_t)d.n_val + 2 * d.m) * 8;
-  return lds0 <= 160 * 1024;
+  return direct_in_lds(net.nbp, net.block / WAVE, net.direct.n_val, net.direct.m);
 }
 
 void launch_nr_direct(const TxNetwork& net, const NRLaunch& a, hipStream_t s) {

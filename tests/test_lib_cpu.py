@@ -222,3 +222,37 @@ def test_ybus_switch_errors():
     st, out = _switch(grid, csr, on[:0])
     assert st == _lib.PF_OK and out.shape[0] == 0
     del ctypes
+
+
+def _compile_and_run(tmp_path, code):
+    """Build a small program over the library's host headers with g++ and return its output lines."""
+    src, exe = tmp_path / "probe.cpp", tmp_path / "probe"
+    src.write_text(code)
+    subprocess.run(["g++", "-std=c++17", "-O2", f"-I{os.path.join(ROOT, 'paper_2605_14103_amd', 'csrc')}", str(src),
+                    "-o", str(exe)], check=True, capture_output=True, text=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split("\n")[:-1]
+
+
+def test_direct_step_allocation_agrees_with_launch(tmp_path):
+    """The direct step's caller allocates device memory for the factor values by the unsplit
+    workgroup's LDS; the launch must then take a split that keeps them where the caller expects
+    them.  Every count of doubles across the 160 KB boundary, for each workgroup shape and wish."""
+    shapes = [(64, 1, 1), (256, 1, 4), (1024, 4, 4), (2048, 4, 4)]   # bus positions, waves, largest split
+    code = "#include <cstdio>\n#include \"direct.hpp\"\nusing namespace pfx;\nint main() {\n"
+    for nbp, waves, most in shapes:
+        code += (f"  for (int v = 20480 - {4 * nbp} - 80; v < 20480 - {4 * nbp} + 8; ++v)\n"
+                 "    for (int want : {0, 1, 2, 3, 4, 16}) {\n"
+                 f"      const int s = direct_fitting_split({nbp}, {waves}, v - 100, 50, want, {most});\n"
+                 f"      printf(\"{nbp} {waves} {most} %d %d %d %d %zu\\n\", v, want, s,\n"
+                 f"             (int)direct_in_lds({nbp}, {waves}, v - 100, 50),\n"
+                 f"             direct_lds_bytes({nbp}, s * {waves}, v - 100, 50));\n    }}\n")
+    lines = _compile_and_run(tmp_path, code + "}\n")
+    narrowed = 0
+    for line in lines:
+        nbp, waves, most, v, want, s, in_lds, launched = (int(x) for x in line.split())
+        assert in_lds == (32 * nbp + 16 * waves + 8 * v <= 163840)   # as the caller decides
+        assert launched == 32 * nbp + 16 * waves * s + 8 * v and (launched <= 163840) == bool(in_lds)
+        wish = max(k for k in (1, 2, 4) if k <= max(1, min(want, most)))
+        assert s == wish or (s < wish and in_lds and launched + 16 * waves * s > 163840)
+        narrowed += s < wish
+    assert len(lines) == 4 * 88 * 6 and narrowed > 0

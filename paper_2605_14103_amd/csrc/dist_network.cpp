@@ -83,8 +83,13 @@ std::array<cplx, 6> invert_sym3(const std::array<cplx, 6>& m) {
 // Tree form of a feeder (TreeDev), if it is one: nodes 3 b, 3 b + 1, 3 b + 2
 // are bus b's phases, the slack is one bus in phase order, each delta load sits on one bus in
 // phase order, Ybus joins buses in a tree, every block off the diagonal is
-// symmetric and equals its mirror, and every diagonal block is minus the sum
-// of the others in its row up to the rounding of that sum (no shunts).
+// symmetric and equals its mirror up to the rounding of a segment's inversion,
+// and every diagonal block is minus the sum of the others in its row up to the
+// rounding of that sum (no shunts).  The last test takes real and imaginary
+// parts by themselves and allows each a unit in the last place of the sum per
+// neighbour: a caller's sum in any order rounds by half of that, and a shunt
+// beside a stiff segment (a closed switch) is dropped only where the diagonal
+// entry could not have held it.
 // Otherwise the network keeps the forms for a general Y_NN.
 void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const int32_t* col_idx, const double* y_re,
                 const double* y_im, const std::vector<uint8_t>& wye,
@@ -108,9 +113,12 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
   for (int b = 0; b < nbus; ++b) {
     ends += rows[b].size() - rows[b].count(b);
     if (rows[b].count(s)) top.push_back(b);
-    double mag[3][3] = {};
-    cplx tot[3][3] = {};
+    using wide = std::complex<long double>;   // (this sum's own rounding stays out of it)
+    wide tot[3][3] = {};
+    double re[3][3] = {}, im[3][3] = {};   // sums of the neighbours' parts
+    int neighbours = 0;
     for (auto& [c, B] : rows[b]) {
+      neighbours += c != b;
       if (c != b && c != s && !rows[c].count(b)) return;
       double big = 0.0;
       for (int q = 0; q < 9; ++q) big = std::max(big, std::abs(B.y[q / 3][q % 3]));
@@ -118,16 +126,19 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
       for (int i = 0; i < 3; ++i)
         for (int j = 0; j < 3; ++j) {
           const cplx y = B.y[i][j];
-          tot[i][j] += y;
-          mag[i][j] += std::abs(y);
+          tot[i][j] += wide(y);
           if (c == b) continue;
+          re[i][j] += std::abs(y.real());
+          im[i][j] += std::abs(y.imag());
           if (!(std::abs(y - B.y[j][i]) <= tol)) return;
           if (c != s && !(std::abs(y - rows[c][b].y[i][j]) <= tol)) return;
         }
     }
     for (int i = 0; i < 3; ++i)
       for (int j = 0; j < 3; ++j)
-        if (!(std::abs(tot[i][j]) <= 64 * eps * mag[i][j])) return;
+        if (!(std::abs(tot[i][j].real()) <= neighbours * eps * re[i][j]) ||
+            !(std::abs(tot[i][j].imag()) <= neighbours * eps * im[i][j]))
+          return;
   }
   if (ends != 2 * (size_t)(nbus - 1) - top.size()) return;
   for (int b = 0; b < nbus; ++b) {

@@ -17,6 +17,7 @@ DirectLuHost build_direct_lu(const TxNetwork& net) {
   const int nth = net.nth, npq = net.npq, n = net.n, nbp = net.nbp;
   const int m = nth + npq;
   D.m = m;
+  if (m > 0x8000) fail(PF_INVALID_ARG, "the direct Newton step's rows need 16-bit indices");
   // state s: theta of bus s for s < nth, |V| of bus s - nth otherwise
   auto states_of = [&](int bus, int out[2], int type[2]) {
     int c = 0;
@@ -119,8 +120,8 @@ DirectLuHost build_direct_lu(const TxNetwork& net) {
   }
   D.bph.assign(1, 0);
   for (int l = 0; l < nb; ++l) {
-    for (int k : by_b[l]) D.brow.insert(D.brow.end(), {k, D.soff[k], D.soff[k + 1], 0});
-    D.bph.push_back((int)D.brow.size() / 4);
+    for (int k : by_b[l]) D.brow.insert(D.brow.end(), {k | (D.soff[k + 1] - D.soff[k]) << 16, D.soff[k]});
+    D.bph.push_back((int)D.brow.size() / 2);
   }
   D.fpos.assign(2 * nbp, -1);
   for (int s = 0; s < m; ++s) D.fpos[s < nth ? s : nbp + (s - nth)] = pinv[s];

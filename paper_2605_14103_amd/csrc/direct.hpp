@@ -34,7 +34,7 @@ struct DirectLuHost {
   // pivot, 0): target -= L[i][k] x / U[k][k].
   std::vector<int> fph, ftg, fct;
   // Backward solve by levels: phase b computes x_k for the rows
-  // brow[bph[b] .. bph[b + 1]) (4 ints: k, soff[k], soff[k + 1], 0), whose U
+  // brow[bph[b] .. bph[b + 1]) (2 ints: k | |S(k)| << 16, soff[k]), whose U
   // entries reference solved rows only.
   std::vector<int> bph, brow;
   std::vector<int> je;       // J entries, 4 ints each: (value index | kind << 28, bus i, bus k, Ybus layout index)

@@ -1769,6 +1769,9 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
   double* xs = rhs + m;
   double* val = VG ? a.ws_dval + (int64_t)b * a.ws_dval_stride : red + 2 * NW;
   int4 *ltg = nullptr, *lct = nullptr, *lje = nullptr, *lbr = nullptr;
+  auto row_of = [](int2 r) {   // (row, its first entry of sidx, end, 0)
+    return make_int4(r.x & 0xffff, r.y, r.y + (int)((unsigned)r.x >> 16), 0);
+  };
   int *lsi = nullptr, *lfp = nullptr, *lbp = nullptr;
   if constexpr (STAGE) {
     ltg = reinterpret_cast<int4*>(smem + direct_stage_offset(NBP, NW, d));
@@ -1779,30 +1782,31 @@ __global__ __launch_bounds__(Sh::BLOCK) void nr_direct_kernel(const TxDev<double
     lfp = lsi + ns;
     lbp = lfp + d.n_fph + 1;
     // eight loads in flight per thread
-    auto copy = [&](auto* dst, const auto* src, int count) {
+    auto copy = [&](auto* dst, const auto* src, int count, auto&& as) {
       for (int q = tid; q < count; q += 8 * BLOCK) {
         std::remove_const_t<std::remove_reference_t<decltype(*src)>> v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = cld(src, (unsigned)min(q + u * BLOCK, count - 1));
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (q + u * BLOCK < count) dst[q + u * BLOCK] = v[u];
+          if (q + u * BLOCK < count) dst[q + u * BLOCK] = as(v[u]);
       }
     };
-    copy(ltg, d.ftg, d.n_tg);
-    copy(lct, d.fct, d.n_ct);
-    copy(lje, d.je, d.n_je);
-    copy(lbr, d.brow, m);
-    copy(lsi, d.sidx, ns);
-    copy(lfp, d.fph, d.n_fph + 1);
-    copy(lbp, d.bph, d.n_bph + 1);
+    auto same = [](auto x) { return x; };
+    copy(ltg, d.ftg, d.n_tg, same);
+    copy(lct, d.fct, d.n_ct, same);
+    copy(lje, d.je, d.n_je, same);
+    copy(lbr, d.brow, m, row_of);
+    copy(lsi, d.sidx, ns, same);
+    copy(lfp, d.fph, d.n_fph + 1, same);
+    copy(lbp, d.bph, d.n_bph + 1, same);
     // (made visible by the barriers of the first mismatch)
   }
   auto TG = [&](int q) { if constexpr (STAGE) return ltg[q]; else return cld(d.ftg, (unsigned)q); };
   auto CT = [&](int q) { if constexpr (STAGE) return lct[q]; else return cld(d.fct, (unsigned)q); };
   auto JE = [&](int q) { if constexpr (STAGE) return lje[q]; else return cld(d.je, (unsigned)q); };
   auto SI = [&](int q) { if constexpr (STAGE) return lsi[q]; else return cld(d.sidx, (unsigned)q); };
-  auto BR = [&](int q) { if constexpr (STAGE) return lbr[q]; else return cld(d.brow, (unsigned)q); };
+  auto BR = [&](int q) { if constexpr (STAGE) return lbr[q]; else return row_of(cld(d.brow, (unsigned)q)); };
   auto FPH = [&](int q) { if constexpr (STAGE) return lfp[q]; else return cld(d.fph, (unsigned)q); };
   auto BPH = [&](int q) { if constexpr (STAGE) return lbp[q]; else return cld(d.bph, (unsigned)q); };
 

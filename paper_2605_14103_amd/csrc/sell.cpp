@@ -68,7 +68,7 @@ void upload_sell(Context* ctx, const SellHost& h, bool cplx, SellBuffers& b) {
 }
 
 std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const std::vector<SellRow>& rows,
-                                                           PSellBuffers& b, bool cplx) {
+                                                           PSellBuffers& b, bool cplx, PSellValues values) {
   const int ns = (int)rows.size() / SLICE;
   std::vector<int> off(ns), width(ns);
   int cur = 0;
@@ -100,28 +100,20 @@ std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const s
   b.off = upload(ctx, off);
   b.width = upload(ctx, width);
   b.col = upload(ctx, col);
-  if (cplx) {
-    std::vector<double> v64(2 * val.size());
-    std::vector<float> v32(2 * val.size());
-    for (size_t i = 0; i < val.size(); ++i) {
-      const size_t p = psell_at<double2>(i), q = psell_at<float2>(i);
-      v64[2 * p] = val[i];
-      v64[2 * p + 1] = vim[i];
-      v32[2 * q] = (float)val[i];
-      v32[2 * q + 1] = (float)vim[i];
+  const size_t parts = cplx ? 2 : 1;
+  std::vector<double> v64(values != PSELL_FP32 ? parts * val.size() : 0);
+  std::vector<float> v32(values != PSELL_FP64 ? parts * val.size() : 0);
+  for (size_t i = 0; i < val.size(); ++i) {
+    const size_t p = cplx ? psell_at<double2>(i) : psell_at<double>(i);
+    const size_t q = cplx ? psell_at<float2>(i) : psell_at<float>(i);
+    for (size_t c = 0; c < parts; ++c) {
+      const double v = c ? vim[i] : val[i];
+      if (!v64.empty()) v64[parts * p + c] = v;
+      if (!v32.empty()) v32[parts * q + c] = (float)v;
     }
-    b.val64 = upload(ctx, v64);
-    b.val32 = upload(ctx, v32);
-  } else {
-    std::vector<double> v64(val.size());
-    std::vector<float> v32(val.size());
-    for (size_t i = 0; i < val.size(); ++i) {
-      v64[psell_at<double>(i)] = val[i];
-      v32[psell_at<float>(i)] = (float)val[i];
-    }
-    b.val64 = upload(ctx, v64);
-    b.val32 = upload(ctx, v32);
   }
+  if (values != PSELL_FP32) b.val64 = upload(ctx, v64);
+  if (values != PSELL_FP64) b.val32 = upload(ctx, v32);
   return {off, width};
 }
 

@@ -106,8 +106,11 @@ struct PSellBuffers {
   template <typename V>
   PSell<V> view() const;
 };
+// `values`: the precisions that some kernel reads (the others take no memory).
 // Returns the slices' group offsets and widths (as uploaded).
+enum PSellValues { PSELL_BOTH, PSELL_FP64, PSELL_FP32 };
 std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const std::vector<SellRow>& rows,
-                                                           PSellBuffers& b, bool cplx = false);
+                                                           PSellBuffers& b, bool cplx = false,
+                                                           PSellValues values = PSELL_BOTH);
 
 }  // namespace pfx

@@ -89,7 +89,7 @@ struct DirectDev {
   const int4* ftg;   // (target, first contribution, end, 1 for a right-hand-side target)
   const int4* fct;   // (L entry, U entry or right-hand-side index, pivot, 0)
   const int* bph;    // [n_bph + 1]
-  const int4* brow;  // (row, its first entry of sidx, end, 0)
+  const int2* brow;  // (row | its entries << 16, its first entry of sidx)
   const int4* je;    // (value index | kind << 28, bus i, bus k, Ybus layout index)
 };
 

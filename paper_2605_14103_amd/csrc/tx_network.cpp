@@ -34,7 +34,7 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return E.e1[a].size() > E.e1[b].size(); });
-  auto lay_out_e1 = [&](EfBuffers::E1& f1, size_t split_row) {
+  auto lay_out_e1 = [&](EfBuffers::E1& f1, size_t split_row, PSellValues values) {
     const int n_split = (int)(std::find_if(order.begin(), order.end(), [&](int r) { return E.e1[r].size() <= split_row; }) -
                               order.begin());
     const int ns_split = (n_split + 15) / 16, ns1 = ns_split + (N - n_split + SLICE - 1) / SLICE;
@@ -51,7 +51,7 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
         ++e;
       }
     }
-    const auto [off1, width1] = upload_psell(ctx, rows1, f1.val);   // widths in groups of four entries
+    const auto [off1, width1] = upload_psell(ctx, rows1, f1.val, false, values);   // widths in groups of four entries
     // Slices to waves, for each split of the workgroup: longest first, each to
     // the least loaded wave (a wave may take any number of slices, so the one
     // with the longest slice takes few others).  Per wave, e1_nq entries; width 0
@@ -59,7 +59,7 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
     std::vector<int> sl(ns1);
     std::iota(sl.begin(), sl.end(), 0);
     std::stable_sort(sl.begin(), sl.end(), [&](int a, int b) { return width1[a] > width1[b]; });
-    for (int v = 0; v < 3; ++v) {
+    for (int v = 0; v < 3 && kb % (1 << v) == 0; ++v) {   // (no split finer than the slots)
       const int nws = nw << v;
       std::vector<int> load(nws, 0), cnt(nws, 0), owner(ns1, 0), slot(ns1, 0);
       for (int s : sl) {
@@ -86,8 +86,8 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
     return 4 * SLICE * (long)std::accumulate(width1.begin(), width1.end(), 0);   // stored entries
   };
   constexpr size_t SPLIT_ROW = 16;
-  lay_out_e1(f.e1[0], SPLIT_ROW);
-  const long padded1 = lay_out_e1(f.e1[1], (size_t)N);
+  lay_out_e1(f.e1[0], SPLIT_ROW, PSELL_FP64);
+  const long padded1 = lay_out_e1(f.e1[1], (size_t)N, PSELL_FP32);
   // E3: one row per matrix row (bus order), padded to nbp rows.
   std::vector<Row> rows3(nbp);
   for (int i = 0; i < N; ++i)
@@ -443,9 +443,9 @@ TxNetwork* tx_network_create(Context* ctx, int n_bus, int nnz, const int32_t* ro
     net->ysrc_ptr = upload(ctx, sp);
     net->ysrc_idx = upload(ctx, si);
   }
-  upload_psell(ctx, ytr, net->yt, true);
+  upload_psell(ctx, ytr, net->yt, true, PSELL_FP64);   // the transposes: the adjoint's, FP64 throughout
   upload_psell(ctx, gr, net->g);
-  upload_psell(ctx, gtr, net->gt);
+  upload_psell(ctx, gtr, net->gt, false, PSELL_FP64);
   net->int2ext_d = upload(ctx, net->int2ext);
 
   std::vector<int> bf(n_branch), bt(n_branch);
@@ -503,7 +503,7 @@ void ensure_direct(TxNetwork& net) {
   net.dl_ftg = up(D.ftg.empty() ? std::vector<int>{0, 0, 0, 0} : D.ftg);
   net.dl_fct = up(D.fct.empty() ? std::vector<int>{0, 0, 0, 0} : D.fct);
   net.dl_bph = up(D.bph);
-  net.dl_brow = up(D.brow.empty() ? std::vector<int>{0, 0, 0, 0} : D.brow);
+  net.dl_brow = up(D.brow.empty() ? std::vector<int>{0, 0} : D.brow);
   net.dl_je = up(D.je.empty() ? std::vector<int>{0, 0, 0, 0} : D.je);
   DirectDev& d = net.direct;
   d.m = D.m;
@@ -520,7 +520,7 @@ void ensure_direct(TxNetwork& net) {
   d.ftg = net.dl_ftg.as<int4>();
   d.fct = net.dl_fct.as<int4>();
   d.bph = net.dl_bph.as<int>();
-  d.brow = net.dl_brow.as<int4>();
+  d.brow = net.dl_brow.as<int2>();
   d.je = net.dl_je.as<int4>();
   net.direct_nval = D.n_val;
   net.direct_ready = true;

@@ -38,6 +38,7 @@
 
 #include "device_ops.hpp"
 #include "direct.hpp"
+#include "nr_layout.hpp"
 #include "tx.hpp"
 
 namespace pfx {
@@ -85,50 +86,6 @@ struct Shape {
     return S == 1 ? k * NW + wave_id() : (group() * KB + k) * NWV + wave_id() % NWV;
   }
 };
-
-struct NrLayout {
-  int xs, tmp, red, redn, H, cs, sn, gres, gfin, y, w, total;
-};
-
-__host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
-
-// Column j of the packed Hessenberg matrix holds rows 0..j at offset j(j+1)/2.
-__host__ __device__ inline int hcol(int j) { return j * (j + 1) / 2; }
-
-__host__ __device__ inline NrLayout nr_layout(int nbp, int nth, int npq, int kmax, int R, int NW, bool split, int ts) {
-  NrLayout L;
-  int o = 0;
-  int xs_bytes = 2 * nbp * 8;                          // V (FP64 pairs) in the mismatch
-  if (2 * nbp * ts > xs_bytes) xs_bytes = 2 * nbp * ts;  // dV pairs in the Jacobian-vector product
-  // the preconditioner's two right-hand sides and pass buffers: [0, 2 nth) and [nth, nth + npq)
-  if (2 * nth * ts > xs_bytes) xs_bytes = 2 * nth * ts;
-  if ((nth + npq) * ts > xs_bytes) xs_bytes = (nth + npq) * ts;
-  L.xs = o;
-  o += align16(xs_bytes);
-  // Reduction partials, double-buffered.  The preconditioner's dense-core
-  // right-hand side lives there too when it fits: no partial is pending while
-  // the preconditioner runs (each phase in between ends with a barrier).
-  const int red_bytes = 2 * (R + 2) * NW * 8;
-  L.red = o;  o += align16(red_bytes);
-  const int tmp_bytes = (kmax + 4 * 16 / ts) * ts;   // four parts of whole packs of the dense core
-  if (tmp_bytes <= red_bytes) {
-    L.tmp = L.red;
-  } else {
-    L.tmp = o;
-    o += align16(tmp_bytes);
-  }
-  L.redn = o; o += align16(NW * 8);   // the norm reduction after the projection
-  L.H = o;    o += align16(hcol(R) * ts);
-  L.cs = o;   o += align16(R * ts);
-  L.sn = o;   o += align16(R * ts);
-  L.gres = o; o += align16((R + 1) * ts);
-  L.gfin = o; o += align16(R * ts);
-  L.y = o;    o += align16(R * ts);
-  L.w = o;    // a split FP32 workgroup's vector for its sums
-  if (split && ts == 4) o += align16(2 * nbp * ts);
-  L.total = o;
-  return L;
-}
 
 template <typename T>
 struct Smem {
@@ -607,7 +564,8 @@ __device__ void efac_apply(const EfDev<T>& f, const T* x, T* aux, T* tmp, T (&ou
     if (t.y > 0) put(t, cld(f.e1_row, (unsigned)(t.z + lane)), pgroups_dot(f.e1, t.x, t.y, x));
   }
   // The dense core reads whole packs, in FP64 in four parts of `qn` packs: zero
-  // the core right-hand side past k.
+  // the core right-hand side past k (core_entries of nr_layout.hpp; the zeros may
+  // lie over `redn`, which nobody reads here).
   constexpr int P = 16 / (int)sizeof(T);
   const int qn = ((f.k + P - 1) / P + 3) / 4;
   if ((int)threadIdx.x < 4 * qn * P - f.k) tmp[f.k + threadIdx.x] = 0;

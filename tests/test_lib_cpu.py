@@ -256,3 +256,26 @@ def test_direct_step_allocation_agrees_with_launch(tmp_path):
         assert s == wish or (s < wish and in_lds and launched + 16 * waves * s > 163840)
         narrowed += s < wish
     assert len(lines) == 4 * 88 * 6 and narrowed > 0
+
+
+def test_solver_lds_grew_for_no_unsplit_grid(tmp_path):
+    """LDS of the Newton and adjoint kernels over every core size and restart: the core's right-hand
+    side with its zeros lies within the layout and clear of everything live beside it, and an unsplit
+    workgroup of the largest grids takes no more than the right-hand side in whole fours needs, so
+    that none is refused for the zeros."""
+    shapes = [(64, 1, 1), (256, 1, 4), (1024, 4, 4), (2048, 4, 4), (4096, 8, 2), (8192, 16, 1)]
+    code = "#include <cstdio>\n#include \"nr_layout.hpp\"\nusing namespace pfx;\nint main() {\n"
+    for nbp, waves, most in shapes:
+        code += (f"  for (int s = 1; s <= {most}; s *= 2) for (int ts = 4; ts <= 8; ts += 4)\n"
+                 "    for (int k = 0; k <= 2048; ++k) for (int R = 1; R <= 64; ++R) {\n"
+                 f"      const NrLayout L = nr_layout({nbp}, {nbp - 1}, {nbp - 1}, k, R, s * {waves}, s > 1, ts);\n"
+                 "      const int end = L.tmp + core_entries(k, ts) * ts;\n"
+                 "      // whole part within its own area (the partials', or its own), zeros before H\n"
+                 "      const bool inside = L.tmp + (k + 3) / 4 * 4 * ts <= L.redn && end <= L.H;\n"
+                 f"      int old = 16 * {nbp}, red = 16 * (R + 2) * {waves}, core = ((k ? k : 1) + 3) / 4 * 4 * ts;\n"
+                 f"      old += red + (core > red ? align16(core) : 0) + align16(8 * {waves}) + align16(R * (R + 1) / 2 * ts);\n"
+                 "      old += 4 * align16(R * ts) + align16((R + 1) * ts);\n"
+                 f"      if (!inside || (old <= 163840 && L.total > 163840) || ({waves} >= 8 && s == 1 && L.total > old))\n"
+                 f"        printf(\"{nbp} %d %d %d %d: %d, before %d, inside %d\\n\", s, ts, k, R, L.total, old, (int)inside);\n"
+                 "    }\n")
+    assert _compile_and_run(tmp_path, code + "}\n") == []

@@ -77,6 +77,7 @@ struct Shape {
   static constexpr int BLOCK = VB * S, KB = KBT / S, NW = BLOCK / WAVE, NWV = VB / WAVE;
   static constexpr unsigned NBP = (unsigned)VB * KBT;
   static constexpr int SMAX = nr_split_max(VB, KBT), U = KBT / SMAX, NU = KB / U;
+  static constexpr bool TIGHT = NU == 4 && U > 1;   // short of registers in multi_dot
   static_assert(KBT % S == 0 && SMAX % S == 0 && (KB % 2 == 0 || KB == 1), "shape");
   static __device__ __forceinline__ int group() { return S == 1 ? 0 : wave_id() / NWV; }
   static __device__ __forceinline__ unsigned col() { return S == 1 ? threadIdx.x : threadIdx.x % VB; }
@@ -1057,11 +1058,10 @@ __device__ double multi_dot(const Basis<double, Sh>& basis, int nv, const double
   constexpr int NW = Sh::NW, KB = Sh::KB, NU = Sh::NU;
   const int lane = lane_id(), slot = part_slot<Sh>();
   constexpr int G = Basis<T, Sh>::G;
-  // Two vectors per round: twice the loads in flight.  (With four units their
-  // sums for two vectors cost 31 more spilled registers: the 2000-bus batch of
-  // 1024, with three to five vectors at a time, ran 2.00 against 1.93 ms, while with the
-  // block-Jacobi preconditioner and up to thirty it gains, 73.2 -> 66.0 ms.)
-  constexpr bool TWO = NU < 4 || Sh::LONG;
+  // Two vectors per round: twice the loads in flight.  With four units of two
+  // slots (256 x 8 unsplit) their sums for two vectors cost 31 more spilled
+  // registers, which cycles of three to five steps do not win back: see long_cycles.
+  constexpr bool TWO = !Sh::TIGHT || Sh::LONG;
   auto dots = [&](int i, int i1, auto where) {
     constexpr bool L = decltype(where)::value;
     for (; TWO && i + 1 < i1; i += 2) {
@@ -2274,8 +2274,16 @@ void allow_lds(Kernel kernel, size_t lds) {
                                 (int)lds));
 }
 
-// A network whose preconditioner leaves cycles of up to `restart` Arnoldi steps.
-bool long_cycles(const TxNetwork& net) { return net.block_precond; }
+// Solves whose cycles take six Arnoldi steps and more, for which a TIGHT shape
+// forms two dot products a round: with a block-diagonal preconditioner (up to
+// the restart), or where every Newton step's system is solved to 1e-5 or below.
+// 2000 buses, 1024 scenarios, one vector a round -> two: block-Jacobi 73.2 ->
+// 65.5 ms; rtol 1e-10 4513 -> 4286 us, 1e-7 3031 -> 2959, 1e-5 2491 -> 2464, 1e-3
+// 2059 -> 2057; the adaptive default (three to four steps) 1936 -> 1972, so not there.
+// The adjoint (12 steps to 1e-10, 1615 -> 1506; 1e-4 644 -> 631) always does.
+bool long_cycles(const TxNetwork& net, const NRLaunch& a) {
+  return net.block_precond || (!a.forcing && a.rtol <= 1e-5);
+}
 
 template <class Sh>
 using Long = Shape<Sh::VB, Sh::KBT, Sh::S, true>;
@@ -2292,8 +2300,8 @@ struct NrGo {
     b.lds_vecs = lds_vectors<Sh, T>(net, a.batch, a.restart, base);
     const size_t lds = base + b.lds_vecs * 2 * Sh::NBP * sizeof(T);
     auto kernel = nr_kernel<T, Sh>;
-    if constexpr (sizeof(T) == 8 && Sh::NU == 4) {
-      if (long_cycles(net)) kernel = nr_kernel<T, Long<Sh>>;
+    if constexpr (sizeof(T) == 8 && Sh::TIGHT) {
+      if (long_cycles(net, a)) kernel = nr_kernel<T, Long<Sh>>;
     }
     allow_lds(kernel, lds);
     hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<T>(), b);
@@ -2364,10 +2372,7 @@ struct AdjGo {
     const size_t base = lds_bytes(net, Sh::S, a.restart, 8);
     b.lds_vecs = lds_vectors<Sh, double>(net, a.batch, a.restart, base);
     const size_t lds = base + b.lds_vecs * 2 * Sh::NBP * sizeof(double);
-    auto kernel = adjoint_kernel<Sh>;
-    if constexpr (Sh::NU == 4) {
-      if (long_cycles(net)) kernel = adjoint_kernel<Long<Sh>>;
-    }
+    auto kernel = adjoint_kernel<std::conditional_t<Sh::TIGHT, Long<Sh>, Sh>>;
     allow_lds(kernel, lds);
     hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(Sh::BLOCK), lds, s, net.desc<double>(), b);
     PFX_HIP(hipGetLastError());

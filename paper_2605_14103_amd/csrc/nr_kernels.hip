@@ -2438,15 +2438,21 @@ void launch_adjoint(const TxNetwork& net, const AdjLaunch& a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-constexpr int LOSS_BLOCK = 1024;
 // Branch-current loss L = sum_f |I_f|^2, I_f = (y_s + j b/2) V_f - y_s V_t,
 // and dL/dV in torch's convention conj(g), g_k = dL/dV_k (complex derivative).
 // One workgroup per scenario; the gradient is accumulated per bus by walking
 // each bus's incident branches (no atomics, fixed order).
-// (1024 threads: with 256, each walked eight buses of a 2000-bus grid one after
-// another, 47 us for 256 scenarios against 30.)
+// Bound by latency: a thread walks its buses' branches one after another, so
+// large grids take as many threads as a workgroup has; on small ones most of those
+// would only wait at the reduction.  256 / 512 / 1024 threads: 30 buses x 16384
+// scenarios 45.1 / 46.2 / 56.1 us, 118 x 4096 20.9 / 22.0 / 23.6, 256 x 4096 36.7 /
+// 36.5 / 38.5, 300 x 4096 60.9 / 58.4 / 64.8, 500 x 300 13.0 / 12.6 / 12.5, 700 x
+// 1024 26.0 / 26.1 / 27.1, 1000 x 1024 53.7 / 50.5 / 42.8, 2000 x 256 35.7 / 29.2 /
+// 28.6, 2000 x 1024 134 / 117 / 105.
+template <int LOSS_BLOCK>
 __global__ __launch_bounds__(LOSS_BLOCK) void branch_loss_kernel(const TxDev<double>* __restrict__ netp,
-                                                          const int* inc_ptr, const int* inc_br, LossLaunch a) {
+                                                                 const int* inc_ptr, const int* inc_br,
+                                                                 LossLaunch a) {
   __shared__ double red[LOSS_BLOCK / WAVE];
   const TxDev<double> net = load_desc(netp);
   const int b = blockIdx.x;
@@ -2494,8 +2500,10 @@ __global__ __launch_bounds__(LOSS_BLOCK) void branch_loss_kernel(const TxDev<dou
 
 void launch_branch_loss(const TxNetwork& net, const LossLaunch& a, hipStream_t s) {
   if (a.batch == 0) return;
-  hipLaunchKernelGGL(branch_loss_kernel, dim3(a.batch), dim3(LOSS_BLOCK), 0, s, net.desc<double>(),
-                     net.inc_ptr.as<int>(), net.inc_br.as<int>(), a);
+  const int threads = net.n <= 256 ? 256 : net.n <= 768 ? 512 : 1024;
+  auto kernel = threads == 256 ? branch_loss_kernel<256> : threads == 512 ? branch_loss_kernel<512> : branch_loss_kernel<1024>;
+  hipLaunchKernelGGL(kernel, dim3(a.batch), dim3(threads), 0, s, net.desc<double>(), net.inc_ptr.as<int>(),
+                     net.inc_br.as<int>(), a);
   PFX_HIP(hipGetLastError());
 }
 

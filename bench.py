@@ -312,24 +312,26 @@ def bench_feeder(steps: int, warmup: int, cpu: dict | None) -> dict:
     batch = fdm.make_batch(fd, cfg)
     ctx = pf.Context(0)
     net = pf.DistNetwork.from_feeder(ctx, fd)
+    loop = pf.DistNetwork.from_feeder(ctx, fdm.with_loop(fd))
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
     sw, sd = dev(batch.s_wye), dev(batch.s_delta)
     B = batch.batch
     nN = net.info["n_free"]
-    runs = {}
-    # a radial feeder is solved by path sums (zb_tree) whichever update is asked for
-    for prec, sparse, asy in (("fp64", 0, 0), ("mixed", 0, 0), ("fp64", 1, 0), ("mixed", 1, 0), ("fp64", 0, 1),
-                              ("mixed", 0, 1)):
-        key = prec + ("_sparse" if sparse else "") + ("_async" if asy else "")
-        ms, wall, out = time_steps(
-            lambda: net.solve(sw, sd, precision=pf.precision(prec), zbus_sparse=sparse, zbus_async=asy),
-            steps, warmup)
+
+    def run(which, **opts):
+        ms, wall, out = time_steps(lambda: which.solve(sw, sd, **opts), steps, warmup)
         conv = int(out.converged.sum().item())
         its = out.iters.double()
         mean_ms = float(ms.mean())
-        runs[key] = {"value": conv / (mean_ms * 1e-3), "ms_per_step": mean_ms, "converged": conv,
-                     "iters_mean": float(its.mean().item()), "max_mismatch": float(out.mismatch.max().item()),
-                     "latency_ms": {"p50": float(np.percentile(ms, 50)), "p99": float(np.percentile(ms, 99))}}
+        return {"value": conv / (mean_ms * 1e-3), "ms_per_step": mean_ms, "converged": conv,
+                "iters_mean": float(its.mean().item()), "max_mismatch": float(out.mismatch.max().item()),
+                "latency_ms": {"p50": float(np.percentile(ms, 50)), "p99": float(np.percentile(ms, 99))}}
+
+    # a radial feeder is solved by path sums (zb_tree) whichever update is asked for; the
+    # same feeder with one loop closed takes the update that the caller names
+    runs = {p: run(net, precision=pf.precision(p)) for p in ("fp64", "mixed")}
+    general = {name: {p: run(loop, precision=pf.precision(p), **opts) for p in ("fp64", "mixed")}
+               for name, opts in (("dense", {}), ("sparse", {"zbus_sparse": 1}), ("dense_async", {"zbus_async": 1}))}
     r = runs["fp64"]
     # one load power read and one voltage written per node: what a solve cannot do without
     work = float(B) * 16.0 * (nN + fd.n_node)
@@ -347,12 +349,12 @@ def bench_feeder(steps: int, warmup: int, cpu: dict | None) -> dict:
                          "basis": "load powers read once and voltages written once; the kernel keeps the whole "
                                   "iteration on the CU and is bound by instruction issue, not by HBM"},
             "fp64": runs["fp64"], "mixed": runs["mixed"],
-            "sparse_variant": {"fp64": runs["fp64_sparse"], "mixed": runs["mixed_sparse"]},
-            "async_enqueue": {"fp64": runs["fp64_async"], "mixed": runs["mixed_async"]},
+            "with_one_loop": general,
             "mixed_vs_fp64": runs["mixed"]["value"] / r["value"]}
     if cpu is not None:
         line["cpu_baseline"] = cpu
     net.close()
+    loop.close()
     ctx.close()
     return line
 
@@ -450,7 +452,8 @@ def bench_direct_sizes(steps: int, warmup: int) -> dict:
 
 
 def bench_feeder_sizes(steps: int, warmup: int) -> dict:
-    """Solve time as the radial feeder grows (batch 1024, both precisions)."""
+    """Solve time as the feeder grows (batch 1024, both precisions): radial (path sums),
+    and with one loop closed (dense product and sparse factor)."""
     import torch
 
     from paper_2605_14103_amd import pf
@@ -462,20 +465,24 @@ def bench_feeder_sizes(steps: int, warmup: int) -> dict:
         cfg = fdm.FeederConfig(f"feeder{n_bus}", n_bus=n_bus, max_depth=25, batch=1024, seed=n_bus)
         fd = fdm.make_feeder(cfg)
         batch = fdm.make_batch(fd, cfg)
-        t0 = time.perf_counter()
-        net = pf.DistNetwork.from_feeder(ctx, fd)
-        setup_s = time.perf_counter() - t0
         sw, sd = dev(batch.s_wye), dev(batch.s_delta)
-        for prec in ("fp64", "mixed"):
-            ms, _, out = time_steps(lambda: net.solve(sw, sd, precision=pf.precision(prec)), steps, warmup)
-            conv = int(out.converged.sum().item())
-            rows.append({"workload": cfg.name, "free_nodes": net.info["n_free"], "batch": cfg.batch,
-                         "update": "path sums", "precision": prec,
-                         "ms": float(ms.mean()), "solves_per_s": conv / (float(ms.mean()) * 1e-3),
-                         "converged": conv, "iters_mean": float(out.iters.double().mean().item()),
-                         "setup_s": setup_s})
-            print(f"[sizes] {cfg.name} nN={net.info['n_free']} {prec} {ms.mean():.3f} ms", file=sys.stderr, flush=True)
-        net.close()
+        for shape, updates in ((fd, ("path sums",)), (fdm.with_loop(fd), ("dense", "sparse"))):
+            t0 = time.perf_counter()
+            net = pf.DistNetwork.from_feeder(ctx, shape)
+            setup_s = time.perf_counter() - t0
+            for update in updates:
+                for prec in ("fp64", "mixed"):
+                    ms, _, out = time_steps(lambda: net.solve(sw, sd, precision=pf.precision(prec),
+                                                              zbus_sparse=int(update == "sparse")), steps, warmup)
+                    conv = int(out.converged.sum().item())
+                    rows.append({"workload": shape.name, "free_nodes": net.info["n_free"], "batch": cfg.batch,
+                                 "update": update, "precision": prec,
+                                 "ms": float(ms.mean()), "solves_per_s": conv / (float(ms.mean()) * 1e-3),
+                                 "converged": conv, "iters_mean": float(out.iters.double().mean().item()),
+                                 "setup_s": setup_s})
+                    print(f"[sizes] {shape.name} nN={net.info['n_free']} {update} {prec} {ms.mean():.3f} ms",
+                          file=sys.stderr, flush=True)
+            net.close()
     ctx.close()
     best = max(r["solves_per_s"] for r in rows if r["workload"] == "feeder300" and r["precision"] == "fp64")
     return {"metric": METRIC, "value": best, "unit": "solves/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
@@ -660,11 +667,13 @@ def counters_run(workload: str) -> dict:
         batch = fdm.make_batch(fd, fdm.FEEDER300)
         net = pf.DistNetwork.from_feeder(ctx, fd)
         sw, sd = dev(batch.s_wye), dev(batch.s_delta)
-        for sparse in (0, 1):
+        loop = pf.DistNetwork.from_feeder(ctx, fdm.with_loop(fd))
+        for name, which, sparse in (("radial", net, 0), ("dense", loop, 0), ("sparse", loop, 1)):
             for prec in ("fp64", "mixed"):
-                res = net.solve(sw, sd, precision=pf.precision(prec), zbus_sparse=sparse)
+                res = which.solve(sw, sd, precision=pf.precision(prec), zbus_sparse=sparse)
                 torch.cuda.synchronize()
-                out[prec + ("_sparse" if sparse else "")] = {"iters": res.iters.cpu().numpy().tolist()[:4]}
+                out[f"{name}_{prec}"] = {"iters": res.iters.cpu().numpy().tolist()[:4]}
+        loop.close()
     else:
         from workloads import transmission as tx
         cfg = {"tx2000": tx.TX2000, "tx30": tx.TX30}[workload]
@@ -762,8 +771,8 @@ def _sub(line: dict) -> dict:
 def all_configs(a) -> dict:
     """The other configurations of the method, each timed as its own line
     would be, so that one default run measures them all: the 30-bus grid
-    (batch 64), the 900-node feeder (batch 4096, each option that a caller can
-    set; all take the path sums), the adjoint (2000-bus, batch 256) and the serving
+    (batch 64), the 900-node feeder (batch 4096; radial, and with one loop by
+    each update that a caller can choose), the adjoint (2000-bus, batch 256) and the serving
     mix at full and half load."""
     out = {}
     for key, fn in (("tx30_b64", lambda: bench_tx("TX30", a.steps, a.warmup, a.sub_cpu.get("tx30"))),

@@ -178,7 +178,11 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
   }
   const int nb = (int)order.size();
   if (nb != nbus - 1) return;
-  int waves = 16;   // of the numbers that zb_tree is built for, the least that fits
+  // Of the numbers that zb_tree is built for, the least that fits.  A CU holds 16
+  // waves of its registers (12 for 6 and 10), and a number left out would put no more
+  // workgroups there than the next one that is built: two for 7 as for 8, one for 9 as
+  // for 10, and so on.
+  int waves = 16;
   for (int w : {13, 10, 8, 6, 5, 4, 3, 2, 1})
     if (64 * w >= nb) waves = w;
   const int nbp = 64 * waves, none = 64 * (waves | 1);

@@ -47,7 +47,10 @@ namespace {
 
 // a b + c, rounded once: in FP64, products and sums are written with it wherever
 // more than one way of fusing them exists, so that every shape computes the
-// same bits.  (In FP32 they are left as the compiler fuses them.)
+// same bits.  With FP32 inner solves (there also in the FP64 mismatch) and in the
+// direct step's Jacobian entries they are left as the compiler fuses them: that the
+// shapes agree there is what tests/test_gpu_tx_split.py finds with this compiler, not
+// a property of the source.
 __device__ __forceinline__ float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -637,15 +640,16 @@ __device__ void efac_apply(const EfDev<T>& f, const T* x, T* aux, T* tmp, T (&ou
     }
   } else {
     // lanes 16 p .. 16 p + 15 take part p of sixteen rows (the lanes of a quad
-    // read one line: with a part per lane of a quad, this pass took 4 times as long)
+    // read one line: with a part per lane of a quad, this pass took 17 k cycles
+    // against 10 k, by clock reads placed around the phases in a copy of the kernel)
     const int part = lane / 16;
     for (int i0 = wv * 16; i0 < f.k; i0 += Sh::NW * 16) {
       const int i = i0 + lane % 16;
       T acc = 0;
       if (i < f.k) {
         // rounds of eight; past the last pack the last one again, not added (a
-        // tail of single loads took up to seven more round trips: 10 k cycles of 60 k
-        // per Arnoldi step of a split 2000-bus scenario, now 5 k)
+        // tail of single loads took up to seven more round trips: 10 k of the 60 k cycles
+        // of a split 2000-bus scenario's Arnoldi step, now 5 k)
         for (int l = 0; l < qn; l += 8) {
           int4 v[8];
 #pragma unroll
@@ -2240,8 +2244,14 @@ struct ShapeOf {
 // scenarios per CU only more waves of the same one can overlap them: unsplit
 // against split, 2000 buses with per-scenario Ybus values, batch 200 1.67 ->
 // 0.99 ms; a training step of 256 2.12 -> 1.22 ms; 118 buses, batch 1000, mixed
-// 204 -> 135 us.  Once the unsplit waves fill the CUs (2000 buses, batch 1024)
-// the split ones would only queue.
+// 204 -> 135 us.  Past that room split waves queue.  Twice the waves against this
+// rule (us): 118 buses, batch 4096, 436 -> 546 (mixed 334 -> 452); 300 x 600 362 -> 429;
+// 1000 x 768 591 -> 692; 2000 x 300 866 -> 1012, x 513 1273 -> 1299, x 768 1472 -> 1593
+// (mixed 971 -> 1219), x 1024 mixed 1255 -> 1490.  The one size that gains is the full
+// FP64 batch of 2000 x 1024 (1937 -> 1803), which the rule leaves out.
+// The rule looks at its own launch only.  Three solves of 2000 buses at once on three
+// streams, unsplit -> split, us for all three: 64 scenarios each 1154 -> 582, 200 each
+// 1402 -> 1222, 256 each 1591 -> 1563.
 int nr_split(const TxNetwork& net, int batch) {
   const int64_t room = 16 * (int64_t)net.ctx->cu_count, waves = (int64_t)batch * (net.block / WAVE);
   return waves * 4 <= room ? 4 : waves * 2 <= room ? 2 : 1;

@@ -32,7 +32,8 @@ struct Sell {
 // consecutive addresses.  (With a lane's values side by side instead, four
 // lanes of a complex FP64 load touch two lines, and the address unit takes
 // twice as long: the Jacobian-vector product of the 2000-bus grid took 29 k
-// cycles against 24 k with four scenarios per CU.)  Offsets and widths count
+// cycles against 24 k with four scenarios per CU, by clock reads in a copy of
+// the kernel.)  Offsets and widths count
 // groups; padding entries have column 0 and value 0.  Entry
 // p of that row is entry number 4 (off[s] + 64 (p / 4) + l) + p % 4, with its value
 // at psell_at of that number.

@@ -85,6 +85,10 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
     f1.row = upload(ctx, rid);
     return 4 * SLICE * (long)std::accumulate(width1.begin(), width1.end(), 0);   // stored entries
   };
+  // Rows from 8, 16 and 32 entries on over four lanes, and none (us): 118 buses,
+  // batch 1024, 137 / 142 / 152 / 152; 500 x 300 336 / 337 / 349 / 375; 1000 x 200 285 / 285 /
+  // 297 / 315; 2000 x 200 538 / 539 / 536 / 589; 4000 x 64 1180 / 1187 / 1183 / 1288; within
+  // 1 % of each other at 2000 x 1024.
   constexpr size_t SPLIT_ROW = 16;
   lay_out_e1(f.e1[0], SPLIT_ROW, PSELL_FP64);
   const long padded1 = lay_out_e1(f.e1[1], (size_t)N, PSELL_FP32);

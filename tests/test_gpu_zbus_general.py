@@ -2,8 +2,6 @@
 feeders with one closed loop, which the tree form does not take: row and column
 tiles, the residual's slot templates, device-side exits, iteration caps, isolation of
 bad scenarios and the serving engine's steps, against the CPU oracle."""
-import dataclasses
-
 import numpy as np
 import pytest
 
@@ -28,13 +26,7 @@ def ctx():
 
 
 def _looped(cfg):
-    """The config's feeder with one more segment, between its two last buses that are not joined."""
-    fd = fdm.make_feeder(cfg)
-    a, c = next((a, c) for c in range(fd.n_bus - 1, 0, -1) for a in range(c - 1, 0, -1)
-                if fd.parent[c] != a and fd.parent[a] != c)
-    return dataclasses.replace(fd, seg_from=np.append(fd.seg_from, a).astype(np.int32),
-                               seg_to=np.append(fd.seg_to, c).astype(np.int32),
-                               z_seg=np.concatenate([fd.z_seg, fd.z_seg[:1]]))
+    return fdm.with_loop(fdm.make_feeder(cfg))
 
 
 def _register(ctx, fd):

@@ -22,7 +22,7 @@ For a delta bus with nodes (a, b, c), ``s_delta[a]``, ``s_delta[b]`` and
 """
 from __future__ import annotations
 
-from dataclasses import dataclass, field
+from dataclasses import dataclass, field, replace
 
 import numpy as np
 
@@ -140,6 +140,16 @@ def make_feeder(cfg: FeederConfig) -> Feeder:
     return Feeder(n_bus=n, parent=parent, depth=depth, seg_from=seg_from, seg_to=seg_to,
                   z_seg=z, load_kind=load_kind, s_base_wye=s_wye, s_base_delta=s_delta,
                   v_slack=v_slack, name=cfg.name)
+
+
+def with_loop(feeder: Feeder) -> Feeder:
+    """The feeder with one more segment, which closes a loop: between the two last
+    buses that no segment joins yet (impedance of the first segment)."""
+    a, c = next((a, c) for c in range(feeder.n_bus - 1, 0, -1) for a in range(c - 1, 0, -1)
+                if feeder.parent[c] != a and feeder.parent[a] != c)
+    return replace(feeder, seg_from=np.append(feeder.seg_from, a).astype(np.int32),
+                   seg_to=np.append(feeder.seg_to, c).astype(np.int32),
+                   z_seg=np.concatenate([feeder.z_seg, feeder.z_seg[:1]]), name=feeder.name + "_loop")
 
 
 def make_batch(feeder: Feeder, cfg: FeederConfig, batch: int | None = None,

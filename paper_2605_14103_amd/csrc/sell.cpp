@@ -68,7 +68,7 @@ void upload_sell(Context* ctx, const SellHost& h, bool cplx, SellBuffers& b) {
 }
 
 std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const std::vector<SellRow>& rows,
-                                                           PSellBuffers& b, bool cplx, PSellValues values) {
+                                                           PSellBuffers& b, bool cplx, PSellParts parts) {
   const int ns = (int)rows.size() / SLICE;
   std::vector<int> off(ns), width(ns);
   int cur = 0;
@@ -97,23 +97,25 @@ std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const s
     }
   b.n_slices = ns;
   b.entries = entries;
-  b.off = upload(ctx, off);
-  b.width = upload(ctx, width);
+  if (parts.slices) {
+    b.off = upload(ctx, off);
+    b.width = upload(ctx, width);
+  }
   b.col = upload(ctx, col);
-  const size_t parts = cplx ? 2 : 1;
-  std::vector<double> v64(values != PSELL_FP32 ? parts * val.size() : 0);
-  std::vector<float> v32(values != PSELL_FP64 ? parts * val.size() : 0);
+  const size_t per = cplx ? 2 : 1;
+  std::vector<double> v64(parts.fp64 ? per * val.size() : 0);
+  std::vector<float> v32(parts.fp32 ? per * val.size() : 0);
   for (size_t i = 0; i < val.size(); ++i) {
     const size_t p = cplx ? psell_at<double2>(i) : psell_at<double>(i);
     const size_t q = cplx ? psell_at<float2>(i) : psell_at<float>(i);
-    for (size_t c = 0; c < parts; ++c) {
+    for (size_t c = 0; c < per; ++c) {
       const double v = c ? vim[i] : val[i];
-      if (!v64.empty()) v64[parts * p + c] = v;
-      if (!v32.empty()) v32[parts * q + c] = (float)v;
+      if (parts.fp64) v64[per * p + c] = v;
+      if (parts.fp32) v32[per * q + c] = (float)v;
     }
   }
-  if (values != PSELL_FP32) b.val64 = upload(ctx, v64);
-  if (values != PSELL_FP64) b.val32 = upload(ctx, v32);
+  if (parts.fp64) b.val64 = upload(ctx, v64);
+  if (parts.fp32) b.val32 = upload(ctx, v32);
   return {off, width};
 }
 

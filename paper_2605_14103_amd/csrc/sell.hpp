@@ -107,11 +107,14 @@ struct PSellBuffers {
   template <typename V>
   PSell<V> view() const;
 };
-// `values`: the precisions that some kernel reads (the others take no memory).
+// `parts`: what some kernel reads (the rest takes no memory and no copy); without
+// `slices` the kernel has the offsets and widths from lists of its own.
 // Returns the slices' group offsets and widths (as uploaded).
-enum PSellValues { PSELL_BOTH, PSELL_FP64, PSELL_FP32 };
+struct PSellParts {
+  bool fp64 = true, fp32 = true, slices = true;
+};
 std::pair<std::vector<int>, std::vector<int>> upload_psell(Context* ctx, const std::vector<SellRow>& rows,
                                                            PSellBuffers& b, bool cplx = false,
-                                                           PSellValues values = PSELL_BOTH);
+                                                           PSellParts parts = {});
 
 }  // namespace pfx

@@ -97,14 +97,31 @@ struct EfBuffers {
   ExplicitFactor host;
   bool direct = false;
   PSellBuffers inv;
+  // Lists for each split of the workgroup, one after the other in `lists` (each
+  // from entry at[v] on), then row ids from entry `row` on: one allocation, since
+  // a small grid's registration is mostly allocations.
+  struct Lists {
+    DeviceBuffer lists;
+    int at[3] = {0, 0, 0}, row = 0;
+    void add(std::vector<int>& all, int v, const std::vector<int>& list) {
+      at[v] = (int)all.size();
+      all.insert(all.end(), list.begin(), list.end());
+    }
+    void finish(Context* ctx, std::vector<int>& all, const std::vector<int>& rows) {
+      row = (int)all.size();
+      all.insert(all.end(), rows.begin(), rows.end());
+      lists = upload(ctx, all);
+    }
+  };
   struct E1 {
     PSellBuffers val;
-    DeviceBuffer row, wave[3];
+    Lists by_wave;
     int nq[3] = {0, 0, 0};
   };
   E1 e1[2];   // for the FP64 and the FP32 kernels
   PSellBuffers e3, e3s;
-  DeviceBuffer e3s_row, e3s_pos[3], sinv64, sinv32;
+  Lists e3s_by_wave;
+  DeviceBuffer sinv64, sinv32;
   template <typename T>
   EfDev<T> view() const;
 };

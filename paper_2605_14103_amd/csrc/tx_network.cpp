@@ -34,7 +34,7 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return E.e1[a].size() > E.e1[b].size(); });
-  auto lay_out_e1 = [&](EfBuffers::E1& f1, size_t split_row, PSellValues values) {
+  auto lay_out_e1 = [&](EfBuffers::E1& f1, size_t split_row, PSellParts parts) {
     const int n_split = (int)(std::find_if(order.begin(), order.end(), [&](int r) { return E.e1[r].size() <= split_row; }) -
                               order.begin());
     const int ns_split = (n_split + 15) / 16, ns1 = ns_split + (N - n_split + SLICE - 1) / SLICE;
@@ -51,7 +51,7 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
         ++e;
       }
     }
-    const auto [off1, width1] = upload_psell(ctx, rows1, f1.val, false, values);   // widths in groups of four entries
+    const auto [off1, width1] = upload_psell(ctx, rows1, f1.val, false, parts);   // widths in groups of four entries
     // Slices to waves, for each split of the workgroup: longest first, each to
     // the least loaded wave (a wave may take any number of slices, so the one
     // with the longest slice takes few others).  Per wave, e1_nq entries; width 0
@@ -59,6 +59,7 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
     std::vector<int> sl(ns1);
     std::iota(sl.begin(), sl.end(), 0);
     std::stable_sort(sl.begin(), sl.end(), [&](int a, int b) { return width1[a] > width1[b]; });
+    std::vector<int> all;
     for (int v = 0; v < 3 && kb % (1 << v) == 0; ++v) {   // (no split finer than the slots)
       const int nws = nw << v;
       std::vector<int> load(nws, 0), cnt(nws, 0), owner(ns1, 0), slot(ns1, 0);
@@ -80,9 +81,9 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
         e[3] = s < ns_split ? 1 : 0;
       }
       f1.nq[v] = nq1;
-      f1.wave[v] = upload(ctx, wave_list);
+      f1.by_wave.add(all, v, wave_list);
     }
-    f1.row = upload(ctx, rid);
+    f1.by_wave.finish(ctx, all, rid);
     return 4 * SLICE * (long)std::accumulate(width1.begin(), width1.end(), 0);   // stored entries
   };
   // Rows from 8, 16 and 32 entries on over four lanes, and none (us): 118 buses,
@@ -90,8 +91,8 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
   // 297 / 315; 2000 x 200 538 / 539 / 536 / 589; 4000 x 64 1180 / 1187 / 1183 / 1288; within
   // 1 % of each other at 2000 x 1024.
   constexpr size_t SPLIT_ROW = 16;
-  lay_out_e1(f.e1[0], SPLIT_ROW, PSELL_FP64);
-  const long padded1 = lay_out_e1(f.e1[1], (size_t)N, PSELL_FP32);
+  lay_out_e1(f.e1[0], SPLIT_ROW, {true, false, false});
+  const long padded1 = lay_out_e1(f.e1[1], (size_t)N, {false, true, false});
   // E3: one row per matrix row (bus order), padded to nbp rows.
   std::vector<Row> rows3(nbp);
   for (int i = 0; i < N; ++i)
@@ -115,7 +116,8 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
       for (auto [p, v] : E.e3[E.pinv[ord[q]]]) rows3s[q].push_back({p, v, 0.0});
       rid3[q] = ord[q];
     }
-    const auto [off3, width3] = upload_psell(ctx, rows3s, f.e3s);
+    const auto [off3, width3] = upload_psell(ctx, rows3s, f.e3s, false, {true, true, false});
+    std::vector<int> all;
     for (int v = 0; v < 3 && kb % (1 << v) == 0; ++v) {
       const int nws = nw << v, kbs = kb >> v;
       std::vector<int> load3(nws, 0), cnt3(nws, 0), pos((size_t)nws * kbs * 4, 0);
@@ -132,10 +134,10 @@ void upload_factor(Context* ctx, EfBuffers& f, int block, int kb, int nbp) {
       // (positions without a slice: width 0, the rows of none)
       for (size_t q = 0; q < pos.size(); q += 4)
         if (pos[q + 1] == 0) pos[q + 2] = ns * SLICE;
-      f.e3s_pos[v] = upload(ctx, pos);
+      f.e3s_by_wave.add(all, v, pos);
     }
     rid3.resize((size_t)(ns + 1) * SLICE, -1);
-    f.e3s_row = upload(ctx, rid3);
+    f.e3s_by_wave.finish(ctx, all, rid3);
   }
   // With no core, A^-1 = E3 E1 (times the permutation) may stay sparse: if its
   // sliced rows are not much longer than E1's and E3's together, it is
@@ -247,15 +249,15 @@ EfDev<T> EfBuffers::view() const {
   d.k = host.k;
   const E1& f1 = e1[f64 ? 0 : 1];
   d.e1 = f1.val.view<T>();
-  d.e1_row = f1.row.as<int>();
+  d.e1_row = f1.by_wave.lists.as<int>() + f1.by_wave.row;
   for (int v = 0; v < 3; ++v) {
-    d.e1_wave[v] = f1.wave[v].as<int>();
+    d.e1_wave[v] = f1.by_wave.lists.as<int>() + f1.by_wave.at[v];
     d.e1_nq[v] = f1.nq[v];
-    d.e3s_pos[v] = e3s_pos[v].as<int>();
+    d.e3s_pos[v] = e3s_by_wave.lists.as<int>() + e3s_by_wave.at[v];
   }
   d.e3 = e3.view<T>();
   d.e3s = e3s.view<T>();
-  d.e3s_row = e3s_row.as<int>();
+  d.e3s_row = e3s_by_wave.lists.as<int>() + e3s_by_wave.row;
   d.sinv = f64 ? sinv64.as<T>() : sinv32.as<T>();
   d.direct = direct ? 1 : 0;
   d.inv = direct ? inv.view<T>() : PSell<T>{nullptr, nullptr, nullptr, nullptr};
@@ -447,9 +449,9 @@ TxNetwork* tx_network_create(Context* ctx, int n_bus, int nnz, const int32_t* ro
     net->ysrc_ptr = upload(ctx, sp);
     net->ysrc_idx = upload(ctx, si);
   }
-  upload_psell(ctx, ytr, net->yt, true, PSELL_FP64);   // the transposes: the adjoint's, FP64 throughout
+  upload_psell(ctx, ytr, net->yt, true, {true, false, true});   // the transposes: the adjoint's, FP64 throughout
   upload_psell(ctx, gr, net->g);
-  upload_psell(ctx, gtr, net->gt, false, PSELL_FP64);
+  upload_psell(ctx, gtr, net->gt, false, {true, false, true});
   net->int2ext_d = upload(ctx, net->int2ext);
 
   std::vector<int> bf(n_branch), bt(n_branch);

@@ -314,8 +314,9 @@ pf_status pf_dist_ybus_from_segments(int32_t n_bus, int32_t n_seg, const int32_t
  * the no-load voltage v0 = -Z Y_NS v_S (Sec. II-B, eq. (10)) in FP64, keeps Z
  * in FP64 and FP32 on the device.  A tree without shunts (nodes 3 b, 3 b + 1,
  * 3 b + 2 the phases of bus b, at most 1024 buses below the slack, symmetric
- * segments, row sums of Ybus zero up to rounding, each delta load on one bus
- * in phase order) needs no Z: its segments' 3x3 impedances are kept instead,
+ * segments, row sums of Ybus zero up to rounding, largest segment admittance
+ * times largest path impedance below 1e7, each delta load on one bus in phase
+ * order) needs no Z: its segments' 3x3 impedances are kept instead,
  * and v0 is the slack voltage.  setup_opts may be null.
  * Errors: PF_INVALID_ARG, PF_SINGULAR_SETUP, PF_OUT_OF_MEMORY, PF_HIP_ERROR. */
 pf_status pf_dist_network_create(pf_context* ctx, int32_t n_node, int32_t nnz, const int32_t* row_ptr,

@@ -80,6 +80,14 @@ std::array<cplx, 6> invert_sym3(const std::array<cplx, 6>& m) {
   return {A / det, (a * c - f * f) / det, (a * b - d * d) / det, D / det, (d * f - a * e) / det, F / det};
 }
 
+// Largest admittance of a segment times largest impedance of a path from the
+// slack (largest entries of the 3x3 blocks), up to which the tree form is taken.
+// It bounds what the rounding of Ybus does to Z, and the general form's set-up
+// refuses a feeder once that passes 1e-8 (PF_SINGULAR_SETUP): among 60 random trees
+// with segments shortened step by step, never below 3e7.  Past this line that
+// set-up decides, rather than solves which cannot reach their tolerance.
+constexpr double TREE_STIFFNESS = 1e7;
+
 // Tree form of a feeder (TreeDev), if it is one: nodes 3 b, 3 b + 1, 3 b + 2
 // are bus b's phases, the slack is one bus in phase order, each delta load sits on one bus in
 // phase order, Ybus joins buses in a tree, every block off the diagonal is
@@ -89,7 +97,7 @@ std::array<cplx, 6> invert_sym3(const std::array<cplx, 6>& m) {
 // parts by themselves and allows each a unit in the last place of the sum per
 // neighbour: a caller's sum in any order rounds by half of that, and a shunt
 // beside a stiff segment (a closed switch) is dropped only where the diagonal
-// entry could not have held it.
+// entry could not have held it.  Nor may the feeder be too stiff (TREE_STIFFNESS).
 // Otherwise the network keeps the forms for a general Y_NN.
 void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const int32_t* col_idx, const double* y_re,
                 const double* y_im, const std::vector<uint8_t>& wye,
@@ -188,7 +196,8 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
   const int nbp = 64 * waves, none = 64 * (waves | 1);
   std::vector<int> bus(4 * (size_t)nbp, 0), link(4 * (size_t)nbp, none | none << 16), more, ev(nbp, 0);
   std::vector<int> rest(2 * (size_t)nbp, 0), kids(nbp / 64, 0);
-  std::vector<double> y(12 * (size_t)nbp, 0.0), z(12 * (size_t)nbp, 0.0);
+  std::vector<double> y(12 * (size_t)nbp, 0.0), z(12 * (size_t)nbp, 0.0), path(nb, 0.0);
+  double y_max = 0.0, path_max = 0.0;
   for (int q = 0; q < nb; ++q) {
     const int b = order[q], f = free_of(b);
     int flags = 0;
@@ -217,6 +226,13 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
         for (int k = 0; k < 3; ++k) e += ys[at3[i][k]] * zs[at3[k][j]];
         if (!(std::abs(e) <= 1e-10)) return;   // (nearly) singular segment
       }
+    double z_max = 0.0;
+    for (int k = 0; k < 6; ++k) {
+      y_max = std::max(y_max, std::abs(ys[k]));
+      z_max = std::max(z_max, std::abs(zs[k]));
+    }
+    path[q] = z_max + (parent[b] == s ? 0.0 : path[pos[parent[b]]]);
+    path_max = std::max(path_max, path[q]);
     for (int k = 0; k < 6; ++k) {
       const size_t o = 2 * ((size_t)k * nbp + q);
       y[o] = ys[k].real();
@@ -225,6 +241,7 @@ void build_tree(Context* ctx, DistNetwork& net, const int32_t* row_ptr, const in
       z[o + 1] = zs[k].imag();
     }
   }
+  if (!(y_max * path_max <= TREE_STIFFNESS)) return;
   for (int e = 0; e < 2 * nbp; ++e) {
     const bool real = e < 2 * nb;
     const int q = !real ? nb : pos[event[e] >= 0 ? event[e] : ~event[e]];

@@ -221,6 +221,21 @@ def test_unsymmetric_feeders_stay_refused(change):
     assert e.value.status == L.PF_SINGULAR_SETUP
 
 
+@pytest.mark.parametrize("z", [1e-12, 1e-14])
+def test_too_stiff_feeders_stay_refused(z):
+    """Segments so short beside the others that the admittance matrix's rounding alone exceeds the
+    solver's tolerance are reported when the feeder is registered, as for the general form, and not
+    by solves that never converge."""
+    from paper_2605_14103_amd import _lib as L
+    f = Case(30)
+    f.Y[:] = 0
+    for k, (a, c) in enumerate(f.segments):
+        f.add_segment(a, c, z / 0.01 * f.z[k] if k % 5 == 4 else f.z[k])
+    with pytest.raises(L.PfError) as e:
+        f.solve()
+    assert e.value.status == L.PF_SINGULAR_SETUP
+
+
 @pytest.mark.parametrize("b_shunt", [2e-7, 0.0])
 def test_small_shunt_behind_a_closed_switch(b_shunt):
     """A closed switch (1e-7 pu) with 2e-7 pu of charging behind it, no load: the shunt lies far

@@ -645,10 +645,13 @@ __global__ __launch_bounds__(ZB_THREADS) void zb_finish(DistDev net, ZbusLaunch 
 // barriers per iteration; HBM is touched for the loads and the result only.
 // Against this, the general forms pay two launches, a read-back and a pass of
 // v and r through HBM per iteration, and a dense product or a few hundred
-// dependent factor levels.  Measured against them, 300 buses: one scenario 1222
-// -> 27 us, 4096 scenarios 2852 (dense) -> 312 us, 1000 in mixed precision 1038
-// -> 95 us; 600 buses, 1024 scenarios 1059 (sparse factor) -> 190 us.  So it is
-// taken for every such feeder.  (All components scanned in every wave: 29, 352, 107 and 212 us.)
+// dependent factor levels.  Measured against them (calls back to back on the same
+// loads; with new loads each call 4096 scenarios take 321 us), 300 buses: one
+// scenario 1222 -> 27 us, 4096 scenarios 2852 (dense) -> 309 us, 1000 in mixed
+// precision 1038 -> 95 us; 600 buses, 1024 scenarios 1059 (sparse factor) -> 190 us.
+// Stars and chains gain as well (600 in a star, 1024 scenarios, sparse factor 301 ->
+// 103 us; in a chain 171 -> 2.3 ms), and so do 10 buses x 65536 (2.6 -> 0.33 ms).  So it
+// is taken for every such feeder.  (All components scanned in every wave: 29, 352, 107 and 212 us.)
 //
 // STEP: an engine's step (a.slots): v, the statistics and the flags come from
 // and go back to the slot's state, `steps` residuals at most; otherwise the
